@@ -244,7 +244,7 @@ int choose_plan_uncached(const sv_gate *g, int G, int n, int dtype, int precisio
     return SV_OK;
 }
 
-int pauli_tables(sv_state *s, const sv_pauli_sum *H, dev::PauliDev &P);
+int pauli_tables(sv_state *s, const sv_pauli_sum *H, int n, dev::PauliDev &P);
 
 }  // namespace
 
@@ -685,14 +685,14 @@ int read_result(sv_state *s, const double *d_src, size_t count, double *out)
 
 size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Group terms by x mask, stage the tables and upload them into the arena.
+// Group the terms, stage the tables and upload them into the arena.
 // The caller synchronised arena_free and records it after its launches.
-int pauli_tables(sv_state *s, const sv_pauli_sum *H, dev::PauliDev &P)
+int pauli_tables(sv_state *s, const sv_pauli_sum *H, int n, dev::PauliDev &P)
 {
     const size_t total = pauli_table_bytes(H);
     SV_HIP(s->stage.ensure(total));
     SV_HIP(s->arena.ensure(total));
-    pauli_table_fill(H, static_cast<char *>(s->stage.p), static_cast<const char *>(s->arena.p), P);
+    pauli_table_fill(H, n, s->dtype, static_cast<char *>(s->stage.p), static_cast<const char *>(s->arena.p), P);
     SV_HIP(hipMemcpyAsync(s->arena.p, s->stage.p, total, hipMemcpyHostToDevice, s->stream));
     return SV_OK;
 }
@@ -718,45 +718,61 @@ int check_pauli(const sv_pauli_sum *H, int n)
 
 namespace {
 
-// Byte offsets of the device tables of a Pauli sum with ng x-mask groups and
-// nt terms: group masks, group offsets, term z masks, coefficients, i-powers.
+// Byte offsets of the device tables of a Pauli sum with ng groups and nt
+// terms: group masks, group offsets, term z masks, coefficients.
 struct PauliLayout {
-    size_t gx, goff, tz, tc, tp, total;
+    size_t gx, goff, tz, tc, total;
     PauliLayout(int ng, int nt)
     {
         gx = 0;
         goff = al256(gx + 8 * std::max(ng, 1));
         tz = al256(goff + 4 * (ng + 1));
         tc = al256(tz + 8 * std::max(nt, 1));
-        tp = al256(tc + 8 * std::max(nt, 1));
-        total = al256(tp + 4 * std::max(nt, 1));
+        total = al256(tc + 8 * std::max(nt, 1));
     }
 };
 
-int count_x_groups(const sv_pauli_sum *H)
+// The group of a term: its x mask and whether its weight is imaginary.
+uint64_t pauli_group(const sv_pauli_sum *H, int t)
 {
-    std::vector<uint64_t> x(H->xmask, H->xmask + H->n_terms);
+    return H->xmask[t] | (__builtin_popcountll(H->xmask[t] & H->zmask[t]) & 1 ? dev::kPauliImag : 0);
+}
+
+int count_groups(const sv_pauli_sum *H)
+{
+    std::vector<uint64_t> x(size_t(H->n_terms));
+    for (int t = 0; t < H->n_terms; ++t) x[size_t(t)] = pauli_group(H, t);
     std::sort(x.begin(), x.end());
     return int(std::unique(x.begin(), x.end()) - x.begin());
 }
 
 }  // namespace
 
-size_t pauli_table_bytes(const sv_pauli_sum *H) { return PauliLayout(count_x_groups(H), H->n_terms).total; }
+size_t pauli_table_bytes(const sv_pauli_sum *H) { return PauliLayout(count_groups(H), H->n_terms).total; }
 
-void pauli_table_fill(const sv_pauli_sum *H, char *h, const char *d, dev::PauliDev &P)
+void pauli_table_fill(const sv_pauli_sum *H, int n, int dtype, char *h, const char *d, dev::PauliDev &P)
 {
     const int nt = H->n_terms;
-    std::vector<int> order(nt);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return H->xmask[a] < H->xmask[b]; });
+    P.n_pass = dev::pauli_passes(n, dtype, P.pass_w);
+    std::vector<int> order(nt), pass(nt);
+    std::vector<uint64_t> group(nt);
+    for (int t = 0; t < nt; ++t) {
+        order[t] = t;
+        group[t] = pauli_group(H, t);
+        pass[t] = dev::pauli_pass_of(H->xmask[t], dtype, P.n_pass, P.pass_w);
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+        return pass[a] != pass[b] ? pass[a] < pass[b] : group[a] < group[b];
+    });
     std::vector<uint64_t> gx;
     std::vector<int32_t> goff;
-    for (int i = 0; i < nt; ++i) {
-        if (i == 0 || H->xmask[order[i]] != H->xmask[order[i - 1]]) {
-            gx.push_back(H->xmask[order[i]]);
-            goff.push_back(i);
-        }
+    for (int p = 0, i = 0; p < P.n_pass; ++p) {
+        for (; i < nt && pass[order[i]] == p; ++i)
+            if (gx.empty() || group[order[i]] != gx.back()) {
+                gx.push_back(group[order[i]]);
+                goff.push_back(i);
+            }
+        P.pass_end[p] = int(gx.size());
     }
     goff.push_back(nt);
     const int ng = int(gx.size());
@@ -765,16 +781,15 @@ void pauli_table_fill(const sv_pauli_sum *H, char *h, const char *d, dev::PauliD
     std::memcpy(h + L.goff, goff.data(), 4 * (ng + 1));
     for (int i = 0; i < nt; ++i) {
         const int t = order[i];
+        const bool minus = __builtin_popcountll(H->xmask[t] & H->zmask[t]) & 2;  // i^2, i^3
         reinterpret_cast<uint64_t *>(h + L.tz)[i] = H->zmask[t];
-        reinterpret_cast<double *>(h + L.tc)[i] = H->coef[t];
-        reinterpret_cast<int32_t *>(h + L.tp)[i] = __builtin_popcountll(H->xmask[t] & H->zmask[t]) & 3;
+        reinterpret_cast<double *>(h + L.tc)[i] = minus ? -H->coef[t] : H->coef[t];
     }
     P.n_groups = ng;
     P.gx = reinterpret_cast<const uint64_t *>(d + L.gx);
     P.goff = reinterpret_cast<const int32_t *>(d + L.goff);
     P.tz = reinterpret_cast<const uint64_t *>(d + L.tz);
     P.tc = reinterpret_cast<const double *>(d + L.tc);
-    P.tpow = reinterpret_cast<const int32_t *>(d + L.tp);
 }
 
 }  // namespace sv
@@ -827,7 +842,7 @@ extern "C" int sv_expectation(sv_state *s, const sv_pauli_sum *H, double *out)
     if (int rc = select_device(s)) return rc;
     SV_HIP(hipEventSynchronize(s->arena_free));
     dev::PauliDev P;
-    if (int rc = pauli_tables(s, H, P)) return rc;
+    if (int rc = pauli_tables(s, H, s->n, P)) return rc;
     double *part = static_cast<double *>(s->red.p);
     double *res = part + 2 * dev::kRedBlocks;
     {
@@ -853,7 +868,7 @@ extern "C" int sv_dm_expectation(sv_state *rho, const sv_pauli_sum *H, double *o
     if (int rc = select_device(rho)) return rc;
     SV_HIP(hipEventSynchronize(rho->arena_free));
     dev::PauliDev P;
-    if (int rc = pauli_tables(rho, H, P)) return rc;
+    if (int rc = pauli_tables(rho, H, n, P)) return rc;
     double *part = static_cast<double *>(rho->red.p);
     double *res = part + 2 * dev::kRedBlocks;
     {
@@ -1104,7 +1119,7 @@ extern "C" int sv_apply_pauli_sum(sv_state *psi, const sv_pauli_sum *H, sv_state
     if (H->n_terms == 0) {
         SV_HIP(dev::launch_fill_basis(out->dtype, out->buf, out->n, ~uint64_t(0), psi->stream));
     } else {
-        if (int rc = pauli_tables(psi, H, P)) return rc;
+        if (int rc = pauli_tables(psi, H, psi->n, P)) return rc;
         LaunchTimer t(stat_class(FAM_REDUCE, 4), psi->stream);
         SV_HIP(dev::launch_pauli_apply(psi->dtype, psi->buf, out->buf, psi->n, P, psi->stream));
     }

@@ -154,17 +154,29 @@ hipError_t launch_norm(int dtype, const void *psi, int n, double *d_partials, do
                        hipStream_t st);
 hipError_t launch_inner(int dtype_a, const void *a, int dtype_b, const void *b, int n,
                         double *d_partials, double *d_out, hipStream_t st);
-// Pauli terms grouped by x mask: group g covers terms [goff[g], goff[g+1]) all
-// with x mask gx[g]; per term the z mask, the coefficient and the power of i
-// (number of Y factors mod 4).  Device arrays.
+// Pauli terms in groups of one x mask whose weights are all real or all
+// imaginary (an even or odd number of Y factors): group g covers terms
+// [goff[g], goff[g+1]), gx[g] is its x mask, with kPauliImag set when the
+// weights are imaginary; per term the z mask and the coefficient, with the
+// sign of its power of i.  Device arrays.  The groups of pass p of the tiled
+// kernels (pauli_passes) end at pass_end[p].
+constexpr uint64_t kPauliImag = uint64_t(1) << 63;
+constexpr int kPauliMaxPasses = 5;
+constexpr int kPauliTileMin = 19;  // qubits from which the tiled kernels run
 struct PauliDev {
     int n_groups;
     const uint64_t *gx;
     const int32_t *goff;
     const uint64_t *tz;
     const double *tc;
-    const int32_t *tpow;
+    int n_pass;
+    int pass_w[kPauliMaxPasses];
+    int pass_end[kPauliMaxPasses];
 };
+// The windows (first slot bit) of the tiled kernels' passes over an n-qubit
+// state, and the first of them whose tile holds x (0 when none does).
+int pauli_passes(int n, int dtype, int *w);
+int pauli_pass_of(uint64_t x, int dtype, int n_pass, const int *w);
 hipError_t launch_pauli_expect(int dtype, const void *psi, int n, const PauliDev &H, double *d_partials,
                                double *d_out, hipStream_t st);
 hipError_t launch_pauli_apply(int dtype, const void *psi, void *out, int n, const PauliDev &H,

@@ -14,6 +14,9 @@
 // amplitude psi[i ^ x] is loaded once per group.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace sv {
@@ -110,20 +113,27 @@ __global__ void __launch_bounds__(kRedThreads) k_inner(const A *__restrict__ a, 
     block_reduce_store<2>(s, partials + 2 * blockIdx.x);
 }
 
-// weight of group g at partner index j: sum_t c_t i^{pow_t} (-1)^{popcount(j & z_t)}
-__device__ __forceinline__ void group_weight(const PauliDev &H, int g, uint64_t j, double &wr, double &wi)
+// weight of group g at partner index j: sum_t c_t (-1)^{popcount(j & z_t)}
+// (times i for a group with kPauliImag set)
+__device__ __forceinline__ double group_weight(const PauliDev &H, int g, uint64_t j)
 {
-    wr = 0.0;
-    wi = 0.0;
+    double w = 0.0;
     for (int t = H.goff[g]; t < H.goff[g + 1]; ++t) {
-        double c = H.tc[t];
-        if (__popcll(j & H.tz[t]) & 1) c = -c;
-        switch (H.tpow[t] & 3) {
-        case 0: wr += c; break;
-        case 1: wi += c; break;
-        case 2: wr -= c; break;
-        default: wi -= c; break;
-        }
+        const double c = H.tc[t];
+        w += __popcll(j & H.tz[t]) & 1 ? -c : c;
+    }
+    return w;
+}
+
+// (re, im) times w, or times i w for an imaginary group
+__device__ __forceinline__ void add_weighted(uint64_t gx, double w, double pr, double pi, double &sr, double &si)
+{
+    if (gx & kPauliImag) {
+        sr = fma(-w, pi, sr);
+        si = fma(w, pr, si);
+    } else {
+        sr = fma(w, pr, sr);
+        si = fma(w, pi, si);
     }
 }
 
@@ -132,17 +142,15 @@ __global__ void __launch_bounds__(kRedThreads) k_pauli_expect(const T *__restric
                                                              double *partials)
 {
     Acc<1> a{{0.0}};
-    for (uint64_t i = uint64_t(blockIdx.x) * kRedThreads + threadIdx.x; i < N; i += uint64_t(kRedBlocks) * kRedThreads) {
+    for (uint64_t i = uint64_t(blockIdx.x) * kRedThreads + threadIdx.x; i < N; i += uint64_t(gridDim.x) * kRedThreads) {
         double cr, ci;
         ld(psi, i, cr, ci);
         double sr = 0.0, si = 0.0;
         for (int g = 0; g < H.n_groups; ++g) {
-            const uint64_t j = i ^ H.gx[g];
-            double pr, pi, wr, wi;
+            const uint64_t j = i ^ (H.gx[g] & ~kPauliImag);
+            double pr, pi;
             ld(psi, j, pr, pi);
-            group_weight(H, g, j, wr, wi);
-            sr = fma(wr, pr, fma(-wi, pi, sr));
-            si = fma(wr, pi, fma(wi, pr, si));
+            add_weighted(H.gx[g], group_weight(H, g, j), pr, pi, sr, si);
         }
         // Re(conj(psi_i) * s)
         a.v[0] = fma(cr, sr, fma(ci, si, a.v[0]));
@@ -162,10 +170,10 @@ __global__ void __launch_bounds__(kRedThreads) k_dm_expect(const T *__restrict__
     const uint64_t N = uint64_t(1) << n;
     for (uint64_t a = uint64_t(blockIdx.x) * kRedThreads + threadIdx.x; a < N; a += uint64_t(kRedBlocks) * kRedThreads) {
         for (int g = 0; g < H.n_groups; ++g) {
-            double rr, ri, wr, wi;
-            ld(rho, (a << n) | (a ^ H.gx[g]), rr, ri);
-            group_weight(H, g, a, wr, wi);
-            acc.v[0] = fma(rr, wr, fma(-ri, wi, acc.v[0]));
+            double rr, ri;
+            ld(rho, (a << n) | (a ^ (H.gx[g] & ~kPauliImag)), rr, ri);
+            const double w = group_weight(H, g, a);
+            acc.v[0] = H.gx[g] & kPauliImag ? fma(-ri, w, acc.v[0]) : fma(rr, w, acc.v[0]);
         }
     }
     block_reduce_store<1>(acc, partials + blockIdx.x);
@@ -318,15 +326,259 @@ __global__ void __launch_bounds__(256) k_pauli_apply(const T *__restrict__ psi, 
     for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < N; i += stride) {
         double sr = 0.0, si = 0.0;
         for (int g = 0; g < H.n_groups; ++g) {
-            const uint64_t j = i ^ H.gx[g];
-            double pr, pi, wr, wi;
+            const uint64_t j = i ^ (H.gx[g] & ~kPauliImag);
+            double pr, pi;
             ld(psi, j, pr, pi);
-            group_weight(H, g, j, wr, wi);
-            sr = fma(wr, pr, fma(-wi, pi, sr));
-            si = fma(wr, pi, fma(wi, pr, si));
+            add_weighted(H.gx[g], group_weight(H, g, j), pr, pi, sr, si);
         }
         out[2 * i] = T(sr);
         out[2 * i + 1] = T(si);
+    }
+}
+
+// <psi|H|psi> and H psi over LDS tiles, for states of at least kPauliTileMin
+// qubits.
+//
+// What bounds it.  One thread per amplitude (k_pauli_expect, k_pauli_apply)
+// spends its time on a popcount, a table load and a 8-byte gather per term and
+// amplitude: 4.8 and 3.4 ms for the 26-qubit chain with 8 random strings (59
+// terms, 35 groups) where reading the state takes 0.1 ms.  Here
+//   * a tile is 2048 16-byte slots (2^12 complex64 or 2^11 complex128
+//     amplitudes, 32 KiB: several workgroups per compute unit, one loading
+//     while others compute), spanned by the lowest 3 slot bits (128-byte runs)
+//     and a window of 8 consecutive ones, so that a partner i ^ x whose x lies
+//     inside comes from LDS;
+//   * <psi|H|psi> takes one pass per window that holds groups (its sums are
+//     FP64 partials, so passes add up exactly as one would); a group that no
+//     window holds gathers its partners from memory in the first pass;
+//   * H psi is one pass (its sums must be whole when they are rounded to the
+//     amplitude type): partners outside the tile are gathered, 16 bytes a lane,
+//     and the tiles in flight on one XCD differ in the top bits, so those
+//     gathers find their lines in that XCD's L2 and the lower ones in the
+//     memory-side cache;
+//   * a thread holds R = 8 (4) amplitudes that differ in the tile's top two
+//     bits (and in position 0), so a term costs it one popcount and one add:
+//     the term goes to the bucket of its z bits on those positions, and a
+//     Walsh-Hadamard transform of the R buckets gives the R weights.  A group
+//     of one term skips the transform.
+// Measured at 26 qubits, the terms above: 1.0 and 1.33 ms (before: 4.8 and 3.4).
+template <typename T>
+struct PauliTile {
+    static constexpr int PB = sizeof(T) == 4 ? 1 : 0;  // position bits inside a 16-byte slot
+    static constexpr int R = 4 << PB;                  // amplitudes per thread
+};
+constexpr int kPauliTileThreads = 512;
+constexpr int kPauliWindow = 8;                                // window bits
+constexpr int kPauliTileSlotBits = 3 + kPauliWindow;           // 512 threads of 4 slots
+constexpr uint32_t kPauliWinMask = (1u << kPauliWindow) - 1;
+
+// the tables of dev::PauliDev
+struct PauliTables {
+    const uint64_t *gx;
+    const int32_t *goff;
+    const uint64_t *tz;
+    const double *tc;
+};
+
+// A read-only table entry through the scalar cache (uniform index).
+template <typename V>
+__device__ __forceinline__ V table(const V *p, int i)
+{
+    typedef const __attribute__((address_space(4))) V *cptr;
+    return reinterpret_cast<cptr>(reinterpret_cast<uintptr_t>(p))[i];
+}
+
+__device__ __forceinline__ double flip_sign(double v, uint32_t parity)
+{
+    return __longlong_as_double(__double_as_longlong(v) ^ (uint64_t(parity) << 63));
+}
+
+// the amplitudes of a 16-byte slot, widened
+typedef float vfloat4 __attribute__((ext_vector_type(4)));
+typedef double vdouble2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void slot_amps(vfloat4 v, double (&re)[2], double (&im)[2])
+{
+    re[0] = v.x; im[0] = v.y; re[1] = v.z; im[1] = v.w;
+}
+__device__ __forceinline__ void slot_amps(vdouble2 v, double (&re)[1], double (&im)[1])
+{
+    re[0] = v.x; im[0] = v.y;
+}
+
+template <typename T, bool APPLY>
+__global__ void __launch_bounds__(kPauliTileThreads, 4)
+    k_pauli_tile(const T *__restrict__ psi_, T *__restrict__ out_, int slot_bits, int w, int g0, int g1, const PauliTables H,
+                 double *__restrict__ partials, int add)
+{
+    using Slot = typename std::conditional<sizeof(T) == 4, vfloat4, vdouble2>::type;
+    constexpr int PB = PauliTile<T>::PB, R = PauliTile<T>::R, NA = 1 << PB;
+    __shared__ Slot X[1 << kPauliTileSlotBits];
+    const Slot *__restrict__ psi = reinterpret_cast<const Slot *>(psi_);
+    const int tid = threadIdx.x;
+    // slot bits of the tile: 0..2 and w..w+7
+    const uint64_t tile_mask = 7u | (uint64_t(kPauliWinMask) << w);
+    const uint64_t n_tiles = uint64_t(1) << (slot_bits - kPauliTileSlotBits);
+    auto in_tile = [&](uint64_t v) { return uint32_t(v & 7u) | (uint32_t(v >> w) & kPauliWinMask) << 3; };
+    const int tile_bits = slot_bits - kPauliTileSlotBits;
+    double e = 0.0;
+    for (uint64_t v = blockIdx.x; v < n_tiles; v += gridDim.x) {
+        // H psi: the 64 tiles that one XCD (v % 8) has in flight differ in the
+        // top six tile bits, the XCDs in the next three
+        uint64_t tile = v;
+        if (APPLY && tile_bits >= 9)
+            tile = ((v >> 3) & 63u) << (tile_bits - 6) | (v & 7u) << (tile_bits - 9) | v >> 9;
+        const uint64_t low = tile & ((uint64_t(1) << (w - 3)) - 1);
+        const uint64_t base = low << 3 | (tile >> (w - 3)) << (w + kPauliWindow);
+        auto slot_of = [&](int rr) {
+            const uint32_t s = uint32_t(tid) | uint32_t(rr) << 9;
+            return base | (s & 7u) | uint64_t(s >> 3) << w;
+        };
+        {
+            Slot buf[4];
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) buf[rr] = psi[slot_of(rr)];
+            __syncthreads();  // the previous tile's readers are done
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) X[tid | rr << 9] = buf[rr];
+        }
+        __syncthreads();
+        double sr[R], si[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) sr[r] = si[r] = 0.0;
+        for (int g = g0; g < g1; ++g) {
+            const uint64_t gx = table(H.gx, g);
+            const uint64_t x = gx & ~kPauliImag, xs = x >> PB;
+            const bool imag = (gx & kPauliImag) != 0, swap = PB && (x & 1u);
+            const int t0 = table(H.goff, g), t1 = table(H.goff, g + 1);
+            // a term's coefficient with its sign on this thread's amplitude r = 0
+            // and the r bits (rr, position 0) that its z masks
+            auto term = [&](uint64_t z, double c, uint32_t &zr) __attribute__((always_inline)) {
+                const uint64_t zs = z >> PB;
+                const uint32_t zl = in_tile(zs);
+                zr = (zl >> 9) << PB | (PB ? uint32_t(z & 1u) : 0u);
+                const uint32_t uni = uint32_t(__popcll(z & x) + __popcll(zs & ~tile_mask & base)) & 1u;
+                return flip_sign(c, (uni + __popc(zl & uint32_t(tid))) & 1u);
+            };
+            // adds weight(r) times the partner of amplitude r: (pr, pi), its slot
+            // neighbour where x holds position 0, times i in an imaginary group
+            auto add_all = [&](auto partner, auto weight, auto swapped, auto times_i) __attribute__((always_inline)) {
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) {
+                    double pr[NA], pi[NA];
+                    slot_amps(partner(rr), pr, pi);
+#pragma unroll
+                    for (int b = 0; b < NA; ++b) {
+                        const int r = rr << PB | b, o = decltype(swapped)::value ? NA - 1 - b : b;
+                        if constexpr (decltype(times_i)::value) {
+                            sr[r] = fma(weight(r), -pi[o], sr[r]);
+                            si[r] = fma(weight(r), pr[o], si[r]);
+                        } else {
+                            sr[r] = fma(weight(r), pr[o], sr[r]);
+                            si[r] = fma(weight(r), pi[o], si[r]);
+                        }
+                    }
+                }
+            };
+            auto accumulate = [&](auto partner, auto weight) __attribute__((always_inline)) {
+                constexpr std::true_type yes{};
+                constexpr std::false_type no{};
+                if (imag) {
+                    if (swap) add_all(partner, weight, yes, yes);
+                    else add_all(partner, weight, no, yes);
+                } else {
+                    if (swap) add_all(partner, weight, yes, no);
+                    else add_all(partner, weight, no, no);
+                }
+            };
+            auto group = [&](auto partner) __attribute__((always_inline)) {
+                if (t1 - t0 == 1) {
+                    uint32_t zr;
+                    const double c = term(table(H.tz, t0), table(H.tc, t0), zr);
+                    if (zr == 0)
+                        accumulate(partner, [&](int) { return c; });
+                    else
+                        accumulate(partner, [&](int r) { return flip_sign(c, __popc(uint32_t(r) & zr) & 1u); });
+                    return;
+                }
+                double a[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) a[r] = 0.0;
+                for (int t = t0; t < t1; t += 4) {
+                    // four terms' table entries on their way at once
+                    uint64_t z[4];
+                    double c[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int tu = t + u < t1 ? t + u : t1 - 1;
+                        z[u] = table(H.tz, tu);
+                        c[u] = table(H.tc, tu);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (t + u >= t1) break;  // uniform
+                        uint32_t zr;
+                        const double v = term(z[u], c[u], zr);
+                        // one bucket is touched: the empty statement keeps each
+                        // add behind its (uniform) branch
+#pragma unroll
+                        for (int r = 0; r < R; ++r)
+                            if (zr == uint32_t(r)) {
+                                a[r] += v;
+                                asm volatile("" : "+v"(a[r]));
+                            }
+                    }
+                }
+#pragma unroll
+                for (int h = 1; h < R; h <<= 1)
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        if (!(r & h)) {
+                            const double u = a[r], d = a[r | h];
+                            a[r] = u + d;
+                            a[r | h] = u - d;
+                        }
+                accumulate(partner, [&](int r) { return a[r]; });
+            };
+            if (xs & ~tile_mask) {  // uniform
+                Slot p[4];
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) p[rr] = psi[slot_of(rr) ^ xs];
+                group([&](int rr) { return p[rr]; });
+            } else {
+                const uint32_t at = uint32_t(tid) ^ in_tile(xs);
+                group([&](int rr) { return X[at ^ uint32_t(rr) << 9]; });
+            }
+        }
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+            if constexpr (APPLY) {
+                Slot o;
+                if constexpr (PB == 1) {
+                    o.x = T(sr[2 * rr]); o.y = T(si[2 * rr]); o.z = T(sr[2 * rr + 1]); o.w = T(si[2 * rr + 1]);
+                } else {
+                    o.x = sr[rr]; o.y = si[rr];
+                }
+                reinterpret_cast<Slot *>(out_)[slot_of(rr)] = o;
+            } else {
+                double cr[NA], ci[NA];
+                slot_amps(X[tid | rr << 9], cr, ci);
+#pragma unroll
+                for (int b = 0; b < NA; ++b)  // Re(conj(psi_i) (H psi)_i)
+                    e = fma(cr[b], sr[rr << PB | b], fma(ci[b], si[rr << PB | b], e));
+            }
+        }
+    }
+    if constexpr (!APPLY) {
+        __shared__ double sh[kPauliTileThreads / 64];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o, 64);
+        if ((tid & 63) == 0) sh[tid >> 6] = e;
+        __syncthreads();
+        if (tid == 0) {
+            double v = add ? partials[blockIdx.x] : 0.0;
+            for (int i = 0; i < kPauliTileThreads / 64; ++i) v += sh[i];
+            partials[blockIdx.x] = v;
+        }
     }
 }
 
@@ -379,16 +631,80 @@ hipError_t launch_inner(int dtype_a, const void *a, int dtype_b, const void *b, 
     return hipGetLastError();
 }
 
+namespace {
+
+unsigned pauli_tile_grid(int slot_bits, unsigned cap)
+{
+    const uint64_t tiles = uint64_t(1) << (slot_bits - kPauliTileSlotBits);
+    return unsigned(tiles < cap ? tiles : cap);
+}
+
+template <typename T>
+hipError_t pauli_expect_t(const T *psi, int n, const PauliDev &H, double *d_partials, double *d_out, hipStream_t st)
+{
+    unsigned blocks;
+    if (n >= kPauliTileMin) {
+        const int slot_bits = n - PauliTile<T>::PB;
+        blocks = pauli_tile_grid(slot_bits, kRedBlocks);
+        int add = 0;
+        for (int p = 0; p < H.n_pass; ++p) {
+            if (H.pass_end[p] == (p ? H.pass_end[p - 1] : 0)) continue;
+            hipLaunchKernelGGL((k_pauli_tile<T, false>), dim3(blocks), dim3(kPauliTileThreads), 0, st, psi,
+                               static_cast<T *>(nullptr), slot_bits, H.pass_w[p], p ? H.pass_end[p - 1] : 0,
+                               H.pass_end[p], PauliTables{H.gx, H.goff, H.tz, H.tc}, d_partials, add);
+            add = 1;
+        }
+    } else {
+        const uint64_t N = uint64_t(1) << n, b = (N + kRedThreads - 1) / kRedThreads;
+        blocks = unsigned(b < kRedBlocks ? b : kRedBlocks);
+        hipLaunchKernelGGL(k_pauli_expect<T>, dim3(blocks), dim3(kRedThreads), 0, st, psi, N, H, d_partials);
+    }
+    hipLaunchKernelGGL(k_final<1>, dim3(1), dim3(kRedThreads), 0, st, d_partials, int(blocks), d_out);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t pauli_apply_t(const T *psi, T *out, int n, const PauliDev &H, hipStream_t st)
+{
+    if (n >= kPauliTileMin) {
+        const int slot_bits = n - PauliTile<T>::PB;
+        hipLaunchKernelGGL((k_pauli_tile<T, true>), dim3(pauli_tile_grid(slot_bits, 512)), dim3(kPauliTileThreads), 0, st,
+                           psi, out, slot_bits, 3, 0, H.n_groups, PauliTables{H.gx, H.goff, H.tz, H.tc},
+                           static_cast<double *>(nullptr), 0);
+    } else {
+        const uint64_t N = uint64_t(1) << n;
+        hipLaunchKernelGGL(k_pauli_apply<T>, dim3(unsigned((N + 255) / 256)), dim3(256), 0, st, psi, out, N, H);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+int pauli_passes(int n, int dtype, int *w)
+{
+    if (n < kPauliTileMin) {
+        w[0] = 3;
+        return 1;
+    }
+    const int slot_bits = n - (dtype == SV_C64 ? 1 : 0);
+    int p = 0;
+    for (int at = 3; p == 0 || at < slot_bits; at += kPauliWindow) w[p++] = std::min(at, slot_bits - kPauliWindow);
+    return p;
+}
+
+int pauli_pass_of(uint64_t x, int dtype, int n_pass, const int *w)
+{
+    const uint64_t xs = dtype == SV_C64 ? x >> 1 : x;
+    for (int p = 0; p < n_pass; ++p)
+        if (!(xs & ~(uint64_t(7) | uint64_t(kPauliWinMask) << w[p]))) return p;
+    return 0;
+}
+
 hipError_t launch_pauli_expect(int dtype, const void *psi, int n, const PauliDev &H, double *d_partials,
                                double *d_out, hipStream_t st)
 {
-    const uint64_t N = uint64_t(1) << n;
-    if (dtype == SV_C64)
-        hipLaunchKernelGGL(k_pauli_expect<float>, dim3(kRedBlocks), dim3(kRedThreads), 0, st, static_cast<const float *>(psi), N, H, d_partials);
-    else
-        hipLaunchKernelGGL(k_pauli_expect<double>, dim3(kRedBlocks), dim3(kRedThreads), 0, st, static_cast<const double *>(psi), N, H, d_partials);
-    hipLaunchKernelGGL(k_final<1>, dim3(1), dim3(kRedThreads), 0, st, d_partials, kRedBlocks, d_out);
-    return hipGetLastError();
+    if (dtype == SV_C64) return pauli_expect_t(static_cast<const float *>(psi), n, H, d_partials, d_out, st);
+    return pauli_expect_t(static_cast<const double *>(psi), n, H, d_partials, d_out, st);
 }
 
 hipError_t launch_dm_expect(int dtype, const void *rho, int n, const PauliDev &H, double *d_partials, double *d_out,
@@ -451,16 +767,8 @@ hipError_t launch_kraus_probs(int dtype, const void *psi, int n, const KrausDev 
 
 hipError_t launch_pauli_apply(int dtype, const void *psi, void *out, int n, const PauliDev &H, hipStream_t st)
 {
-    const uint64_t N = uint64_t(1) << n;
-    uint64_t blocks = (N + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
-    if (dtype == SV_C64)
-        hipLaunchKernelGGL(k_pauli_apply<float>, dim3(unsigned(blocks)), dim3(256), 0, st, static_cast<const float *>(psi),
-                           static_cast<float *>(out), N, H);
-    else
-        hipLaunchKernelGGL(k_pauli_apply<double>, dim3(unsigned(blocks)), dim3(256), 0, st, static_cast<const double *>(psi),
-                           static_cast<double *>(out), N, H);
-    return hipGetLastError();
+    if (dtype == SV_C64) return pauli_apply_t(static_cast<const float *>(psi), static_cast<float *>(out), n, H, st);
+    return pauli_apply_t(static_cast<const double *>(psi), static_cast<double *>(out), n, H, st);
 }
 
 hipError_t launch_sum_partials(const double *d_partials, int n_slots, double *d_out, hipStream_t st)
