@@ -910,40 +910,255 @@ int kraus_weights(sv_state *s, const KrausSet &ks, double *p)
     return read_result(s, res, size_t(ks.n_ops), p);
 }
 
-// Draw one Kraus operator with probability p_i / sum p by the uniform u and
-// apply K_i / sqrt(p_i).  The first i whose running sum exceeds u * sum p is
-// taken (zero-weight operators are never taken).
-int sample_kraus(sv_state *s, const sv_super_op &op, double u, int32_t *chosen, double *p_chosen)
+// The draw: the first operator of nonzero weight whose running sum exceeds
+// u * sum p (zero-weight operators are never taken).
+int pick_kraus(const double *p, int n_ops, double u, int *pick, double *total)
 {
-    KrausSet ks;
-    if (int rc = kraus_canonical(op, s->n, ks)) return rc;
-    double p[kMaxKrausOps];
-    if (int rc = kraus_weights(s, ks, p)) return rc;
-    double total = 0.0;
-    for (int i = 0; i < ks.n_ops; ++i) total += p[i];
-    if (!(total > 0.0) || !std::isfinite(total)) return fail(SV_ERR_ARG, "Kraus outcome weights sum to %g", total);
-    int pick = -1;
+    double sum = 0.0;
+    for (int i = 0; i < n_ops; ++i) sum += p[i];
+    if (!(sum > 0.0) || !std::isfinite(sum)) return fail(SV_ERR_ARG, "Kraus outcome weights sum to %g", sum);
+    *pick = -1;
+    *total = sum;
     double run = 0.0;
-    for (int i = 0; i < ks.n_ops; ++i) {
+    for (int i = 0; i < n_ops; ++i) {
         run += p[i];
-        if (p[i] > 0.0) pick = i;  // the last nonzero one, should rounding leave u * total above every sum
-        if (p[i] > 0.0 && u * total < run) break;
+        if (p[i] > 0.0) *pick = i;  // the last nonzero one, should rounding leave u * total above every sum
+        if (p[i] > 0.0 && u * sum < run) break;
     }
-    const size_t D = size_t(1) << ks.k;
-    const double scale = 1.0 / std::sqrt(p[pick]);
-    std::vector<double> m(2 * D * D);
-    for (size_t e = 0; e < 2 * D * D; ++e) m[e] = ks.abi[2 * D * D * pick + e] * scale;
-    sv_gate h{};
-    h.kind = SV_G_MATRIX;
-    h.k = ks.k;
-    h.param = -1;
-    for (int a = 0; a < ks.k; ++a) h.q[a] = ks.q[a];
-    h.m = m.data();
-    if (int rc = apply_gate_impl(s, &h)) return rc;
-    if (chosen) *chosen = pick;
-    if (p_chosen) *p_chosen = p[pick] / total;
     return SV_OK;
 }
+
+// Channels sampled one after another on a state, with no gates in between.
+//
+// Where K_i^dagger K_i is diagonal for every operator of a channel (damping,
+// dephasing, Pauli channels, projective measurement), the outcome weights
+// depend on the probabilities of its qubits' basis values only.  One pass
+// (launch_weighted_bins) then gives the joint probabilities of up to kMaxBins
+// qubits, from which the outcomes of all channels on them are drawn in order;
+// and a drawn operator need not be applied before the next pass, which weights
+// each amplitude by diag(K^dagger K) / p of it instead, as long as the channels
+// act on distinct qubits.  The drawn operators are applied together, as gates,
+// by flush() or with the gates that follow them (take()).  Other channels run
+// one by one: their weights (kraus_weights), then their operator.
+class KrausSampler {
+  public:
+    explicit KrausSampler(sv_state *s) : s_(s) { clear_weights(); }
+
+    // Channel j of `count` with uniform u[j]: its outcome into picks[j] and
+    // the outcome's probability into probs[j] (either may be NULL).
+    int run(const KrausSet *ks, int count, const double *u, int32_t *picks, double *probs)
+    {
+        for (int j = 0; j < count;) {
+            int end = j, bits = 0;
+            uint64_t used = pending_mask_;
+            for (; end < count; ++end) {
+                bool flat = true;
+                uint64_t mask = 0;
+                for (int i = 0; i < ks[end].k; ++i) mask |= uint64_t(1) << ks[end].q[i];
+                if ((mask & used) || !diagonal(ks[end], &flat)) break;
+                if (!flat && bits + ks[end].k > dev::kMaxBins) break;
+                if (!flat) bits += ks[end].k;
+                used |= mask;
+            }
+            if (end > j && weights_factor_) {
+                if (int rc = draw_group(ks + j, end - j, u + j, picks ? picks + j : nullptr, probs ? probs + j : nullptr)) return rc;
+                j = end;
+                continue;
+            }
+            if (!pending_.empty()) {  // the next channel needs the state itself
+                if (int rc = flush()) return rc;
+                continue;
+            }
+            double p[kMaxKrausOps], total = 0.0;
+            int pick = -1;
+            if (int rc = kraus_weights(s_, ks[j], p)) return rc;
+            if (int rc = pick_kraus(p, ks[j].n_ops, u[j], &pick, &total)) return rc;
+            add_pending(ks[j], pick, p[pick]);
+            if (int rc = flush()) return rc;
+            if (picks) picks[j] = pick;
+            if (probs) probs[j] = p[pick] / total;
+            ++j;
+        }
+        return SV_OK;
+    }
+
+    // Qubits of the widest drawn operator (0 when there is none).
+    int widest() const
+    {
+        int k = 0;
+        for (const Pending &p : pending_) k = std::max(k, p.k);
+        return k;
+    }
+
+    // Applies the drawn operators, fused, in the state's own arithmetic.
+    int flush()
+    {
+        if (pending_.empty()) return SV_OK;
+        std::vector<sv_gate> g;
+        std::vector<std::vector<double>> keep;
+        take(g, keep);
+        if (g.size() == 1) return apply_gate_impl(s_, g.data());
+        sv_run_opts o;
+        o.max_k = 4;
+        o.precision = s_->dtype == SV_C64 ? SV_PREC_FP32 : SV_PREC_FP64;
+        o.rule = s_->dtype == SV_C64 && s_->n >= dev::kMinTileQubits ? SV_RULE_TILED : SV_RULE_ENHANCED;
+        o.use_graph = 0;
+        return run_circuit_impl(s_, g.data(), int(g.size()), &o);
+    }
+
+    // The drawn operators as gates (matrices in `keep`), for a caller that
+    // applies them before anything else reads the state.
+    void take(std::vector<sv_gate> &g, std::vector<std::vector<double>> &keep)
+    {
+        for (Pending &p : pending_) {
+            sv_gate h{};
+            h.kind = SV_G_MATRIX;
+            h.k = p.k;
+            h.param = -1;
+            for (int a = 0; a < p.k; ++a) h.q[a] = p.q[a];
+            keep.push_back(std::move(p.m));
+            h.m = keep.back().data();
+            g.push_back(h);
+        }
+        pending_.clear();
+        pending_mask_ = 0;
+        clear_weights();
+    }
+
+  private:
+    struct Pending {
+        int k;
+        int q[3];
+        std::vector<double> m;
+    };
+
+    void clear_weights()
+    {
+        for (auto &w : w_) w[0] = w[1] = 1.0;
+        scale_ = 1.0;
+        weights_factor_ = true;
+    }
+
+    // diag(K_i^dagger K_i) of operator i (ABI order)
+    static void diag_of(const KrausSet &ks, int i, double *d)
+    {
+        const int D = 1 << ks.k;
+        const double *m = ks.abi.data() + size_t(2) * D * D * i;
+        for (int c = 0; c < D; ++c) {
+            d[c] = 0.0;
+            for (int r = 0; r < D; ++r) d[c] += m[2 * (r * D + c)] * m[2 * (r * D + c)] + m[2 * (r * D + c) + 1] * m[2 * (r * D + c) + 1];
+        }
+    }
+
+    // K_i^dagger K_i diagonal for every i: no two columns of K_i meet in a row.
+    // *flat: it is a multiple of the identity for every i.
+    static bool diagonal(const KrausSet &ks, bool *flat)
+    {
+        const int D = 1 << ks.k;
+        *flat = true;
+        for (int i = 0; i < ks.n_ops; ++i) {
+            const double *m = ks.abi.data() + size_t(2) * D * D * i;
+            for (int r = 0; r < D; ++r) {
+                int filled = 0;
+                for (int c = 0; c < D; ++c) filled += m[2 * (r * D + c)] != 0.0 || m[2 * (r * D + c) + 1] != 0.0;
+                if (filled > 1) return false;
+            }
+            double d[8];
+            diag_of(ks, i, d);
+            for (int c = 1; c < D; ++c) *flat = *flat && d[c] == d[0];
+        }
+        return true;
+    }
+
+    void add_pending(const KrausSet &ks, int pick, double p)
+    {
+        const size_t D = size_t(1) << ks.k;
+        const double scale = 1.0 / std::sqrt(p);
+        Pending x;
+        x.k = ks.k;
+        for (int a = 0; a < 3; ++a) x.q[a] = ks.q[a];
+        x.m.resize(2 * D * D);
+        for (size_t e = 0; e < 2 * D * D; ++e) x.m[e] = ks.abi[2 * D * D * size_t(pick) + e] * scale;
+        for (int a = 0; a < ks.k; ++a) pending_mask_ |= uint64_t(1) << ks.q[a];
+        pending_.push_back(std::move(x));
+    }
+
+    int draw_group(const KrausSet *ks, int count, const double *u, int32_t *picks, double *probs)
+    {
+        // the qubits whose values matter, in the order of their channels (the
+        // first channel's first qubit on the top bit of the joint index)
+        int order[dev::kMaxBins], pos[dev::kMaxBins], m = 0;
+        for (int j = 0; j < count; ++j) {
+            bool flat;
+            diagonal(ks[j], &flat);
+            for (int a = 0; a < ks[j].k && !flat; ++a) order[m++] = ks[j].q[a];
+        }
+        std::copy(order, order + m, pos);
+        std::sort(pos, pos + m);
+        if (int rc = select_device(s_)) return rc;
+        SV_HIP(s_->red.ensure(dev::weighted_bins_bytes(s_->n, pos, m)));
+        SV_HIP(s_->red_host.ensure(sizeof(double) << m));
+        const double *bins = static_cast<const double *>(s_->red_host.p);
+        {
+            LaunchTimer t(stat_class(FAM_REDUCE, 6), s_->stream);
+            SV_HIP(dev::launch_weighted_bins(s_->dtype, s_->buf, s_->n, pos, m, w_, scale_,
+                                             static_cast<double *>(s_->red.p), static_cast<double *>(s_->red_host.p),
+                                             s_->stream));
+        }
+        SV_HIP(hipStreamSynchronize(s_->stream));
+        // joint probabilities by channel order; channel by channel its top bits
+        // are summed out with the drawn operator's weights
+        std::vector<double> P(size_t(1) << m);
+        for (size_t v = 0; v < P.size(); ++v) {
+            size_t b = 0;
+            for (int i = 0; i < m; ++i)
+                if ((v >> (m - 1 - i)) & 1) b |= size_t(1) << (std::lower_bound(pos, pos + m, order[i]) - pos);
+            P[v] = bins[b];
+        }
+        for (int j = 0; j < count; ++j) {
+            bool flat;
+            diagonal(ks[j], &flat);
+            const size_t D = flat ? 1 : size_t(1) << ks[j].k, rest = P.size() / D;
+            double S[8], p[kMaxKrausOps], d[8], total = 0.0;
+            for (size_t t = 0; t < D; ++t) {
+                S[t] = 0.0;
+                for (size_t r = 0; r < rest; ++r) S[t] += P[t * rest + r];
+            }
+            for (int i = 0; i < ks[j].n_ops; ++i) {
+                diag_of(ks[j], i, d);
+                p[i] = 0.0;
+                for (size_t t = 0; t < D; ++t) p[i] += d[t] * S[t];
+            }
+            int pick = -1;
+            if (int rc = pick_kraus(p, ks[j].n_ops, u[j], &pick, &total)) {
+                const std::string msg = last_error_cstr();
+                (void)flush();  // the channels before it have acted
+                return fail(rc, "%s", msg.c_str());
+            }
+            diag_of(ks[j], pick, d);
+            for (size_t r = 0; r < rest; ++r) {
+                double v = 0.0;
+                for (size_t t = 0; t < D; ++t) v += d[t] / p[pick] * P[t * rest + r];
+                P[r] = v;
+            }
+            P.resize(rest);
+            if (flat) scale_ *= d[0] / p[pick];
+            else if (ks[j].k == 1) w_[ks[j].q[0]][0] = d[0] / p[pick], w_[ks[j].q[0]][1] = d[1] / p[pick];
+            else weights_factor_ = false;  // not a product over qubits: applied before the next pass
+            add_pending(ks[j], pick, p[pick]);
+            if (picks) picks[j] = pick;
+            if (probs) probs[j] = p[pick] / total;
+        }
+        return SV_OK;
+    }
+
+    sv_state *s_;
+    std::vector<Pending> pending_;
+    uint64_t pending_mask_ = 0;
+    double w_[SV_MAX_QUBITS_C64][2];  // weights of the pending operators by qubit value
+    double scale_;                    // and of those that are multiples of a unitary
+    bool weights_factor_;
+};
 
 }  // namespace
 
@@ -966,7 +1181,11 @@ extern "C" int sv_apply_kraus_sampled(sv_state *s, const sv_super_op *op, double
     if (int rc = check_state(s)) return rc;
     if (!op) return fail(SV_ERR_ARG, "NULL operator");
     if (!(u >= 0.0 && u < 1.0)) return fail(SV_ERR_ARG, "uniform %g outside [0, 1)", u);
-    return sample_kraus(s, *op, u, chosen, p_chosen);
+    KrausSet ks;
+    if (int rc = kraus_canonical(*op, s->n, ks)) return rc;
+    KrausSampler sampler(s);
+    if (int rc = sampler.run(&ks, 1, &u, chosen, p_chosen)) return rc;
+    return sampler.flush();
 }
 
 extern "C" int sv_run_trajectory(sv_state *s, const sv_gate *g, int G, const sv_super_op *ops, int n_ops,
@@ -976,28 +1195,45 @@ extern "C" int sv_run_trajectory(sv_state *s, const sv_gate *g, int G, const sv_
     if (int rc = check_state(s)) return rc;
     if (int rc = validate_gates(g, G, s->n)) return rc;
     if (n_ops < 0 || (n_ops && (!ops || !uniforms))) return fail(SV_ERR_ARG, "NULL operator or uniform array");
+    std::vector<KrausSet> ks(static_cast<size_t>(n_ops));
     for (int j = 0; j < n_ops; ++j) {
-        KrausSet ks;
-        if (int rc = kraus_canonical(ops[j], s->n, ks)) return rc;
+        if (int rc = kraus_canonical(ops[j], s->n, ks[size_t(j)])) return rc;
         if (ops[j].after < 0 || ops[j].after > G || (j && ops[j].after < ops[j - 1].after))
             return fail(SV_ERR_ARG, "operator %d: after = %d out of order (0..%d, nondecreasing)", j, ops[j].after, G);
         if (!(uniforms[j] >= 0.0 && uniforms[j] < 1.0))
             return fail(SV_ERR_ARG, "uniform %d = %g outside [0, 1)", j, uniforms[j]);
     }
-    int done = 0;
-    for (int j = 0; j <= n_ops; ++j) {
+    // Drawn operators join the gates that follow them where those are fused;
+    // split FP16 takes only unitary gates, and an unfused run would give each
+    // operator a pass of its own.
+    const bool join = o && o->rule != SV_RULE_NONE && o->precision != SV_PREC_SPLIT_FP16;
+    KrausSampler sampler(s);
+    for (int j = 0, done = 0;;) {
         const int upto = j < n_ops ? ops[j].after : G;
         if (upto > done) {
-            if (int rc = run_circuit_impl(s, g + done, upto - done, o)) return rc;
+            std::vector<sv_gate> part;
+            std::vector<std::vector<double>> keep;
+            if (join && (o->max_k < 0 || o->max_k >= sampler.widest())) sampler.take(part, keep);
+            else if (int rc = sampler.flush()) return rc;
+            if (part.empty()) {
+                if (int rc = run_circuit_impl(s, g + done, upto - done, o)) return rc;
+            } else {
+                part.insert(part.end(), g + done, g + upto);
+                if (int rc = run_circuit_impl(s, part.data(), int(part.size()), o)) return rc;
+            }
             done = upto;
         }
-        if (j < n_ops) {
-            int32_t pick = -1;
-            if (int rc = sample_kraus(s, ops[j], uniforms[j], &pick, nullptr)) return rc;
-            if (outcomes) outcomes[j] = pick;
-        }
+        if (j == n_ops) break;
+        int end = j;
+        while (end < n_ops && ops[end].after == upto) ++end;
+        std::vector<int32_t> picks(size_t(end - j), -1);
+        const int rc = sampler.run(ks.data() + j, end - j, uniforms + j, picks.data(), nullptr);
+        for (int i = 0; outcomes && i < end - j; ++i)
+            if (picks[size_t(i)] >= 0) outcomes[j + i] = picks[size_t(i)];
+        if (rc) return rc;
+        j = end;
     }
-    return SV_OK;
+    return sampler.flush();
 }
 
 // ============================================================== projections, measurement, control
@@ -1054,8 +1290,7 @@ extern "C" int sv_measure(sv_state *s, int k, const int32_t *q, const double *un
     // qubit by qubit: the Kraus set {|0><0|, |1><1|} sampled with uniforms[j]
     static const double proj[16] = {1, 0, 0, 0, 0, 0, 0, 0,   // |0><0|
                                     0, 0, 0, 0, 0, 0, 1, 0};  // |1><1|
-    uint64_t out = 0;
-    double ptot = 1.0;
+    std::vector<KrausSet> ks(static_cast<size_t>(k));
     for (int j = 0; j < k; ++j) {
         sv_super_op op{};
         op.after = 0;
@@ -1063,11 +1298,18 @@ extern "C" int sv_measure(sv_state *s, int k, const int32_t *q, const double *un
         op.q[0] = q[j];
         op.n_left = op.n_right = 2;
         op.left = op.right = proj;
-        int32_t b = 0;
-        double pb = 0.0;
-        if (int rc = sample_kraus(s, op, uniforms[j], &b, &pb)) return rc;
-        out = (out << 1) | uint64_t(b);
-        ptot *= pb;
+        if (int rc = kraus_canonical(op, s->n, ks[size_t(j)])) return rc;
+    }
+    std::vector<int32_t> b(static_cast<size_t>(k));
+    std::vector<double> pb(static_cast<size_t>(k));
+    KrausSampler sampler(s);
+    if (int rc = sampler.run(ks.data(), k, uniforms, b.data(), pb.data())) return rc;
+    if (int rc = sampler.flush()) return rc;
+    uint64_t out = 0;
+    double ptot = 1.0;
+    for (int j = 0; j < k; ++j) {
+        out = (out << 1) | uint64_t(b[size_t(j)]);
+        ptot *= pb[size_t(j)];
     }
     if (bits) *bits = out;
     if (prob) *prob = ptot;

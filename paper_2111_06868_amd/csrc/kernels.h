@@ -195,6 +195,14 @@ struct KrausDev {
 // holds kRedBlocks * kMaxKraus doubles).
 hipError_t launch_kraus_probs(int dtype, const void *psi, int n, const KrausDev &K, double *d_partials,
                               double *d_out, hipStream_t st);
+// out[v], v < 2^m: scale sum over the amplitudes whose bits on the m ascending
+// positions are v (bit j of v on pos[j]) of |psi_i|^2 prod_p w[p][bit p of i], in
+// FP64 (out may be pinned host memory; d_partials: weighted_bins_bytes).  The
+// one-amplitude loads of complex64 come in pairs: its n is at least 1.
+constexpr int kMaxBins = 10;
+size_t weighted_bins_bytes(int n, const int *pos, int m);
+hipError_t launch_weighted_bins(int dtype, const void *psi, int n, const int *pos, int m, const double (*w)[2],
+                                double scale, double *d_partials, double *out, hipStream_t st);
 // Tr(rho H) of rho (n qubits) held row-major in a state of 2n qubits.
 hipError_t launch_dm_expect(int dtype, const void *rho, int n, const PauliDev &H, double *d_partials, double *d_out,
                             hipStream_t st);

@@ -11,6 +11,14 @@ from oracle import ref
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    yield
+    torch.cuda.synchronize()
+
+
 def _terms(n, rng):
     terms = [(0.5, ()), (-0.25, ((0, "Y"),)), (0.75, ((n - 1, "Y"), (0, "X")))]
     terms += [(float(rng.normal()), ((i, "Z"), (i + 1, "Z"))) for i in range(n - 1)]
