@@ -57,7 +57,9 @@ extern "C" {
 #define SV_C128 1
 
 /* arithmetic used to apply fused blocks (sv_run_opts.precision) */
-#define SV_PREC_FP32 0       /* complex64 state; FP32 matvec / FP32 MFMA           */
+#define SV_PREC_FP32 0       /* complex64 state; FP32 matvec / FP32 MFMA; tile     */
+                             /* passes as SV_PREC_SPLIT_BF16X3 (closer to 64-bit   */
+                             /* values than FP32 MFMA)                             */
 #define SV_PREC_SPLIT_BF16 1 /* complex64 state; k>=4 blocks as hi+lo BF16 MFMA    */
 #define SV_PREC_SPLIT_FP16 2 /* complex64 state; k>=4 blocks as hi+lo FP16 MFMA;   */
                              /* MATRIX gates must be unitary (to 1e-6), else       */
@@ -265,7 +267,7 @@ int sv_apply_plan(sv_state *s, const sv_plan *p, int precision, int use_graph);
  * pass is fused into blocks of <= 4 qubits
  * (gates move only where every qubit keeps its own gate order).  Each tile
  * of 2^14 (or 2^13) amplitudes is staged in LDS once, every block of the
- * pass is applied to it (SV_PREC_FP32: FP32 MFMA; SV_PREC_SPLIT_BF16 /
+ * pass is applied to it (SV_PREC_FP32: as SV_PREC_SPLIT_BF16X3; SV_PREC_SPLIT_BF16 /
  * SV_PREC_SPLIT_FP16: hi+lo 16-bit MFMA, the FP16 values scaled by a power of
  * two, chosen per tile from its largest magnitude in the call's first FP16
  * pass and per pass from the state's norm, which that pass measures, in the

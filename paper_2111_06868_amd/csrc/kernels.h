@@ -35,7 +35,7 @@ hipError_t launch_mfma_f32(int k, const int *sorted_q, const float *d_a, void *p
 // true: two parts, d_parts[2] unused) bit patterns.
 hipError_t launch_mfma_split(int k, bool fp16, const int *sorted_q, const uint16_t *const *d_parts, void *psi,
                              int n, hipStream_t st, int tc_log, int grid_cap);
-// Multi-block tile passes (complex64, FP32 or split BF16 / FP16 MFMA): up to
+// Multi-block tile passes (complex64, split BF16 / FP16 MFMA): up to
 // tile_max_blocks() 4-qubit blocks whose positions have a union of at most
 // tile_bits positions, applied in one HBM pass over tiles of
 // 2^tile_bits amplitudes held by workgroups of `waves` waves; shapes
@@ -56,12 +56,12 @@ struct TileArgs {
     uint32_t swz[kMaxTileBits];        // LDS index of each tile bit (XOR-linear placement)
 };
 // Tile-pass operand of one 4-qubit block (canonical 16 x 16 matrix m), in
-// kTileOperandWords 32-bit words: FP32: Re U then Im U (16 x 16 floats each,
-// row-major); split BF16 (both BF16 codes): three parts of U (part p =
-// RNE(U - parts before it)), split FP16: two parts, 256 words each, one word
-// per entry holding (re, im) as 16-bit values (re in the low half); unused
-// words are 0.  The precision codes are also the tile passes' arithmetic:
-// kTileOperandBF16X3 splits the tile values into three parts instead of two.
+// kTileOperandWords 32-bit words: FP32 and both BF16 codes: three BF16 parts
+// of U (part p = RNE(U - parts before it)), split FP16: two parts, 256 words
+// each, one word per entry holding (re, im) as 16-bit values (re in the low
+// half); unused words are 0.  The precision codes are also the tile passes'
+// arithmetic: kTileOperandF32 and kTileOperandBF16X3 split the tile values into
+// three parts instead of two.
 constexpr int kTileOperandWords = 768;
 constexpr int kTileOperandF32 = 0, kTileOperandBF16 = 1, kTileOperandF16 = 2, kTileOperandBF16X3 = 3;
 void pack_tile_operand(const cd *m, int prec, uint32_t *out);

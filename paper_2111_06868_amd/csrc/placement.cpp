@@ -70,8 +70,7 @@ void search_swizzle(TileArgs &a, int tile_bits, int lane_shift)
 {
     uint32_t best[kMaxTileBits], cand[kMaxTileBits];
     for (int b = 0; b < tile_bits; ++b) best[b] = (1u << b) ^ (((1u << b) >> 4) & 0x1Eu);
-    // FP32 passes (lane_shift < 0: 4-byte accesses, MFMA-bound) keep the first
-    int bc = lane_shift < 0 ? 0 : placement_conflicts(best, a, tile_bits, lane_shift);
+    int bc = placement_conflicts(best, a, tile_bits, lane_shift);
     uint64_t x = 0x9E3779B97F4A7C15ull;
     for (int t = 0; t < 2048 && bc > 0; ++t) {
         for (int b = 0; b < tile_bits; ++b) {
@@ -120,18 +119,19 @@ void choose_swizzle(TileArgs &a, int tile_bits, int lane_shift)
 
 }  // namespace
 
-// Lanes of a wave take columns l32 NBW + q (split) or l32 (FP32), so a lane
-// group's columns differ from column bit log2(NBW) (split) or 0 up.  FP32
-// passes (4-byte accesses, MFMA-bound) keep the first candidate.
+// Lanes of a wave take columns l32 NBW + q, so a lane group's columns differ
+// from column bit log2(NBW) up (in every precision).
 void choose_tile_placement(TileArgs &a, int tile_bits, int waves, int prec)
 {
+    (void)prec;
     const int nbw = (1 << (tile_bits - 9)) / waves;
-    choose_swizzle(a, tile_bits, prec == kTileOperandF32 ? -1 : __builtin_ctz(unsigned(nbw)));
+    choose_swizzle(a, tile_bits, __builtin_ctz(unsigned(nbw)));
 }
 
 int tile_placement_conflicts(const TileArgs &a, int tile_bits, int waves, int prec)
 {
-    if (prec == kTileOperandF32 || waves <= 0) return 0;
+    (void)prec;
+    if (waves <= 0) return 0;
     return placement_conflicts(a.swz, a, tile_bits, __builtin_ctz(unsigned((1 << (tile_bits - 9)) / waves)));
 }
 

@@ -33,6 +33,7 @@ namespace dev {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float vf4 __attribute__((ext_vector_type(4)));
 typedef float vf2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -40,16 +41,38 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
-// Arithmetic of a tile pass: FP32 MFMA, or hi + lo split products in BF16 or
-// FP16 (FP32 accumulation).
-constexpr int kPrecF32 = kTileOperandF32, kPrecBF16 = kTileOperandBF16, kPrecF16 = kTileOperandF16,
-              kPrecBF16X3 = kTileOperandBF16X3;
+// Arithmetic of a tile pass: split products in BF16 or FP16 with FP32
+// accumulation.  FP32 and BF16X3 passes run the same kernels (kPrecX3): three
+// BF16 parts of the matrix and of the state, six products, which is closer to
+// 64-bit values than FP32 MFMA (whose sums round 32 times) and does a block in
+// 2.8 instead of 5.0 us per tile.
+constexpr int kPrecX3 = kTileOperandF32, kPrecBF16 = kTileOperandBF16, kPrecF16 = kTileOperandF16;
 
 // LDS words per lane of one block's operand (the A' fragments of the 64
-// lanes, expanded at staging so that the block loop reads them as they are):
-// FP32 16, split 8 per matrix part (FP16: two parts, BF16: three).  The
-// smaller FP32 and FP16 operands let more blocks share a launch.
-constexpr int lane_words(int prec) { return prec == kPrecBF16 || prec == kPrecBF16X3 ? 24 : 16; }
+// lanes): 8 per matrix part where every part is expanded at staging, so that
+// the block loop reads it as it is (FP16: two parts, BF16: three).  X3 expands
+// the first part only and keeps the two others compact (4 words a lane each,
+// expanded when read), so that as many blocks share a launch as with FP16;
+// launches of fewer blocks have room for 24 words a lane (x3_whole).
+constexpr int lane_words(int prec) { return prec == kPrecBF16 ? 24 : 16; }
+
+// Where a lane's 16-byte chunk of X3's parts sits (words into the operand).
+// The XORs put the chunks that one LDS access reads (8 lanes over 32 banks,
+// 16 over 64) on distinct banks; the two lanes of a complex row read the same
+// compact chunk.
+__device__ __forceinline__ uint32_t x3_expanded_at(uint32_t lane, uint32_t i)
+{
+    return lane * 8 + 4 * (i ^ (((lane >> 2) ^ (lane >> 3)) & 1u));
+}
+template <class C>
+__host__ __device__ constexpr bool x3_whole(int n_sub)
+{
+    return n_sub * 64 * 24 <= C::OP_AREA;
+}
+__device__ __forceinline__ uint32_t x3_compact_at(uint32_t part, uint32_t ci, uint32_t c)
+{
+    return 512 + (part - 1) * 256 + ci * 16 + 4 * (c ^ ((ci >> 1) & 3u));
+}
 
 // 16-byte chunk c of lane L's fragments sits at chunk c ^ frag_swz<LW>(L) of
 // its LW words.  With 64-byte lanes (LW = 16) the lanes of one 16-byte LDS
@@ -84,7 +107,11 @@ struct TileCfg {
     static constexpr int OPERAND_WORDS = 64 * LW;
     static constexpr int FIT = (LDS_BUDGET - N * 8 - 8 * WAVES) / (4 * (OPERAND_WORDS + TABLE_WORDS));
     static constexpr int MAX_SUB = FIT < kMaxTileSubBlocks ? FIT : kMaxTileSubBlocks;
-    static_assert(THREADS % 256 == 0 && THREADS <= 1024 && NB_PER_WAVE >= 1, "tile shape");
+    // X3 (LW = 16) keeps all three parts expanded where the launch's blocks leave room
+    static constexpr int OP_AREA = LW == 16 ? (LDS_BUDGET - N * 8 - 8 * WAVES - 4 * MAX_SUB * TABLE_WORDS) / 16 * 4
+                                            : MAX_SUB * OPERAND_WORDS;
+    static_assert(THREADS % 256 == 0 && THREADS <= 1024 && NB_PER_WAVE >= 1 && OP_AREA >= MAX_SUB * OPERAND_WORDS,
+                  "tile shape");
 };
 
 __device__ __forceinline__ uint32_t deposit(uint32_t v, uint32_t mask)
@@ -297,7 +324,7 @@ template <int TB, int WAVES, int LW>
 struct TileShared {
     using C = TileCfg<TB, WAVES, LW>;
     vf4 X4[C::N / 2];
-    uint32_t op[C::MAX_SUB][C::OPERAND_WORDS];
+    alignas(16) uint32_t op[C::OP_AREA];  // the blocks' operands, C::op_words(n_sub) apart
     uint32_t cq[C::MAX_SUB][C::CBLOCKS];
     uint32_t cl[C::MAX_SUB][32];
     float red[WAVES];  // per-wave partial of the next tile's scale (FP16 passes)
@@ -309,35 +336,73 @@ struct TileShared {
 // words per lane, and the column tables.  Lane (half, l32) takes row r = l32 of A' =
 // [[Ur,-Ui],[Ui,Ur]] interleaved by (re, im): complex row ci = r / 2, part
 // ri = r % 2.
-//   FP32: word j < 16 = A'[r][2 j + half], i.e. Ur[ci][j] (ri == half),
-//   -Ui[ci][j] (ri = 0, half = 1) or Ui[ci][j] (ri = 1, half = 0).
-//   split: word 8 p + 4 i + e (part p = 0..2, step i = 0, 1, e = 0..3) holds
-//   the 16-bit pair A'[r][16 i + 8 half + 2 e + {0, 1}] of part p: (Ur, -Ui)
+//   word 8 p + 4 i + e (part p = 0..2, step i = 0, 1, e = 0..3) holds the
+//   16-bit pair A'[r][16 i + 8 half + 2 e + {0, 1}] of part p: (Ur, -Ui)
 //   for ri = 0, (Ui, Ur) for ri = 1, at complex column j = 8 i + 4 half + e.
 template <int TB, int WAVES, int PREC>
 __device__ __forceinline__ void stage_blocks(TileShared<TB, WAVES, lane_words(PREC)> &sh, const uint32_t *A,
-                                             const TileArgs &args, int tid)
+                                             const TileArgs &args, int tid, bool whole)
 {
     using C = TileCfg<TB, WAVES, lane_words(PREC)>;
-    constexpr bool SPLIT = PREC != kPrecF32;
-    constexpr int USED = lane_words(PREC);  // every word is read by the block loop
+    constexpr int CHUNKS = lane_words(PREC) / 4;  // 16-byte chunks per lane, each 4 consecutive compact words
+    constexpr bool X3 = PREC == kPrecX3;
     const int nsub = args.n_sub;
-    for (int e = tid; e < nsub * 64 * USED; e += C::THREADS) {
-        const int s = e / (64 * USED), r = e % (64 * USED);
-        const int lane = r / USED, wd = r % USED;
-        const int half = lane >> 5, l32 = lane & 31, ci = l32 >> 1, ri = l32 & 1;
-        const uint32_t *cop = A + size_t(s) * kTileOperandWords;
-        uint32_t v;
-        if (!SPLIT) {
-            v = cop[(ri == half ? 0 : 256) + ci * 16 + wd];
-            if (ri == 0 && half == 1) v ^= 0x80000000u;
+    const int per_block = 64 * (whole ? 6 : CHUNKS);
+    const int units = nsub * per_block;
+    typedef uint32_t vu4 __attribute__((ext_vector_type(4)));
+    // X3: units 0..127 of a block are the first part's fragments, the rest
+    // the compact chunks of the two other parts, or their fragments
+    struct Unit {
+        int s, lane, c, part;
+        bool expand;
+    };
+    auto unit_of = [&](int u) {
+        Unit x;
+        x.s = whole ? u / (64 * 6) : u / (64 * CHUNKS);
+        const int r = u - x.s * per_block;
+        x.expand = !X3 || whole || r < 128;
+        if (X3) {
+            x.lane = x.expand ? (r & 127) >> 1 : (r & 63) >> 2;  // compact: the complex row
+            x.c = x.expand ? r & 1 : r & 3;
+            x.part = x.expand ? r >> 7 : 1 + ((r - 128) >> 6);
         } else {
-            const int part = wd >> 3, i = (wd >> 2) & 1, e4 = wd & 3;
-            const uint32_t w = cop[part * 256 + ci * 16 + 8 * i + 4 * half + e4];
-            v = ri ? ((w >> 16) | (w << 16)) : (w ^ 0x80000000u);
+            x.lane = r / CHUNKS;
+            x.c = r % CHUNKS;
+            x.part = x.c >> 1;
         }
-        const int at = int(((uint32_t(wd) >> 2) ^ frag_swz<USED>(uint32_t(lane))) << 2) | (wd & 3);
-        sh.op[s][lane * USED + at] = v;
+        return x;
+    };
+    // four loads in flight per thread: the operands come from HBM, and word
+    // by word their latency alone was 2 us of a launch
+    constexpr int DEPTH = 4;
+    for (int u0 = tid; u0 < units; u0 += DEPTH * C::THREADS) {
+        vu4 v[DEPTH];
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            const int u = u0 + d * C::THREADS;
+            if (u >= units) continue;
+            const Unit x = unit_of(u);
+            // X3: row 16 c + l16, columns 4 kg ..; else row l32, columns 8 i + 4 half ..
+            const int at = X3 ? (x.expand ? (8 * x.c + ((x.lane & 15) >> 1)) * 16 + 4 * (x.lane >> 4) : x.lane * 16 + 4 * x.c)
+                              : ((x.lane & 31) >> 1) * 16 + 8 * (x.c & 1) + 4 * (x.lane >> 5);
+            v[d] = *reinterpret_cast<const vu4 *>(A + size_t(x.s) * kTileOperandWords + 256 * x.part + at);
+        }
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            const int u = u0 + d * C::THREADS;
+            if (u >= units) continue;
+            const Unit x = unit_of(u);
+            vu4 w = v[d];
+            if (x.expand) w = x.lane & 1 ? (w >> 16) | (w << 16) : w ^ 0x80000000u;
+            uint32_t to;
+            if (!X3)
+                to = uint32_t(x.lane) * lane_words(PREC) + 4 * (uint32_t(x.c) ^ frag_swz<lane_words(PREC)>(uint32_t(x.lane)));
+            else if (x.expand)
+                to = 512 * uint32_t(x.part) + x3_expanded_at(uint32_t(x.lane), uint32_t(x.c));
+            else
+                to = x3_compact_at(uint32_t(x.part), uint32_t(x.lane), uint32_t(x.c));
+            *reinterpret_cast<vu4 *>(&sh.op[x.s * (4 * per_block) + to]) = w;
+        }
     }
     for (int e = tid; e < nsub * (C::CBLOCKS + 32); e += C::THREADS) {
         const int s = e / (C::CBLOCKS + 32), r = e % (C::CBLOCKS + 32);
@@ -346,19 +411,10 @@ __device__ __forceinline__ void stage_blocks(TileShared<TB, WAVES, lane_words(PR
         const uint32_t cmask = ((1u << TB) - 1) & ~m;
         constexpr int NBW = C::NB_PER_WAVE;
         if (r < C::CBLOCKS)
-            sh.cq[s][r] = swz(deposit(SPLIT ? uint32_t((r / NBW) * 32 * NBW + r % NBW) : uint32_t(r * 32), cmask),
-                              args);
+            sh.cq[s][r] = swz(deposit(uint32_t((r / NBW) * 32 * NBW + r % NBW), cmask), args);
         else
-            sh.cl[s][r - C::CBLOCKS] = swz(deposit(uint32_t(r - C::CBLOCKS) * (SPLIT ? NBW : 1), cmask), args);
+            sh.cl[s][r - C::CBLOCKS] = swz(deposit(uint32_t(r - C::CBLOCKS) * NBW, cmask), args);
     }
-}
-
-__device__ __forceinline__ void lds_st(char *Xb, uint32_t byte_off, float re, float im)
-{
-    vf2 v;
-    v.x = re;
-    v.y = im;
-    *reinterpret_cast<vf2 *>(Xb + byte_off) = v;
 }
 
 // hi = RNE(v), lo = RNE(v - hi) and, with three parts, lo2 = RNE(v - hi - lo)
@@ -407,6 +463,16 @@ __device__ __forceinline__ f32x16 mfma16(f16x8 a, f16x8 b, f32x16 c)
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
 
+// One 16 x 16 x 32 product of 16-bit operands with FP32 accumulation.
+__device__ __forceinline__ f32x4 mfma16x16(bf16x8 a, bf16x8 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mfma16x16(f16x8 a, f16x8 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+}
+
 __device__ __forceinline__ void lds_st4(char *Xb, uint32_t byte_off, float a, float b, float c, float d)
 {
     vf4 v;
@@ -417,14 +483,13 @@ __device__ __forceinline__ void lds_st4(char *Xb, uint32_t byte_off, float a, fl
     *reinterpret_cast<vf4 *>(Xb + byte_off) = v;
 }
 
-// One block of the pass on the tile in LDS.  D real row = 8 (v / 4) + 4 half
+// One block of the pass on the tile in LDS (BF16 and FP16; X3: apply_block_x3).
+// D real row = 8 (v / 4) + 4 half
 // + v % 4: acc[4 g + 2 e] and acc[4 g + 2 e + 1] are (re, im) of complex row
 // 4 g + 2 half + e.  Each wave owns its columns, so its reads of the block
 // precede its writes; the caller places the barrier.
 //
-// FP32: lane (half, l32) reads re (half 0) or im (half 1) of complex row j,
-// one 4-byte read per row and column block.  Split: every LDS access moves
-// 16 bytes, two complex values that differ in tile bit 0.  If tile bit 0 is
+// Every LDS access moves 16 bytes, two complex values that differ in tile bit 0.  If tile bit 0 is
 // the block's row bit 0, these are rows (t, t + 1) of one column; otherwise
 // tile bit 0 is the lowest column bit, i.e. column blocks (q, q + 1).
 template <int TB, int WAVES, int PREC, int SCALE>
@@ -432,7 +497,6 @@ __device__ __forceinline__ void apply_block(TileShared<TB, WAVES, lane_words(PRE
                                             int w, int half, int l32, float scale, float unscale)
 {
     using C = TileCfg<TB, WAVES, lane_words(PREC)>;
-    constexpr bool SPLIT = PREC != kPrecF32;
     using H2 = typename std::conditional<PREC == kPrecF16, f16x2, bf16x2>::type;  // packed 16-bit pair
     using H8 = typename std::conditional<PREC == kPrecF16, f16x8, bf16x8>::type;  // MFMA operand
     constexpr int NBW = C::NB_PER_WAVE;
@@ -446,8 +510,7 @@ __device__ __forceinline__ void apply_block(TileShared<TB, WAVES, lane_words(PRE
 #pragma unroll
     for (int q = 0; q < NBW; ++q) {
         const uint32_t col = cl ^ sh.cq[s][w * NBW + q];
-        // B rows: FP32 2j + half (re | im of complex row j); split 8i + 4 half + t
-        lq[q] = SPLIT ? (col ^ (half ? rb[2] : 0u)) << 3 : (col << 3) | uint32_t(half << 2);
+        lq[q] = (col ^ (half ? rb[2] : 0u)) << 3;  // B rows 8 i + 4 half + t
         wq[q] = (col ^ (half ? rb[1] : 0u)) << 3;  // complex row bit 1 = half
     }
     f32x16 acc[NBW];
@@ -455,40 +518,13 @@ __device__ __forceinline__ void apply_block(TileShared<TB, WAVES, lane_words(PRE
     for (int q = 0; q < NBW; ++q)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
-    const uint32_t *op = sh.op[s];
-    const vf4 *ap = reinterpret_cast<const vf4 *>(op + (half * 32 + l32) * lane_words(PREC));  // staged fragments
-    const uint32_t fsw = frag_swz<lane_words(PREC)>(uint32_t(half * 32 + l32));  // their chunk order
-    if (!SPLIT) {
-        float a[16];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const vf4 v = ap[uint32_t(i) ^ fsw];
-            a[4 * i] = v.x;
-            a[4 * i + 1] = v.y;
-            a[4 * i + 2] = v.z;
-            a[4 * i + 3] = v.w;
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-#pragma unroll
-            for (int q = 0; q < NBW; ++q) {
-                const float b = *reinterpret_cast<const float *>(Xb + ((row_of(rb, j) << 3) ^ lq[q]));
-                acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b, acc[q], 0, 0, 0);
-            }
-#pragma unroll
-        for (int q = 0; q < NBW; ++q)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-#pragma unroll
-                for (int e = 0; e < 2; ++e)
-                    lds_st(Xb, (row_of(rb, 4 * g + e) << 3) ^ wq[q], acc[q][4 * g + 2 * e],
-                           acc[q][4 * g + 2 * e + 1]);
-        return;
-    }
-    // split: step i (K = 16 i .. 16 i + 15) with the operand's parts A_p
+    const uint32_t *op = sh.op + s * C::OPERAND_WORDS;
+    const uint32_t lane = uint32_t(half * 32 + l32);
+    const vf4 *ap = reinterpret_cast<const vf4 *>(op + lane * lane_words(PREC));  // staged fragments
+    const uint32_t fsw = frag_swz<lane_words(PREC)>(lane);                        // their chunk order
+    // step i (K = 16 i .. 16 i + 15) with the operand's parts A_p
     // (BF16: three, FP16: two) and the tile values split into NS parts X_s:
-    // every A_p X_0, every A_0 X_s, and A_1 X_1 when CROSS, the smaller terms
-    // accumulated first.
+    // every A_p X_0 and every A_0 X_s, the smaller terms accumulated first.
     // FP16: the values are scaled by `scale` before the split (SCALE 0: one
     // scale per tile; SCALE 1: the tile is held scaled in LDS with one scale
     // per pass), A_1 is held multiplied by 2^11 and meets X_0 2^-11 (so that
@@ -497,8 +533,7 @@ __device__ __forceinline__ void apply_block(TileShared<TB, WAVES, lane_words(PRE
     constexpr bool F16 = PREC == kPrecF16;
     constexpr bool SCALE_HERE = F16 && SCALE == 0;
     constexpr int NP = F16 ? 2 : 3;
-    constexpr int NS = PREC == kPrecBF16X3 ? 3 : 2;
-    constexpr bool CROSS = PREC == kPrecBF16X3;
+    constexpr int NS = 2;
     auto scaled = [&](vf4 v) { return SCALE_HERE ? v * scale : v; };
     auto out = [&](float v) { return SCALE_HERE ? v * unscale : v; };
     // X_0 2^-11 of a pair's X_0 (FP16 only; exact unless it falls below
@@ -522,7 +557,7 @@ __device__ __forceinline__ void apply_block(TileShared<TB, WAVES, lane_words(PRE
 #pragma unroll
             for (int sp = 0; sp < NS; ++sp) {
                 const int p = d - sp;
-                if (p >= 0 && p < NP && (sp == 0 || p == 0 || (CROSS && p == 1 && sp == 1)))
+                if (p >= 0 && p < NP && (sp == 0 || p == 0))
                     c = mfma16(xa[p], b[sp], c);
             }
         return c;
@@ -630,23 +665,131 @@ __device__ __forceinline__ void apply_block(TileShared<TB, WAVES, lane_words(PRE
     }
 }
 
+// X3's block on the tile in LDS, in 16 x 16 x 32 products: lane (kg, l16) holds
+// the 8 consecutive K values (4 complex rows 4 kg + {0..3}) of column l16, so
+// one product covers the whole contraction, and a step's accumulators are 8
+// registers (16 with a column pair) instead of the 32 of two 32 x 32 blocks:
+// with three parts of each value the latter spilled the prefetched tile.  D
+// real row = 16 r + 4 kg + v (r = 0, 1): complex rows 8 r + 2 kg + {0, 1}.
+// The columns of a wave, their LDS addresses and the 16-byte accesses are
+// those of apply_block, 16 columns (g2) at a time.
+template <int TB, int WAVES>
+__device__ __forceinline__ void apply_block_x3(TileShared<TB, WAVES, lane_words(kPrecX3)> &sh, const TileArgs &args,
+                                               int s, int w, int lane, bool whole)
+{
+    using C = TileCfg<TB, WAVES, lane_words(kPrecX3)>;
+    constexpr int NBW = C::NB_PER_WAVE;
+    typedef uint32_t vu4 __attribute__((ext_vector_type(4)));
+    char *Xb = reinterpret_cast<char *>(sh.X4);
+    const uint32_t kg = uint32_t(lane) >> 4, l16 = uint32_t(lane) & 15u;
+    uint32_t rb[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) rb[b] = args.swz[args.tbit[s][b]] << 3;  // byte terms
+    const uint32_t rterm = (kg & 1u ? rb[2] : 0u) ^ (kg & 2u ? rb[3] : 0u);
+    const uint32_t wterm = (kg & 1u ? rb[1] : 0u) ^ (kg & 2u ? rb[2] : 0u);
+    // A' fragments: row 16 r + l16 (complex row 8 r + l16 / 2), complex columns
+    // 4 kg .. 4 kg + 3; compact words are turned by 16 bits (the low 5 bits of
+    // `turn`) on odd rows and their high half negated on even ones
+    const uint32_t turn = l16 << 4, negate = (l16 << 31) ^ 0x80000000u;
+    const uint32_t *op = sh.op + s * (whole ? 64 * 24 : 64 * 16);
+    bf16x8 xa[2][3];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const bool fragment = p == 0 || whole;
+            const uint32_t at = fragment ? 512u * uint32_t(p) + x3_expanded_at(uint32_t(lane), uint32_t(r))
+                                         : x3_compact_at(uint32_t(p), uint32_t(8 * r) + (l16 >> 1), kg);
+            vu4 f = *reinterpret_cast<const vu4 *>(op + at);
+            if (!fragment) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) f[e] = __builtin_amdgcn_alignbit(f[e], f[e], turn) ^ negate;
+            }
+            __builtin_memcpy(&xa[r][p], &f, 16);
+        }
+    // acc[r] = sum of the products A_p X_s, the smaller first, of 4 complex values
+    auto column = [&](const vf2 *x, f32x4 *acc) __attribute__((always_inline)) {
+        bf16x2 pp[4][3];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) split_pair<3>(x[t].x, x[t].y, pp[t], -1.f);
+        bf16x8 b[3];
+#pragma unroll
+        for (int sp = 0; sp < 3; ++sp) {
+            const bf16x2 t[4] = {pp[0][sp], pp[1][sp], pp[2][sp], pp[3][sp]};
+            __builtin_memcpy(&b[sp], t, 16);
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            f32x4 c = {0.f, 0.f, 0.f, 0.f};
+            c = mfma16x16(xa[r][2], b[0], c);
+            c = mfma16x16(xa[r][1], b[1], c);
+            c = mfma16x16(xa[r][0], b[2], c);
+            c = mfma16x16(xa[r][1], b[0], c);
+            c = mfma16x16(xa[r][0], b[1], c);
+            acc[r] = mfma16x16(xa[r][0], b[0], c);
+        }
+    };
+#pragma unroll
+    for (int g2 = 0; g2 < 2; ++g2) {
+        const uint32_t cl = sh.cl[s][l16 + 16u * uint32_t(g2)] << 3;
+        if (args.tbit[s][0] == 0) {  // uniform: rows (t, t + 1) share a slot
+#pragma unroll
+            for (int q = 0; q < NBW; ++q) {
+                const uint32_t col = cl ^ sh.cq[s][w * NBW + q] << 3, rd = col ^ rterm, wr = col ^ wterm;
+                vf2 x[4];
+#pragma unroll
+                for (int k2 = 0; k2 < 2; ++k2) {
+                    const vf4 v = *reinterpret_cast<const vf4 *>(Xb + (row_of(rb, 2 * k2) ^ rd));
+                    x[2 * k2] = vf2{v.x, v.y};
+                    x[2 * k2 + 1] = vf2{v.z, v.w};
+                }
+                f32x4 acc[2];
+                column(x, acc);
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+                    *reinterpret_cast<vf4 *>(Xb + (row_of(rb, 8 * r) ^ wr)) = acc[r];
+            }
+        } else {  // column blocks (q, q + 1) share a slot
+#pragma unroll
+            for (int q = 0; q < NBW; q += 2) {
+                const uint32_t col = cl ^ sh.cq[s][w * NBW + q] << 3, rd = col ^ rterm, wr = col ^ wterm;
+                vf2 x0[4], x1[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const vf4 v = *reinterpret_cast<const vf4 *>(Xb + (row_of(rb, t) ^ rd));
+                    x0[t] = vf2{v.x, v.y};
+                    x1[t] = vf2{v.z, v.w};
+                }
+                f32x4 a0[2], a1[2];
+                column(x0, a0);
+                column(x1, a1);
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+                        lds_st4(Xb, row_of(rb, 8 * r + e) ^ wr, a0[r][2 * e], a0[r][2 * e + 1],
+                                a1[r][2 * e], a1[r][2 * e + 1]);
+            }
+        }
+    }
+}
+
 // The tile loop of one workgroup: tiles T, T + step, .. below T_end of the
 // state at psi.  A = the blocks' compact operands (pack_tile_operand), back to
-// back.  FP32 (kPrecF32): FP32 MFMA.  Split (kPrecBF16, kPrecBF16X3,
-// kPrecF16): the host splits U into 16-bit parts, U = A_0 + A_1 + A_2 for
+// back.  The host splits U into 16-bit parts, U = A_0 + A_1 + A_2 for
 // BF16 (8 more significand bits each, about FP32's 24 in all) and A_0 + A_1
 // for FP16; each B operand (8 consecutive K values = 4 complex rows of one
 // column) is split while it is read from LDS, into X_0 + X_1 (kPrecBF16,
-// kPrecF16) or X_0 + X_1 + X_2 (kPrecBF16X3), and the products
-// sum_p A_p X_0 + sum_s A_0 X_s (plus A_1 X_1 for kPrecBF16X3) run on
+// kPrecF16) or X_0 + X_1 + X_2 (kPrecX3), and the products
+// sum_p A_p X_0 + sum_s A_0 X_s (plus A_1 X_1 for kPrecX3) run on
 // 32 x 32 x 16 MFMA with FP32 accumulation.  The dropped terms are about
 // 2^-17 (BF16: the state's third part, A_1 X_1), 2^-22 (FP16) and 2^-25
-// (BF16X3) relative to the result.  FP16 passes scale the values per tile
+// (X3) relative to the result.  FP16 passes scale the values per tile
 // (tile_scale; SCALE 0, and SCALE 2, which also reports the workgroup's sum
 // of squares to norm.out) or per pass from the state's norm (norm_scale;
 // SCALE 1, from the sums an earlier pass of the run reported; SCALE 3, the
 // same scale with the state already held scaled in HBM, copied as it is).
-template <int TB, int WAVES, int PREC, int SCALE>
+template <int TB, int WAVES, int PREC, int SCALE, int WHOLE>
 __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)> &sh, float *__restrict__ psi,
                                           const uint32_t *__restrict__ A, const TileArgs &args, uint64_t T,
                                           uint64_t T_end, uint64_t step, const TileNorm &norm)
@@ -658,7 +801,9 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
 
-    stage_blocks<TB, WAVES, PREC>(sh, A, args, tid);
+    // X3: whether every part is staged expanded (WHOLE 1, 0; -1: by the blocks)
+    const bool whole = PREC == kPrecX3 && (WHOLE < 0 ? x3_whole<TileCfg<TB, WAVES, lane_words(PREC)>>(args.n_sub) : WHOLE > 0);
+    stage_blocks<TB, WAVES, PREC>(sh, A, args, tid, whole);
     TileCopy<TB, WAVES> cp;
     cp.init(args, tid);
     // the largest magnitude in buf over the workgroup: a wave maximum into
@@ -686,7 +831,8 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
 
     // FP16 with SCALE 1: one scale for the pass from the state's norm, the
     // sum of the workgroups' sums of squares that an earlier pass of the run
-    // wrote (fixed order; uniform, in scalar registers).  The copy-in
+    // wrote (64 lanes' strided sums, then a butterfly: a fixed order; uniform,
+    // in scalar registers).  The copy-in
     // multiplies by it unless the state is already held scaled in HBM, and
     // the copy-out divides by it unless the state is to stay scaled.  SCALE 3:
     // the state is held scaled in HBM before and after the pass, so the pass
@@ -694,7 +840,9 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
     float pscale = 1.f, punscale = 1.f;
     if (F16 && SCALE == 1) {
         double r2 = 0.0;
-        for (int i = 0; i < norm.n_in; ++i) r2 += norm.in[i];
+        for (int i = lane; i < norm.n_in; i += 64) r2 += norm.in[i];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) r2 += __shfl_xor(r2, o, 64);
         norm_scale(sqrt(r2), pscale, punscale);
         if (norm.in_scaled) pscale = 1.f;
         if (norm.out_scaled) punscale = 1.f;
@@ -725,9 +873,9 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
     // these were issued a whole round of block work earlier.
     // a pass that starts the state from a basis state reads nothing: the
     // basis state lies in the tile whose outside positions match its bits,
-    // at the tile index its tile-position bits form (FP32 and split FP16; in
-    // the split BF16 kernels the extra registers made them spill)
-    constexpr bool CAN_SYNTH = PREC == kPrecF32 || PREC == kPrecF16;
+    // at the tile index its tile-position bits form (split FP16, and X3 in a
+    // variant of its own, SCALE 4: the extra registers make it spill)
+    constexpr bool CAN_SYNTH = PREC == kPrecF16 || SCALE == 4;
     const bool synth = CAN_SYNTH && norm.basis >= 0;  // uniform
     uint64_t b_out = 0;
     uint32_t b_t = 0;
@@ -785,7 +933,10 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
             __builtin_amdgcn_s_setprio(0);
         }
         for (int s = 0; s < args.n_sub; ++s) {
-            apply_block<TB, WAVES, PREC, F16 && !PER_TILE ? 1 : 0>(sh, args, s, w, half, l32, scale, unscale);
+            if constexpr (PREC == kPrecX3)
+                apply_block_x3<TB, WAVES>(sh, args, s, w, lane, whole);
+            else
+                apply_block<TB, WAVES, PREC, F16 && !PER_TILE ? 1 : 0>(sh, args, s, w, half, l32, scale, unscale);
             __syncthreads();
         }
         prev = base;
@@ -809,13 +960,13 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
 
 // One pass over one state (gridDim.y = 1) or over psi and psi2 alike
 // (gridDim.y = 2): a persistent grid strides over the tiles of its state.
-template <int TB, int WAVES, int PREC, int SCALE>
+template <int TB, int WAVES, int PREC, int SCALE, int WHOLE = 0>
 __global__ void __launch_bounds__(64 * WAVES) k_tile_pass(float *__restrict__ psi, const uint32_t *__restrict__ A,
                                                           const TileArgs args, float *__restrict__ psi2,
                                                           const TileNorm norm)
 {
     __shared__ TileShared<TB, WAVES, lane_words(PREC)> sh;
-    tile_loop<TB, WAVES, PREC, SCALE>(sh, blockIdx.y ? psi2 : psi, A, args, blockIdx.x, args.n_tiles, gridDim.x,
+    tile_loop<TB, WAVES, PREC, SCALE, WHOLE>(sh, blockIdx.y ? psi2 : psi, A, args, blockIdx.x, args.n_tiles, gridDim.x,
                                       norm);
 }
 
@@ -830,7 +981,7 @@ __global__ void __launch_bounds__(64 * WAVES) k_tile_batch(const TileUnit *__res
     __shared__ TileShared<TB, WAVES, lane_words(PREC)> sh;
     const TileUnit u = units[blockIdx.x];
     const TilePass &p = passes[u.pass];
-    tile_loop<TB, WAVES, PREC, 0>(sh, buf + 2 * p.state_off, pool + p.op_off, p.args, u.t0, u.t1, 1, TileNorm{});
+    tile_loop<TB, WAVES, PREC, 0, -1>(sh, buf + 2 * p.state_off, pool + p.op_off, p.args, u.t0, u.t1, 1, TileNorm{});
 }
 
 template <int TB, int WAVES>
@@ -847,8 +998,6 @@ hipError_t tile_launch(const TileArgs &a, const void *d_a, int prec, float *psi,
     plain.basis = norm.basis;
     if (prec == kPrecBF16)
         hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecBF16, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
-    else if (prec == kPrecBF16X3)
-        hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecBF16X3, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
     else if (prec == kPrecF16 && norm.in && norm.in_scaled && norm.out_scaled)
         hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF16, 3>), grid, block, 0, st, psi, A, a, psi2, norm);
     else if (prec == kPrecF16 && norm.in)
@@ -857,8 +1006,16 @@ hipError_t tile_launch(const TileArgs &a, const void *d_a, int prec, float *psi,
         hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF16, 2>), grid, block, 0, st, psi, A, a, psi2, norm);
     else if (prec == kPrecF16)
         hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF16, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
-    else
-        hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF32, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
+    else if (x3_whole<TileCfg<TB, WAVES, lane_words(kPrecX3)>>(a.n_sub)) {
+        if (norm.basis >= 0)
+            hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecX3, 4, 1>), grid, block, 0, st, psi, A, a, psi2, plain);
+        else
+            hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecX3, 0, 1>), grid, block, 0, st, psi, A, a, psi2, plain);
+    } else if (norm.basis >= 0) {
+        hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecX3, 4>), grid, block, 0, st, psi, A, a, psi2, plain);
+    } else {
+        hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecX3, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
+    }
     return hipGetLastError();
 }
 
@@ -888,7 +1045,9 @@ static int max_blocks_of(int tile_bits, int waves)
 int tile_max_blocks(int tile_bits, int waves, int prec)
 {
     if (!tile_shape_supported(tile_bits, waves)) return 0;
-    return lane_words(prec) == 24 ? max_blocks_of<24>(tile_bits, waves) : max_blocks_of<16>(tile_bits, waves);
+    // BF16X3's limit is that of split BF16, though its operands are smaller
+    return prec == kTileOperandBF16 || prec == kTileOperandBF16X3 ? max_blocks_of<24>(tile_bits, waves)
+                                                                   : max_blocks_of<16>(tile_bits, waves);
 }
 
 static uint32_t f2h_rne(float x)
@@ -929,12 +1088,6 @@ void pack_tile_operand(const cd *m, int prec, uint32_t *out)
     for (int r = 0; r < 16; ++r)
         for (int c = 0; c < 16; ++c) {
             const double re = m[r * 16 + c].real(), im = m[r * 16 + c].imag();
-            if (prec == kTileOperandF32) {
-                const float fr = float(re), fi = float(im);
-                std::memcpy(&out[r * 16 + c], &fr, 4);
-                std::memcpy(&out[256 + r * 16 + c], &fi, 4);
-                continue;
-            }
             // part p = RNE(x - parts 0..p-1), as (re, im) halves of one word:
             // three BF16 parts, two FP16 parts (the second held times 2^11,
             // which keeps it in FP16's normal range; the kernel pairs it with
@@ -1032,17 +1185,14 @@ hipError_t launch_tile_batch(const TileUnit *units, int n_units, const TilePass 
     if (n_units <= 0) return hipSuccess;
     const dim3 grid{unsigned(n_units)}, block{unsigned(64 * kBatchTileWaves)};
     float *b = static_cast<float *>(buf);
-    if (prec == kPrecBF16X3)
-        hipLaunchKernelGGL((k_tile_batch<kBatchTileBits, kBatchTileWaves, kPrecBF16X3>), grid, block, 0, st, units,
-                           passes, pool, b);
-    else if (prec == kPrecBF16)
+    if (prec == kPrecBF16)
         hipLaunchKernelGGL((k_tile_batch<kBatchTileBits, kBatchTileWaves, kPrecBF16>), grid, block, 0, st, units, passes,
                            pool, b);
     else if (prec == kPrecF16)
         hipLaunchKernelGGL((k_tile_batch<kBatchTileBits, kBatchTileWaves, kPrecF16>), grid, block, 0, st, units, passes,
                            pool, b);
     else
-        hipLaunchKernelGGL((k_tile_batch<kBatchTileBits, kBatchTileWaves, kPrecF32>), grid, block, 0, st, units, passes,
+        hipLaunchKernelGGL((k_tile_batch<kBatchTileBits, kBatchTileWaves, kPrecX3>), grid, block, 0, st, units, passes,
                            pool, b);
     return hipGetLastError();
 }
