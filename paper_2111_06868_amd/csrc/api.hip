@@ -138,7 +138,7 @@ int run_launches(sv_state *s, std::vector<Launch> &launches, bool use_graph)
 void blocks_to_launches(const std::vector<Block> &blocks, const sv_state *s, int precision, int rule,
                         std::vector<Launch> &out)
 {
-    if (rule == SV_RULE_TILED && s->dtype == SV_C64 && precision != SV_PREC_FP64) {
+    if (rule == SV_RULE_TILED) {
         group_tile_passes(blocks, s->n, precision, out);
         return;
     }
@@ -186,7 +186,7 @@ int choose_plan(const sv_gate *g, int G, int n, int dtype, int precision, int ru
     mix(uint64_t(max_k + 8));
     mix(cost_version());
     mix(uint64_t(tile_union_limit()));
-    mix(uint64_t(tile_pass_bits()) | uint64_t(tile_pass_capacity(precision)) << 8);
+    mix(uint64_t(tile_pass_bits(precision)) | uint64_t(tile_pass_capacity(precision)) << 8);
     mix(uint64_t(G));
     for (int i = 0; i < G; ++i) {
         mix(uint64_t(g[i].kind) | uint64_t(g[i].k) << 8);
@@ -219,7 +219,7 @@ int choose_plan_uncached(const sv_gate *g, int G, int n, int dtype, int precisio
     std::vector<int> rules;
     if (rule == SV_RULE_AUTO) {
         rules.push_back(SV_RULE_ENHANCED);
-        if (dtype == SV_C64 && precision != SV_PREC_FP64 && n >= dev::kMinTileQubits) rules.push_back(SV_RULE_TILED);
+        if (n >= dev::kMinTileQubits) rules.push_back(SV_RULE_TILED);
     } else {
         rules.push_back(rule == SV_RULE_NONE ? SV_RULE_PAPER : rule);
     }
@@ -626,9 +626,9 @@ int run_circuit_impl(sv_state *s, const sv_gate *g, int G, const sv_run_opts *o,
     blocks_to_launches(blocks, s, o->precision, rule, L);
     if (int rc = select_device(s)) return rc;
     if (basis >= 0) {
-        // FP32 and split-FP16 tile passes start from the basis state
+        // FP32, FP64 and split-FP16 tile passes start from the basis state
         // themselves; other first launches get it filled in
-        if (!L.empty() && (L[0].path == PATH_TILE || L[0].path == PATH_TILE_FP16))
+        if (!L.empty() && (L[0].path == PATH_TILE || L[0].path == PATH_TILE_FP16 || L[0].path == PATH_TILE_FP64))
             L[0].basis = basis;
         else
             SV_HIP(dev::launch_fill_basis(s->dtype, s->buf, s->n, uint64_t(basis), s->stream));
@@ -1001,7 +1001,7 @@ class KrausSampler {
         sv_run_opts o;
         o.max_k = 4;
         o.precision = s_->dtype == SV_C64 ? SV_PREC_FP32 : SV_PREC_FP64;
-        o.rule = s_->dtype == SV_C64 && s_->n >= dev::kMinTileQubits ? SV_RULE_TILED : SV_RULE_ENHANCED;
+        o.rule = s_->n >= dev::kMinTileQubits ? SV_RULE_TILED : SV_RULE_ENHANCED;
         o.use_graph = 0;
         return run_circuit_impl(s_, g.data(), int(g.size()), &o);
     }
@@ -1424,7 +1424,7 @@ int dagger_launches(const sv_gate *g, int hi, int lo, const sv_state *s, int pre
     mix(uint64_t(prec));
     mix(cost_version());
     mix(uint64_t(tile_union_limit()));
-    mix(uint64_t(tile_pass_bits()) | uint64_t(tile_pass_capacity(prec)) << 8);
+    mix(uint64_t(tile_pass_bits(prec)) | uint64_t(tile_pass_capacity(prec)) << 8);
     mix(uint64_t(cnt));
     for (int t = 0; t < cnt; ++t) {
         mix(uint64_t(dg[t].k));
@@ -1456,7 +1456,7 @@ int dagger_launches(const sv_gate *g, int hi, int lo, const sv_state *s, int pre
             }
         }
         choice = kbest;
-        if (s->dtype == SV_C64 && kmax <= 4 && dev::tile_supported(s->n, 4)) {
+        if (kmax <= 4 && dev::tile_supported(s->n, 4)) {
             if (best > 1e299) {
                 if (int rc = fuse_gates(dg.data(), cnt, s->n, kbest, SV_RULE_ENHANCED, cost, blocks, false)) return rc;
                 best = plan_cost(blocks, cost);

@@ -64,8 +64,8 @@ struct CostTable {
 // blocks.
 int tile_pass_capacity(int precision = -1);
 
-// Tile bits of the current launch shape (13 or 14).
-int tile_pass_bits();
+// Tile bits of the current launch shape (13 or 14); FP64 passes: 13.
+int tile_pass_bits(int precision = -1);
 
 // Union limit of the tile passes that SV_RULE_TILED plans (8 ..
 // kTilePassMaxUnion; default 10, or the SV_TILE_UNION environment variable).
@@ -81,6 +81,8 @@ int tile_run_bits(uint64_t U, int tile_bits);
 // limit) amplitudes: every union of at most `limit` positions, and larger
 // ones that hold enough of the lowest positions.  States of fewer than
 // tile_bits qubits keep to `limit` positions.
+// FP64 passes (13 tile bits of 16-byte amplitudes) have the runs, in bytes, of
+// 14 tile bits of complex64, so the same limit serves both.
 bool tile_union_fits(uint64_t U, int n, int tile_bits, int limit);
 
 // Cost table used when no autotuned table exists (relative units).

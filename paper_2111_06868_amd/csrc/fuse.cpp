@@ -483,7 +483,7 @@ int fuse_gates(const sv_gate *g, int G, int n, int max_k, int rule, const CostTa
         Frontier passes(g, all);
         std::vector<int> pg;
         int pass = 0;
-        const int tile_bits = tile_pass_bits(), limit = tile_union_limit();
+        const int tile_bits = tile_pass_bits(precision), limit = tile_union_limit();
         auto pass_fits = [n, tile_bits, limit](uint64_t u) { return tile_union_fits(u, n, tile_bits, limit); };
         while (passes.next(pass_fits, pg)) {
             const auto sub = frontier_groups(g, pg, max_k);

@@ -62,8 +62,14 @@ struct TileArgs {
 // half); unused words are 0.  The precision codes are also the tile passes'
 // arithmetic: kTileOperandF32 and kTileOperandBF16X3 split the tile values into
 // three parts instead of two.
-constexpr int kTileOperandWords = 768;
-constexpr int kTileOperandF32 = 0, kTileOperandBF16 = 1, kTileOperandF16 = 2, kTileOperandBF16X3 = 3;
+// FP64 (complex128 states): the 256 complex doubles, in the order the kernel
+// reads them from LDS, in kTileOperandWordsF64 words.
+constexpr int kTileOperandWords = 768, kTileOperandWordsF64 = 1024;
+constexpr int kTileOperandF32 = 0, kTileOperandBF16 = 1, kTileOperandF16 = 2, kTileOperandBF16X3 = 3, kTileOperandF64 = 4;
+constexpr int tile_operand_words(int prec) { return prec == kTileOperandF64 ? kTileOperandWordsF64 : kTileOperandWords; }
+// FP64 passes have one launch shape: tiles of 2^14 8-byte units (2^13
+// amplitudes), 8 waves; their unions have at most 13 positions.
+constexpr int kF64TileBits = 14, kF64TileWaves = 8, kF64MaxUnion = 13;
 void pack_tile_operand(const cd *m, int prec, uint32_t *out);
 // Tile arguments of n_sub blocks (positions ascending per block) on an
 // n-qubit state with 2^tile_bits-amplitude tiles, for a launch of `waves`

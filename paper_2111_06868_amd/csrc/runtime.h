@@ -50,6 +50,7 @@ enum Family {
     FAM_TILE_BF16 = 10,
     FAM_TILE_FP16 = 11,
     FAM_TILE_BF16X3 = 12,
+    FAM_TILE_FP64 = 13,
 };
 
 // Statistics class of a launch: 100 * family + k (k = block size, or the
@@ -82,14 +83,12 @@ enum Path {
     PATH_TILE,
     PATH_TILE_BF16,
     PATH_TILE_FP16,
-    PATH_TILE_BF16X3
+    PATH_TILE_BF16X3,
+    PATH_TILE_FP64
 };
 
-// Tile passes: PATH_TILE, PATH_TILE_BF16, PATH_TILE_FP16, PATH_TILE_BF16X3.
-inline bool is_tile_path(int p)
-{
-    return p == PATH_TILE || p == PATH_TILE_BF16 || p == PATH_TILE_FP16 || p == PATH_TILE_BF16X3;
-}
+// Tile passes: PATH_TILE, PATH_TILE_BF16, PATH_TILE_FP16, PATH_TILE_BF16X3, PATH_TILE_FP64.
+inline bool is_tile_path(int p) { return p >= PATH_TILE && p <= PATH_TILE_FP64; }
 
 struct Tuning {
     int reg_grid_cap[SV_MAX_K + 1];   // 0 = one thread per group

@@ -190,7 +190,7 @@ Tuning &tuning()
     return t;
 }
 
-int tile_pass_bits() { return tuning().tile_bits; }
+int tile_pass_bits(int precision) { return precision == SV_PREC_FP64 ? dev::kF64MaxUnion : tuning().tile_bits; }
 
 int tile_pass_capacity(int precision)
 {
@@ -222,6 +222,7 @@ int path_family(Path p)
     case PATH_TILE_BF16: return FAM_TILE_BF16;
     case PATH_TILE_FP16: return FAM_TILE_FP16;
     case PATH_TILE_BF16X3: return FAM_TILE_BF16X3;
+    case PATH_TILE_FP64: return FAM_TILE_FP64;
     default: return FAM_SPLIT_FP16;
     }
 }
@@ -248,8 +249,9 @@ size_t pack_operands(std::vector<Launch> &launches, int dtype, PinBuf &stage)
         case PATH_TILE_BF16:
         case PATH_TILE_FP16:
         case PATH_TILE_BF16X3:
+        case PATH_TILE_FP64:
             L.arena_off = total;
-            total = align256(total + size_t(L.k) * dev::kTileOperandWords * 4);
+            total = align256(total + size_t(L.k) * dev::tile_operand_words(tile_operand_prec(L.path)) * 4);
             break;
         default:
             L.arena_off = total;
@@ -298,9 +300,11 @@ size_t pack_operands(std::vector<Launch> &launches, int dtype, PinBuf &stage)
         case PATH_TILE_BF16:
         case PATH_TILE_FP16:
         case PATH_TILE_BF16X3:
+        case PATH_TILE_FP64:
             for (int sb = 0; sb < L.k; ++sb)
                 dev::pack_tile_operand(L.m.data() + 256 * sb, tile_operand_prec(L.path),
-                                       reinterpret_cast<uint32_t *>(h + L.arena_off) + dev::kTileOperandWords * sb);
+                                       reinterpret_cast<uint32_t *>(h + L.arena_off) +
+                                           dev::tile_operand_words(tile_operand_prec(L.path)) * sb);
             break;
         default: {
             uint16_t *const parts[3] = {reinterpret_cast<uint16_t *>(h + L.arena_off),
@@ -355,6 +359,7 @@ Path tile_path(int precision)
     if (precision == SV_PREC_SPLIT_BF16) return PATH_TILE_BF16;
     if (precision == SV_PREC_SPLIT_FP16) return PATH_TILE_FP16;
     if (precision == SV_PREC_SPLIT_BF16X3) return PATH_TILE_BF16X3;
+    if (precision == SV_PREC_FP64) return PATH_TILE_FP64;
     return PATH_TILE;
 }
 
@@ -363,6 +368,7 @@ int tile_operand_prec(int path)
     return path == PATH_TILE_BF16     ? dev::kTileOperandBF16
            : path == PATH_TILE_FP16   ? dev::kTileOperandF16
            : path == PATH_TILE_BF16X3 ? dev::kTileOperandBF16X3
+           : path == PATH_TILE_FP64   ? dev::kTileOperandF64
                                       : dev::kTileOperandF32;
 }
 
@@ -391,29 +397,40 @@ void group_tile_passes(const std::vector<Block> &blocks, int n, int precision, s
 {
     out.clear();
     const CostTable cost = lookup_costs(n, precision, nullptr);
-    for (const auto &grp : tile_groups(blocks, n)) {
-        // a block alone: its own dense launch, or a tile pass of one block
-        // where that is priced lower
-        const Block &b0 = blocks[grp[0]];
-        if (grp.size() == 1 && !(b0.k <= 4 && dev::tile_supported(n, 4) && cost.tile[1] < cost.ms[b0.k])) {
-            const Block &b = b0;
+    const bool fp64 = precision == SV_PREC_FP64;
+    for (const auto &grp : tile_groups(blocks, n))
+        for (size_t at = 0; at < grp.size();) {
+            // a pass planned for another arithmetic may cover more positions
+            // than an FP64 tile holds: as many of its blocks as fit
+            size_t end = grp.size();
+            if (fp64) {
+                uint64_t u = 0;
+                for (end = at; end < grp.size(); ++end) {
+                    const uint64_t v = u | mask_of(blocks[grp[end]]);
+                    if (end > at && __builtin_popcountll(v) > dev::kF64MaxUnion) break;
+                    u = v;
+                }
+            }
+            // a block alone: its own dense launch, or a tile pass of one block
+            // where that is priced lower
+            const Block &b0 = blocks[grp[at]];
             Launch L;
-            L.k = b.k;
-            std::copy(b.q, b.q + SV_MAX_K, L.q);
-            L.path = choose_path(SV_C64, precision, b.k, b.q, n);
-            L.m = b.m;
+            if (end - at == 1 && !(b0.k <= 4 && dev::tile_supported(n, 4) && cost.tile[1] < cost.ms[b0.k])) {
+                L.k = b0.k;
+                std::copy(b0.q, b0.q + SV_MAX_K, L.q);
+                L.path = choose_path(fp64 ? SV_C128 : SV_C64, precision, b0.k, b0.q, n);
+                L.m = b0.m;
+            } else {
+                L.path = tile_path(precision);
+                L.k = int(end - at);
+                std::fill(L.q, L.q + SV_MAX_K, 0);
+                std::vector<const Block *> bp;
+                for (size_t i = at; i < end; ++i) bp.push_back(&blocks[grp[i]]);
+                tile_pass_blocks(bp.data(), L.k, n, L.sub_pos, L.m);
+            }
             out.push_back(std::move(L));
-            continue;
+            at = end;
         }
-        Launch L;
-        L.path = tile_path(precision);
-        L.k = int(grp.size());
-        std::fill(L.q, L.q + SV_MAX_K, 0);
-        std::vector<const Block *> bp;
-        for (size_t b : grp) bp.push_back(&blocks[b]);
-        tile_pass_blocks(bp.data(), L.k, n, L.sub_pos, L.m);
-        out.push_back(std::move(L));
-    }
 }
 
 int enqueue(const std::vector<Launch> &launches, int dtype, void *psi, int n, const void *arena, hipStream_t st)
@@ -456,8 +473,9 @@ int enqueue(const Launch *first, size_t count, int dtype, void *psi, int n, cons
         if (is_tile_path(L.path)) {
             // one launch per chunk of blocks whose operands fit the shape's LDS
             const int cap = dev::tile_max_blocks(T.tile_bits, T.tile_waves, tile_operand_prec(L.path));
-            const size_t op_bytes = 4 * dev::kTileOperandWords;
-            const int grid_cap = T.tile_grid_cap * dev::tile_wgs_per_cu(T.tile_bits, T.tile_waves);
+            const size_t op_bytes = 4 * dev::tile_operand_words(tile_operand_prec(L.path));
+            const int grid_cap =
+                T.tile_grid_cap * (L.path == PATH_TILE_FP64 ? 1 : dev::tile_wgs_per_cu(T.tile_bits, T.tile_waves));
             const uint64_t n_tiles = uint64_t(1) << (n - T.tile_bits);
             const uint64_t grid = grid_cap > 0 && n_tiles > uint64_t(grid_cap) ? uint64_t(grid_cap) : n_tiles;
             const bool use_norm = L.path == PATH_TILE_FP16 && !psi2 && grid <= uint64_t(kTileNormSlots);

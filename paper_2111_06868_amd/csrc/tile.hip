@@ -34,6 +34,7 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float vf4 __attribute__((ext_vector_type(4)));
 typedef float vf2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -47,6 +48,11 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 // 64-bit values than FP32 MFMA (whose sums round 32 times) and does a block in
 // 2.8 instead of 5.0 us per tile.
 constexpr int kPrecX3 = kTileOperandF32, kPrecBF16 = kTileOperandBF16, kPrecF16 = kTileOperandF16;
+// FP64 passes of complex128 states run the same tile loop: n qubits of
+// complex128 lie in memory as n + 1 of complex64 whose position 0 chooses
+// between re and im, so layouts, tiles (2^13 amplitudes) and 16-byte copies
+// carry over; only the block arithmetic is their own (apply_block_f64).
+constexpr int kPrecF64 = kTileOperandF64;
 
 // LDS words per lane of one block's operand (the A' fragments of the 64
 // lanes): 8 per matrix part where every part is expanded at staging, so that
@@ -64,6 +70,10 @@ __device__ __forceinline__ uint32_t x3_expanded_at(uint32_t lane, uint32_t i)
 {
     return lane * 8 + 4 * (i ^ (((lane >> 2) ^ (lane >> 3)) & 1u));
 }
+// FP64 operands: entry (ci, j) of U sits at complex slot 16 ci + (j ^ f64_operand_swz(ci)),
+// so that the eight rows and two columns of one access hit distinct banks.
+__host__ __device__ constexpr uint32_t f64_operand_swz(uint32_t ci) { return 2u * (ci & 7u); }
+
 template <class C>
 __host__ __device__ constexpr bool x3_whole(int n_sub)
 {
@@ -197,6 +207,8 @@ struct TileCopy {
     // The same tile of a basis state, read from nowhere: zeros, and 1 at tile
     // index t when the basis state lies in this tile (`here`).  Thread tid's
     // chunk i holds tile indices 2 (tid + i THREADS) and the next one.
+    // (F64: tile index t holds the real part, a double.)
+    template <bool F64>
     __device__ __forceinline__ void basis(vf4 *buf, bool here, uint32_t t, int tid) const
     {
         const uint32_t pair = t >> 1;
@@ -204,7 +216,9 @@ struct TileCopy {
         for (int i = 0; i < kChunks; ++i) {
             buf[i] = vf4{0.f, 0.f, 0.f, 0.f};
             if (here && pair == uint32_t(tid) + uint32_t(i) * kThreads) {
-                if (t & 1u)
+                if (F64)
+                    buf[i].y = __uint_as_float(0x3FF00000u);  // the high word of 1.0
+                else if (t & 1u)
                     buf[i].z = 1.f;
                 else
                     buf[i].x = 1.f;
@@ -345,7 +359,8 @@ __device__ __forceinline__ void stage_blocks(TileShared<TB, WAVES, lane_words(PR
 {
     using C = TileCfg<TB, WAVES, lane_words(PREC)>;
     constexpr int CHUNKS = lane_words(PREC) / 4;  // 16-byte chunks per lane, each 4 consecutive compact words
-    constexpr bool X3 = PREC == kPrecX3;
+    constexpr bool X3 = PREC == kPrecX3, F64 = PREC == kPrecF64;
+    constexpr int STRIDE = F64 ? kTileOperandWordsF64 : kTileOperandWords;
     const int nsub = args.n_sub;
     const int per_block = 64 * (whole ? 6 : CHUNKS);
     const int units = nsub * per_block;
@@ -360,8 +375,11 @@ __device__ __forceinline__ void stage_blocks(TileShared<TB, WAVES, lane_words(PR
         Unit x;
         x.s = whole ? u / (64 * 6) : u / (64 * CHUNKS);
         const int r = u - x.s * per_block;
-        x.expand = !X3 || whole || r < 128;
-        if (X3) {
+        x.expand = !F64 && (!X3 || whole || r < 128);
+        if (F64) {
+            x.lane = r;
+            x.c = x.part = 0;
+        } else if (X3) {
             x.lane = x.expand ? (r & 127) >> 1 : (r & 63) >> 2;  // compact: the complex row
             x.c = x.expand ? r & 1 : r & 3;
             x.part = x.expand ? r >> 7 : 1 + ((r - 128) >> 6);
@@ -383,9 +401,10 @@ __device__ __forceinline__ void stage_blocks(TileShared<TB, WAVES, lane_words(PR
             if (u >= units) continue;
             const Unit x = unit_of(u);
             // X3: row 16 c + l16, columns 4 kg ..; else row l32, columns 8 i + 4 half ..
-            const int at = X3 ? (x.expand ? (8 * x.c + ((x.lane & 15) >> 1)) * 16 + 4 * (x.lane >> 4) : x.lane * 16 + 4 * x.c)
+            const int at = F64 ? 4 * x.lane
+                           : X3 ? (x.expand ? (8 * x.c + ((x.lane & 15) >> 1)) * 16 + 4 * (x.lane >> 4) : x.lane * 16 + 4 * x.c)
                               : ((x.lane & 31) >> 1) * 16 + 8 * (x.c & 1) + 4 * (x.lane >> 5);
-            v[d] = *reinterpret_cast<const vu4 *>(A + size_t(x.s) * kTileOperandWords + 256 * x.part + at);
+            v[d] = *reinterpret_cast<const vu4 *>(A + size_t(x.s) * STRIDE + 256 * x.part + at);
         }
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) {
@@ -395,7 +414,9 @@ __device__ __forceinline__ void stage_blocks(TileShared<TB, WAVES, lane_words(PR
             vu4 w = v[d];
             if (x.expand) w = x.lane & 1 ? (w >> 16) | (w << 16) : w ^ 0x80000000u;
             uint32_t to;
-            if (!X3)
+            if (F64)
+                to = 4 * uint32_t(x.lane);
+            else if (!X3)
                 to = uint32_t(x.lane) * lane_words(PREC) + 4 * (uint32_t(x.c) ^ frag_swz<lane_words(PREC)>(uint32_t(x.lane)));
             else if (x.expand)
                 to = 512 * uint32_t(x.part) + x3_expanded_at(uint32_t(x.lane), uint32_t(x.c));
@@ -774,6 +795,70 @@ __device__ __forceinline__ void apply_block_x3(TileShared<TB, WAVES, lane_words(
     }
 }
 
+// An FP64 block on the tile in LDS: 16 x 16 x 4 products, 2 row tiles x 8
+// steps for 16 columns.  Lane (kq, l16) holds K = 4 t + kq (t = 0..7), part
+// kq % 2 (re, im) of complex row 2 t + kq / 2 of column l16, and the products'
+// D real row 16 r + 4 v + kq is K = 4 (4 r + v) + kq: each lane writes the eight
+// 8-byte places it read.  Column c = (32 w + l16 + 16 g2) NBW + 2 q2 (its lowest
+// bit is the virtual position 0).  The block is bound by the FP64 matrix units
+// (3.4 us for a tile at their peak rate, 5.0 measured; the generic
+// kernel takes a whole state pass, at least 30 us, a block), so 8 waves with 4 column
+// groups each keep the operand (16 words a lane, read once a block) cheap.
+template <int TB, int WAVES>
+__device__ __forceinline__ void apply_block_f64(TileShared<TB, WAVES, lane_words(kPrecF64)> &sh, const TileArgs &args,
+                                                int s, int w, int lane)
+{
+    using C = TileCfg<TB, WAVES, lane_words(kPrecF64)>;
+    constexpr int NBW = C::NB_PER_WAVE;
+    char *Xb = reinterpret_cast<char *>(sh.X4);
+    const uint32_t kq = uint32_t(lane) >> 4, l16 = uint32_t(lane) & 15u;
+    uint32_t rb[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) rb[b] = args.swz[args.tbit[s][b]] << 3;
+    const uint32_t term = (kq & 2u ? rb[0] : 0u) | (kq & 1u) << 3;
+    // A'[16 r + l16][4 t + kq]: complex row 8 r + l16 / 2, column 2 t + kq / 2
+    double a[2][8];
+    const double *op = reinterpret_cast<const double *>(sh.op + s * C::OPERAND_WORDS);
+    const uint32_t ri = l16 & 1u, part = ri ^ (kq & 1u);
+    const uint64_t flip = uint64_t(!ri && (kq & 1u)) << 63;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const uint32_t ci = uint32_t(8 * r) + (l16 >> 1), j = uint32_t(2 * t) + (kq >> 1);
+            const double v = op[2 * (ci * 16 + (j ^ f64_operand_swz(ci))) + part];
+            a[r][t] = __longlong_as_double(__double_as_longlong(v) ^ flip);
+        }
+    // the next group's values are read before this one's are written (the
+    // compiler keeps LDS reads behind writes that might be to the same place)
+    uint32_t col[NBW];
+#pragma unroll
+    for (int g = 0; g < NBW; ++g)
+        col[g] = ((sh.cl[s][l16 + 16u * uint32_t(g & 1)] ^ sh.cq[s][w * NBW + (g & ~1)]) << 3) ^ term;
+    double b[2][8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) b[0][t] = *reinterpret_cast<const double *>(Xb + (row_of(rb, 2 * t) ^ col[0]));
+#pragma unroll
+    for (int g = 0; g < NBW; ++g) {
+        if (g + 1 < NBW) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                b[(g + 1) & 1][t] = *reinterpret_cast<const double *>(Xb + (row_of(rb, 2 * t) ^ col[g + 1]));
+        }
+        f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+                acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r][t], b[g & 1][t], acc[r], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                *reinterpret_cast<double *>(Xb + (row_of(rb, 2 * (4 * r + v)) ^ col[g])) = acc[r][v];
+    }
+}
+
 // The tile loop of one workgroup: tiles T, T + step, .. below T_end of the
 // state at psi.  A = the blocks' compact operands (pack_tile_operand), back to
 // back.  The host splits U into 16-bit parts, U = A_0 + A_1 + A_2 for
@@ -875,7 +960,7 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
     // basis state lies in the tile whose outside positions match its bits,
     // at the tile index its tile-position bits form (split FP16, and X3 in a
     // variant of its own, SCALE 4: the extra registers make it spill)
-    constexpr bool CAN_SYNTH = PREC == kPrecF16 || SCALE == 4;
+    constexpr bool CAN_SYNTH = PREC == kPrecF16 || PREC == kPrecF64 || SCALE == 4;
     const bool synth = CAN_SYNTH && norm.basis >= 0;  // uniform
     uint64_t b_out = 0;
     uint32_t b_t = 0;
@@ -890,7 +975,7 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
     }
     auto fetch = [&](vf4 *into, uint64_t base) {
         if (synth)
-            cp.basis(into, base == b_out, b_t, tid);
+            cp.template basis<PREC == kPrecF64>(into, base == b_out, b_t, tid);
         else
             cp.load(into, psi, base);
     };
@@ -933,7 +1018,9 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
             __builtin_amdgcn_s_setprio(0);
         }
         for (int s = 0; s < args.n_sub; ++s) {
-            if constexpr (PREC == kPrecX3)
+            if constexpr (PREC == kPrecF64)
+                apply_block_f64<TB, WAVES>(sh, args, s, w, lane);
+            else if constexpr (PREC == kPrecX3)
                 apply_block_x3<TB, WAVES>(sh, args, s, w, lane, whole);
             else
                 apply_block<TB, WAVES, PREC, F16 && !PER_TILE ? 1 : 0>(sh, args, s, w, half, l32, scale, unscale);
@@ -996,7 +1083,12 @@ hipError_t tile_launch(const TileArgs &a, const void *d_a, int prec, float *psi,
     const dim3 block(64 * WAVES);
     TileNorm plain;  // the variants without the norm take only the basis start
     plain.basis = norm.basis;
-    if (prec == kPrecBF16)
+    if (prec == kPrecF64) {
+        if constexpr (TB == kF64TileBits && WAVES == kF64TileWaves)
+            hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF64, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
+        else
+            return hipErrorInvalidValue;
+    } else if (prec == kPrecBF16)
         hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecBF16, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
     else if (prec == kPrecF16 && norm.in && norm.in_scaled && norm.out_scaled)
         hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF16, 3>), grid, block, 0, st, psi, A, a, psi2, norm);
@@ -1046,6 +1138,7 @@ int tile_max_blocks(int tile_bits, int waves, int prec)
 {
     if (!tile_shape_supported(tile_bits, waves)) return 0;
     // BF16X3's limit is that of split BF16, though its operands are smaller
+    if (prec == kTileOperandF64) return max_blocks_of<16>(kF64TileBits, kF64TileWaves);
     return prec == kTileOperandBF16 || prec == kTileOperandBF16X3 ? max_blocks_of<24>(tile_bits, waves)
                                                                    : max_blocks_of<16>(tile_bits, waves);
 }
@@ -1084,6 +1177,16 @@ static float bf2f(uint32_t h)
 
 void pack_tile_operand(const cd *m, int prec, uint32_t *out)
 {
+    if (prec == kTileOperandF64) {
+        double *d = reinterpret_cast<double *>(out);
+        for (uint32_t r = 0; r < 16; ++r)
+            for (uint32_t c = 0; c < 16; ++c) {
+                const uint32_t at = r * 16 + (c ^ f64_operand_swz(r));
+                d[2 * at] = m[r * 16 + c].real();
+                d[2 * at + 1] = m[r * 16 + c].imag();
+            }
+        return;
+    }
     std::memset(out, 0, sizeof(uint32_t) * kTileOperandWords);
     for (int r = 0; r < 16; ++r)
         for (int c = 0; c < 16; ++c) {
@@ -1163,10 +1266,23 @@ hipError_t launch_tile_pass(int n_sub, const int (*sub_pos)[4], const void *d_a,
         return hipErrorInvalidValue;
     if ((norm.in_scaled || norm.out_scaled) && !norm.in) return hipErrorInvalidValue;
     if (norm.basis >= 0 && (psi2 || n >= 63 || (uint64_t(norm.basis) >> n) != 0 || norm.in_scaled ||
-                            (prec != kTileOperandF32 && prec != kTileOperandF16)))
+                            (prec != kTileOperandF32 && prec != kTileOperandF16 && prec != kTileOperandF64)))
         return hipErrorInvalidValue;
-    if (prec != kTileOperandF32 && prec != kTileOperandBF16 && prec != kTileOperandF16 && prec != kTileOperandBF16X3)
-        return hipErrorInvalidValue;
+    if (prec < kTileOperandF32 || prec > kTileOperandF64) return hipErrorInvalidValue;
+    if (prec == kTileOperandF64) {
+        // virtual position 0 is re / im: every position moves up by one
+        if (n_sub < 1 || n_sub > tile_max_blocks(kF64TileBits, kF64TileWaves, prec)) return hipErrorInvalidValue;
+        int pos[kMaxTileSubBlocks][4];
+        for (int s = 0; s < n_sub; ++s)
+            for (int i = 0; i < 4; ++i) pos[s][i] = sub_pos[s][i] + 1;
+        TileArgs a;
+        if (hipError_t e = make_tile_args(n_sub, pos, n + 1, kF64TileBits, kF64TileWaves, prec, &a)) return e;
+        if (a.ubit[0] != 0) return hipErrorInvalidValue;  // a union of 14 positions leaves no place for it
+        TileNorm nv = norm;
+        if (nv.basis >= 0) nv.basis <<= 1;
+        return tile_launch<kF64TileBits, kF64TileWaves>(a, d_a, prec, static_cast<float *>(psi), static_cast<float *>(psi2),
+                                                        st, grid_cap, nv, grid_out);
+    }
     if (!tile_shape_supported(tile_bits, waves)) return hipErrorInvalidValue;
     if (n_sub < 1 || n_sub > tile_max_blocks(tile_bits, waves, prec)) return hipErrorInvalidValue;
     TileArgs a;
