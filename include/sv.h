@@ -74,7 +74,8 @@ extern "C" {
 /* fusion rules (sv_fuse) */
 #define SV_RULE_PAPER 0    /* the paper's compress() rule, reproduced exactly    */
 #define SV_RULE_ENHANCED 1 /* paper rule, then cost-aware merging of blocks      */
-#define SV_RULE_NONE 2     /* one block per gate (plain per-gate application)    */
+#define SV_RULE_NONE 2     /* one block per gate (plain per-gate application; a  */
+                           /* run of small gates may share a state pass)         */
 #define SV_RULE_TILED 3    /* enhanced blocks of <= 4 qubits, grouped into LDS   */
                            /* tile passes (see sv_run_circuit)                   */
 #define SV_RULE_AUTO 4     /* the cheaper of ENHANCED and TILED plans, and its k, */
@@ -257,7 +258,8 @@ int sv_apply_plan(sv_state *s, const sv_plan *p, int precision, int use_graph);
  * 'evolution')).  Nothing is applied if any gate is invalid.  Asynchronous
  * (use_graph as for sv_apply_plan).  o == NULL means plain per-gate
  * application: {SV_MAX_K, FP32 or FP64 by amplitude type, SV_RULE_NONE, 0}.
- * With SV_RULE_TILED on a complex64 state of >= 14 qubits, the gates are
+ * With SV_RULE_TILED on a state of >= 14 qubits (complex64 below; complex128
+ * likewise, with FP64 MFMA and tiles of 2^13 amplitudes), the gates are
  * grouped into passes whose positions U leave contiguous HBM runs no shorter
  * than those of a union of sv_set_tile_union() positions (default 10): the
  * tile of a pass is U plus the lowest positions outside it, 14 (or 13) in
@@ -285,7 +287,7 @@ int sv_apply_plan(sv_state *s, const sv_plan *p, int precision, int use_graph);
 int sv_run_circuit(sv_state *s, const sv_gate *g, int G, const sv_run_opts *o);
 /* sv_set_basis(s, basis) followed by sv_run_circuit(s, g, G, o) (paper,
  * Simulations section: simulate with a computational-basis initial state),
- * as one call: when the plan starts with an FP32 or split-FP16 tile pass,
+ * as one call: when the plan starts with an FP32, FP64 or split-FP16 tile pass,
  * that pass produces the basis state itself and reads nothing from HBM (the
  * state's earlier contents are not read; no fill runs); otherwise the state
  * is filled first.
@@ -686,7 +688,10 @@ int sv_stream_probe(sv_state *s, uint64_t tile_positions, int reps, double *ms_p
  * split-BF16 tile passes, 11 = split-FP16 tile passes; k is the block size,
  * for tile passes the number of blocks in the launch, and for reductions 1 =
  * norm, 2 = inner product, 3 = expectation, 4 = Pauli-sum matvec, 5 =
- * density-matrix trace Tr(rho H), 6 = Kraus outcome weights. */
+ * density-matrix trace Tr(rho H), 6 = Kraus outcome weights.  Family 13 = FP64
+ * tile passes (complex128), 12 = BF16X3.  A pass that applies several gates of
+ * at most 3 qubits one by one counts each of them in its class of family 1,
+ * with its share of the pass's time. */
 int sv_stats_enable(int on);
 /* Graph runs of a state (use_graph = 1 calls): their count and how many of
  * them reused the state's instantiated graph (updated in place). */

@@ -135,12 +135,12 @@ int run_launches(sv_state *s, std::vector<Launch> &launches, bool use_graph)
     return SV_OK;
 }
 
-void blocks_to_launches(const std::vector<Block> &blocks, const sv_state *s, int precision, int rule,
-                        std::vector<Launch> &out)
+int blocks_to_launches(const std::vector<Block> &blocks, const sv_state *s, int precision, int rule,
+                       std::vector<Launch> &out)
 {
     if (rule == SV_RULE_TILED) {
         group_tile_passes(blocks, s->n, precision, out);
-        return;
+        return SV_OK;
     }
     out.clear();
     out.reserve(blocks.size());
@@ -152,6 +152,7 @@ void blocks_to_launches(const std::vector<Block> &blocks, const sv_state *s, int
         L.m = b.m;
         out.push_back(std::move(L));
     }
+    return group_gate_passes(out, s->n, s->dtype);
 }
 
 int choose_plan_uncached(const sv_gate *g, int G, int n, int dtype, int precision, int rule, int max_k, bool found,
@@ -588,7 +589,7 @@ extern "C" int sv_apply_plan(sv_state *s, const sv_plan *p, int precision, int u
             if (int rc = check_unitary(p->blocks[i].m, p->blocks[i].k, what.c_str())) return rc;
         }
     std::vector<Launch> L;
-    blocks_to_launches(p->blocks, s, precision, p->rule, L);
+    if (int rc = blocks_to_launches(p->blocks, s, precision, p->rule, L)) return rc;
     if (int rc = select_device(s)) return rc;
     return run_launches(s, L, use_graph != 0);
 }
@@ -623,7 +624,7 @@ int run_circuit_impl(sv_state *s, const sv_gate *g, int G, const sv_run_opts *o,
                             o->precision))
         return rc;
     std::vector<Launch> L;
-    blocks_to_launches(blocks, s, o->precision, rule, L);
+    if (int rc = blocks_to_launches(blocks, s, o->precision, rule, L)) return rc;
     if (int rc = select_device(s)) return rc;
     if (basis >= 0) {
         // FP32, FP64 and split-FP16 tile passes start from the basis state

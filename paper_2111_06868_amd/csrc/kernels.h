@@ -139,6 +139,18 @@ struct TileNorm {
 hipError_t launch_tile_pass(int n_sub, const int (*sub_pos)[4], const void *d_a, int prec, void *psi, int n,
                             hipStream_t st, int grid_cap, int tile_bits, int waves, void *psi2 = nullptr,
                             const TileNorm &norm = TileNorm{}, int *grid_out = nullptr);
+// Gate passes: up to tile_max_blocks(14, 8, kTileOperandF32) stages of gates of
+// at most 3 qubits, each stage on 4 positions (rows of pos, ascending; their
+// union at most 14, complex128: 13), applied gate by gate in one HBM pass.
+// d_ops: kGateHeaderWords words (stage s's ops are [d_ops[s], d_ops[s + 1])),
+// two words per op (gate_code of the stage's row bits it acts on, ascending;
+// offset of its canonical interleaved matrix in values of the state's real
+// type), the matrices (16-byte aligned).  Needs n >= kMinTileQubits.
+constexpr int kGateHeaderWords = 32;
+static_assert(kMaxTileSubBlocks + 1 <= kGateHeaderWords, "stage ranges");
+int gate_code(int k, const int *bits);
+hipError_t launch_gate_pass(int n_stages, const int (*pos)[4], const void *d_ops, int dtype, void *psi, int n,
+                            hipStream_t st, int grid_cap, void *psi2);
 // Host-side packing of the MFMA operands of a canonical k-qubit matrix.
 void pack_real_form_f32(const cd *m, int k, float *out);
 // Split parts: part p = RNE(A' - parts before it), three for BF16, two for

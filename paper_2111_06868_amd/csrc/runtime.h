@@ -58,15 +58,18 @@ enum Family {
 inline int stat_class(int family, int k) { return 100 * family + k; }
 
 // RAII: brackets one launch with HIP events on `st` when timing is enabled.
+// `parts` (optional): how many gates of 1, 2 and 3 qubits the launch applies;
+// each counts in the register kernel's class with its share of the time.
 class LaunchTimer {
   public:
-    LaunchTimer(int cls, hipStream_t st);
+    LaunchTimer(int cls, hipStream_t st, const int *parts = nullptr);
     ~LaunchTimer();
     LaunchTimer(const LaunchTimer &) = delete;
     LaunchTimer &operator=(const LaunchTimer &) = delete;
 
   private:
     int cls_;
+    int parts_[4] = {0, 0, 0, 0};
     hipStream_t st_;
     hipEvent_t a_ = nullptr, b_ = nullptr;
 };
@@ -84,7 +87,8 @@ enum Path {
     PATH_TILE_BF16,
     PATH_TILE_FP16,
     PATH_TILE_BF16X3,
-    PATH_TILE_FP64
+    PATH_TILE_FP64,
+    PATH_GATES
 };
 
 // Tile passes: PATH_TILE, PATH_TILE_BF16, PATH_TILE_FP16, PATH_TILE_BF16X3, PATH_TILE_FP64.
@@ -115,6 +119,8 @@ struct Launch {
     size_t arena_off2 = 0; // second and third operands (split parts 1 and 2)
     size_t arena_off3 = 0;
     size_t norm_off = 0;   // split-FP16 tile paths: byte offset of the run's norm partials
+    std::vector<int> stage_gates;           // PATH_GATES: number of gates of each of the k stages
+    std::vector<std::pair<int, int>> gates; // PATH_GATES: (qubits, gate_code) of each gate; m holds their matrices
     int64_t basis = -1;    // tile paths, >= 0: the launch's first chunk starts the state from |basis>
 };
 // Doubles the norm partials of a run's split-FP16 tile passes may take (one
@@ -132,6 +138,10 @@ void tile_pass_blocks(const Block *const *blocks, int count, int n, int (*sub_po
 // Group consecutive blocks into tile passes (see tile.hip); blocks that do not
 // join a group keep their own launch.
 void group_tile_passes(const std::vector<Block> &blocks, int n, int precision, std::vector<Launch> &out);
+// Replace runs of launches of single gates (PATH_REG, at most 3 qubits) by gate
+// passes (see tile.hip), for states of at least dev::kMinTileQubits qubits.
+// Gates move only where every qubit keeps its own gate order.
+int group_gate_passes(std::vector<Launch> &launches, int n, int dtype);
 // The tile path of a precision (FP32, split BF16, split FP16) and the operand
 // format of a tile path.
 Path tile_path(int precision);

@@ -58,6 +58,7 @@ void PinBuf::release()
 namespace {
 struct Pending {
     int cls;
+    int parts[4];
     hipEvent_t a, b;
 };
 struct StatsState {
@@ -95,9 +96,13 @@ int drain(StatsState &s)
         if (e != hipSuccess) {
             rc = fail(SV_ERR_HIP, "launch timing: %s", hipGetErrorString(e));
         } else {
-            auto &t = s.totals[p.cls];
-            t.first += 1;
-            t.second += ms;
+            const int sum = p.parts[1] + p.parts[2] + p.parts[3];
+            for (int k = sum ? 1 : 0; k <= (sum ? 3 : 0); ++k) {
+                if (sum && !p.parts[k]) continue;
+                auto &t = s.totals[sum ? stat_class(FAM_REG, k) : p.cls];
+                t.first += sum ? p.parts[k] : 1;
+                t.second += sum ? ms * p.parts[k] / sum : ms;
+            }
         }
         s.free_events.push_back(p.a);
         s.free_events.push_back(p.b);
@@ -107,8 +112,9 @@ int drain(StatsState &s)
 }
 }  // namespace
 
-LaunchTimer::LaunchTimer(int cls, hipStream_t st) : cls_(cls), st_(st)
+LaunchTimer::LaunchTimer(int cls, hipStream_t st, const int *parts) : cls_(cls), st_(st)
 {
+    for (int k = 1; parts && k <= 3; ++k) parts_[k] = parts[k];
     auto &s = stats();
     std::lock_guard<std::mutex> lk(s.mu);
     if (!s.on || s.suspended) return;
@@ -123,7 +129,7 @@ LaunchTimer::~LaunchTimer()
     auto &s = stats();
     std::lock_guard<std::mutex> lk(s.mu);
     (void)hipEventRecord(b_, st_);
-    s.pending.push_back({cls_, a_, b_});
+    s.pending.push_back({cls_, {parts_[0], parts_[1], parts_[2], parts_[3]}, a_, b_});
     if (s.pending.size() > 4096) drain(s);
 }
 
@@ -214,7 +220,8 @@ Path choose_path(int dtype, int precision, int k, const int *q, int n)
 int path_family(Path p)
 {
     switch (p) {
-    case PATH_REG: return FAM_REG;
+    case PATH_REG:
+    case PATH_GATES: return FAM_REG;
     case PATH_GENERIC: return FAM_GENERIC;
     case PATH_MFMA32: return FAM_MFMA32;
     case PATH_SPLIT_BF16: return FAM_SPLIT_BF16;
@@ -228,6 +235,34 @@ int path_family(Path p)
 }
 
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// The operand of a gate pass (launch_gate_pass): stage ranges, ops, matrices.
+static size_t gate_pass_ops_bytes(const Launch &L) { return (4 * dev::kGateHeaderWords + 8 * L.gates.size() + 15) & ~size_t(15); }
+static size_t gate_pass_bytes(const Launch &L, int dtype)
+{
+    return gate_pass_ops_bytes(L) + L.m.size() * 2 * (dtype == SV_C64 ? 4 : 8);
+}
+template <typename T>
+static void pack_gate_pass(const Launch &L, char *h)
+{
+    uint32_t *w = reinterpret_cast<uint32_t *>(h);
+    uint32_t at = 0;
+    for (int s = 0; s <= dev::kMaxTileSubBlocks; ++s) {
+        w[s] = at;
+        if (s < L.k) at += uint32_t(L.stage_gates[size_t(s)]);
+    }
+    T *m = reinterpret_cast<T *>(h + gate_pass_ops_bytes(L));
+    for (size_t i = 0; i < L.m.size(); ++i) {
+        m[2 * i] = T(L.m[i].real());
+        m[2 * i + 1] = T(L.m[i].imag());
+    }
+    size_t off = gate_pass_ops_bytes(L) / sizeof(T);
+    for (size_t g = 0; g < L.gates.size(); ++g) {
+        w[dev::kGateHeaderWords + 2 * g] = uint32_t(L.gates[g].second);
+        w[dev::kGateHeaderWords + 2 * g + 1] = uint32_t(off);
+        off += size_t(2) << (2 * L.gates[g].first);
+    }
+}
 
 size_t pack_operands(std::vector<Launch> &launches, int dtype, PinBuf &stage)
 {
@@ -252,6 +287,10 @@ size_t pack_operands(std::vector<Launch> &launches, int dtype, PinBuf &stage)
         case PATH_TILE_FP64:
             L.arena_off = total;
             total = align256(total + size_t(L.k) * dev::tile_operand_words(tile_operand_prec(L.path)) * 4);
+            break;
+        case PATH_GATES:
+            L.arena_off = total;
+            total = align256(total + gate_pass_bytes(L, dtype));
             break;
         default:
             L.arena_off = total;
@@ -305,6 +344,10 @@ size_t pack_operands(std::vector<Launch> &launches, int dtype, PinBuf &stage)
                 dev::pack_tile_operand(L.m.data() + 256 * sb, tile_operand_prec(L.path),
                                        reinterpret_cast<uint32_t *>(h + L.arena_off) +
                                            dev::tile_operand_words(tile_operand_prec(L.path)) * sb);
+            break;
+        case PATH_GATES:
+            if (dtype == SV_C64) pack_gate_pass<float>(L, h + L.arena_off);
+            else pack_gate_pass<double>(L, h + L.arena_off);
             break;
         default: {
             uint16_t *const parts[3] = {reinterpret_cast<uint16_t *>(h + L.arena_off),
@@ -372,23 +415,30 @@ int tile_operand_prec(int path)
                                       : dev::kTileOperandF32;
 }
 
-void tile_pass_blocks(const Block *const *blocks, int count, int n, int (*sub_pos)[4], std::vector<cd> &mats)
+// The positions of tile_pass_blocks' padded blocks.
+static void tile_pass_positions(const Block *const *blocks, int count, int n, int (*sub_pos)[4])
 {
     uint64_t um = 0;
     for (int i = 0; i < count; ++i) um |= mask_of(*blocks[i]);
     // the union gets at least 4 positions (lowest free ones)
     for (int p = 0; p < n && __builtin_popcountll(um) < 4; ++p) um |= uint64_t(1) << p;
-    mats.clear();
     for (int sb = 0; sb < count; ++sb) {
-        const Block &b = *blocks[sb];
-        uint64_t pm = mask_of(b);
+        uint64_t pm = mask_of(*blocks[sb]);
         for (int p = 0; p < 64 && __builtin_popcountll(pm) < 4; ++p)
             if (((um >> p) & 1) && !((pm >> p) & 1)) pm |= uint64_t(1) << p;
         int c = 0;
         for (int p = 0; p < 64; ++p)
             if ((pm >> p) & 1) sub_pos[sb][c++] = p;
+    }
+}
+
+void tile_pass_blocks(const Block *const *blocks, int count, int n, int (*sub_pos)[4], std::vector<cd> &mats)
+{
+    tile_pass_positions(blocks, count, n, sub_pos);
+    mats.clear();
+    for (int sb = 0; sb < count; ++sb) {
         std::vector<cd> m4;
-        pad_to_four(b, sub_pos[sb], m4);
+        pad_to_four(*blocks[sb], sub_pos[sb], m4);
         mats.insert(mats.end(), m4.begin(), m4.end());
     }
 }
@@ -433,6 +483,61 @@ void group_tile_passes(const std::vector<Block> &blocks, int n, int precision, s
         }
 }
 
+int group_gate_passes(std::vector<Launch> &launches, int n, int dtype)
+{
+    if (n < dev::kMinTileQubits) return SV_OK;
+    const int precision = dtype == SV_C64 ? SV_PREC_FP32 : SV_PREC_FP64;
+    auto small = [](const Launch &L) { return L.path == PATH_REG && L.k <= 3; };
+    std::vector<Launch> out;
+    for (size_t at = 0; at < launches.size();) {
+        size_t end = at;
+        while (end < launches.size() && small(launches[end])) ++end;
+        if (end - at < 2) {
+            out.push_back(std::move(launches[at++]));
+            continue;
+        }
+        // stages and passes of the run: blocks of <= 4 positions in tile passes
+        std::vector<sv_gate> g(end - at);
+        for (size_t i = at; i < end; ++i) {
+            g[i - at].k = launches[i].k;
+            std::copy(launches[i].q, launches[i].q + launches[i].k, g[i - at].q);
+        }
+        std::vector<Block> blocks;
+        if (int rc = fuse_gates(g.data(), int(g.size()), n, 4, SV_RULE_TILED, default_costs(), blocks, false, precision)) return rc;
+        const size_t cap = size_t(dev::tile_max_blocks(14, 8, dev::kTileOperandF32));
+        for (const auto &grp : tile_groups(blocks, n))
+            for (size_t c = 0; c < grp.size(); c += cap) {
+                const size_t stop = std::min(grp.size(), c + cap);
+                if (stop - c == 1 && blocks[grp[c]].members.size() == 1) {  // a gate alone
+                    out.push_back(std::move(launches[at + size_t(blocks[grp[c]].members[0])]));
+                    continue;
+                }
+                Launch P;
+                P.path = PATH_GATES;
+                P.k = int(stop - c);
+                std::fill(P.q, P.q + SV_MAX_K, 0);
+                std::vector<const Block *> bp;
+                for (size_t i = c; i < stop; ++i) bp.push_back(&blocks[grp[i]]);
+                tile_pass_positions(bp.data(), P.k, n, P.sub_pos);
+                for (int s = 0; s < P.k; ++s) {
+                    P.stage_gates.push_back(int(bp[size_t(s)]->members.size()));
+                    for (int mem : bp[size_t(s)]->members) {
+                        const Launch &G = launches[at + size_t(mem)];
+                        int b[3] = {0, 0, 0};
+                        for (int j = 0; j < G.k; ++j)
+                            while (P.sub_pos[s][b[j]] != G.q[j]) ++b[j];
+                        P.gates.push_back({G.k, dev::gate_code(G.k, b)});
+                        P.m.insert(P.m.end(), G.m.begin(), G.m.end());
+                    }
+                }
+                out.push_back(std::move(P));
+            }
+        at = end;
+    }
+    launches.swap(out);
+    return SV_OK;
+}
+
 int enqueue(const std::vector<Launch> &launches, int dtype, void *psi, int n, const void *arena, hipStream_t st)
 {
     return enqueue(launches.data(), launches.size(), dtype, psi, n, arena, st);
@@ -464,7 +569,8 @@ int enqueue(const Launch *first, size_t count, int dtype, void *psi, int n, cons
     int norm_grid = 0, norm_done = 0;
     for (const Launch *it = first; it != first + count; ++it) {
         const Launch &L = *it;
-        if (psi2 && L.path != PATH_REG && L.path != PATH_GENERIC && L.path != PATH_MFMA32 && !is_tile_path(L.path)) {
+        if (psi2 && L.path != PATH_REG && L.path != PATH_GENERIC && L.path != PATH_MFMA32 && L.path != PATH_GATES &&
+            !is_tile_path(L.path)) {
             // paths without a second-state launch: one launch per state
             if (int rc = enqueue(it, 1, dtype, psi, n, arena, st)) return rc;
             if (int rc = enqueue(it, 1, dtype, psi2, n, arena, st)) return rc;
@@ -506,9 +612,14 @@ int enqueue(const Launch *first, size_t count, int dtype, void *psi, int n, cons
             }
             continue;
         }
-        LaunchTimer timer(stat_class(path_family(L.path), L.k), st);
+        int parts[4] = {0, 0, 0, 0};
+        for (const auto &g : L.gates) ++parts[g.first];
+        LaunchTimer timer(stat_class(path_family(L.path), L.k), st, L.path == PATH_GATES ? parts : nullptr);
         hipError_t e = hipSuccess;
         switch (L.path) {
+        case PATH_GATES:
+            e = dev::launch_gate_pass(L.k, L.sub_pos, A + L.arena_off, dtype, psi, n, st, T.tile_grid_cap, psi2);
+            break;
         case PATH_REG: e = dev::launch_reg(dtype, L.k, L.q, L.m.data(), psi, n, st, T.reg_grid_cap[L.k], psi2); break;
         case PATH_GENERIC: e = dev::launch_generic(dtype, L.k, L.q, A + L.arena_off, psi, n, st, psi2); break;
         case PATH_MFMA32:
