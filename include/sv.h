@@ -332,9 +332,9 @@ int sv_apply_pauli_sum(sv_state *psi, const sv_pauli_sum *H, sv_state *out);
  * back with psi: two buffers, no stored trajectory).  For every gate with
  * param >= 0 (which must be SV_G_RX, SV_G_RY or SV_G_RZ),
  * grad[param] += dE/dtheta = Im <lam|P|phi>, accumulated in FP64; other
- * entries are untouched, so the caller zeroes grad first.  A run of
- * consecutive rotations on distinct qubits shares one gradient pass (they
- * commute); runs of other gates are undone as fused dagger blocks.
+ * entries are untouched, so the caller zeroes grad first.  The rotations of a
+ * run of one-qubit gates share one gradient pass, however many lie on a qubit;
+ * the gates between two passes are undone as fused dagger blocks.
  * Synchronises.  Errors: SV_ERR_ARG (param >= n_params, a param on a
  * non-rotation). */
 int sv_backward(sv_state *psi, sv_state *scratch, const sv_gate *g, int G, const sv_pauli_sum *H,

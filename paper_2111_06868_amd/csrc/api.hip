@@ -1374,16 +1374,48 @@ extern "C" int sv_apply_pauli_sum(sv_state *psi, const sv_pauli_sum *H, sv_state
 // ============================================================== adjoint
 namespace {
 
-// One step of the backward sweep (gates are visited from last to first).
+// One step of the backward sweep (gates are visited from last to first): the
+// transition sums of a run's qubits, then the launches that undo its gates and
+// those before it up to the next rotation with a parameter.
 struct BwdStep {
-    enum Kind { SINGLE, RUN, UNDO } kind;
-    int gate = -1;        // SINGLE: the gate
-    int slot = -1;        // SINGLE: gradient slot or -1; RUN: first slot
-    int n_terms = 0;      // RUN: rotations in the run
-    uint64_t x[dev::kMaxGradTerms] = {}, z[dev::kMaxGradTerms] = {};
-    int pw[dev::kMaxGradTerms] = {};
-    size_t l0 = 0, l1 = 0;  // RUN / UNDO: launches [l0, l1) that undo the gates
+    int lo = 0, hi = -1;      // the run of one-qubit gates lo..hi (hi: a parameterised one), or empty
+    std::vector<int> qubits;  // its qubits with parameterised gates
+    int slot = -1;            // the first one's slot
+    size_t l0 = 0, l1 = 0;    // launches [l0, l1) that undo gates
 };
+
+// dE/dtheta of the run's parameterised gates from its qubits' sums v (8 doubles
+// each: S, Z, A, B), added to grad.  The generator P of a gate is Im <lam| V P
+// V^dagger |phi> with V the run's later gates on its qubit.
+int run_gradients(const sv_gate *g, const BwdStep &st, const double *v, double *grad)
+{
+    for (size_t k = 0; k < st.qubits.size(); ++k) {
+        auto sum = [&](int i) { return cd(v[8 * k + 2 * i], v[8 * k + 2 * i + 1]); };
+        const cd M[2][2] = {{0.5 * (sum(0) + sum(1)), 0.5 * (sum(2) + sum(3))},
+                            {0.5 * (sum(2) - sum(3)), 0.5 * (sum(0) - sum(1))}};
+        cd V[2][2] = {{1, 0}, {0, 1}};
+        for (int t = st.hi; t >= st.lo; --t) {
+            if (g[t].q[0] != st.qubits[k]) continue;
+            if (g[t].param >= 0) {
+                static const cd P[3][2][2] = {{{0, 1}, {1, 0}}, {{0, cd(0, -1)}, {cd(0, 1), 0}}, {{1, 0}, {0, -1}}};
+                const cd(&p)[2][2] = P[g[t].kind == SV_G_RX ? 0 : g[t].kind == SV_G_RY ? 1 : 2];
+                cd e = 0;  // sum_ab (V P V^dagger)_ab M_ab
+                for (int a = 0; a < 2; ++a)
+                    for (int b = 0; b < 2; ++b)
+                        for (int x = 0; x < 2; ++x)
+                            for (int y = 0; y < 2; ++y) e += V[a][x] * p[x][y] * std::conj(V[b][y]) * M[a][b];
+                grad[g[t].param] += e.imag();
+            }
+            std::vector<cd> U;
+            if (int rc = gate_matrix_abi(g[t], U)) return rc;
+            cd W[2][2];
+            for (int a = 0; a < 2; ++a)
+                for (int b = 0; b < 2; ++b) W[a][b] = V[a][0] * U[size_t(b)] + V[a][1] * U[size_t(2 + b)];
+            std::memcpy(static_cast<void *>(V), W, sizeof V);
+        }
+    }
+    return SV_OK;
+}
 
 // Fuse the daggers of gates hi, hi-1, .., lo (in that order) into blocks and
 // append their launches.
@@ -1531,68 +1563,36 @@ int backward_impl(sv_state *psi, sv_state *scratch, const sv_gate *g, int G, con
     for (int i = 0; i < G; ++i)
         if (g[i].param >= n_params) return fail(SV_ERR_ARG, "gate %d: param %d >= n_params %d", i, g[i].param, n_params);
 
-    // plan the sweep: runs of rotations on distinct qubits share one gradient
-    // pass (they commute, so each sees the same phi and lam); runs of
-    // non-parameterised gates are undone as fused dagger blocks
+    // plan the sweep: every run of one-qubit gates that ends in a parameterised
+    // one shares one pass of transition sums; it is undone together with the
+    // gates before it, down to the next parameterised one
     std::vector<BwdStep> steps;
     std::vector<Launch> launches;
-    std::vector<int> slot_param;
     struct RunJob {
         int hi, lo;
         size_t step;
     };
-    std::vector<RunJob> jobs;  // dagger runs: gates hi..lo, undone at steps[step]
-    int i = G - 1;
-    while (i >= 0) {
-        if (g[i].param >= 0) {
-            uint64_t used = 0;
-            int j = i;
-            while (j >= 0 && g[j].param >= 0 && g[j].k == 1 && !((used >> g[j].q[0]) & 1) &&
-                   i - j < dev::kMaxGradTerms) {
-                used |= uint64_t(1) << g[j].q[0];
-                --j;
-            }
-            if (i - j >= 2) {
-                BwdStep st;
-                st.kind = BwdStep::RUN;
-                st.slot = int(slot_param.size());
-                for (int t = i; t > j; --t) {
-                    const uint64_t b = uint64_t(1) << g[t].q[0];
-                    const int e = st.n_terms++;
-                    st.x[e] = g[t].kind == SV_G_RZ ? 0 : b;
-                    st.z[e] = g[t].kind == SV_G_RX ? 0 : b;
-                    st.pw[e] = g[t].kind == SV_G_RY ? 1 : 0;
-                    slot_param.push_back(g[t].param);
-                }
-                jobs.push_back({i, j + 1, steps.size()});
-                steps.push_back(st);
-                i = j;
-                continue;
-            }
-            BwdStep st;
-            st.kind = BwdStep::SINGLE;
-            st.gate = i;
-            st.slot = int(slot_param.size());
-            slot_param.push_back(g[i].param);
-            steps.push_back(st);
-            --i;
-            continue;
-        }
-        int j = i;
-        while (j >= 0 && g[j].param < 0) --j;
-        if (i - j == 1 && g[i].k <= 2) {
-            BwdStep st;
-            st.kind = BwdStep::SINGLE;
-            st.gate = i;
-            steps.push_back(st);
-            --i;
-            continue;
-        }
+    std::vector<RunJob> jobs;  // gates hi..lo, undone at steps[step]
+    int slots = 0;
+    for (int i = G - 1; i >= 0;) {
         BwdStep st;
-        st.kind = BwdStep::UNDO;
-        jobs.push_back({i, j + 1, steps.size()});
-        steps.push_back(st);
-        i = j;
+        int stop = i;  // the last gate that is not undone in this step
+        if (g[i].param >= 0) {
+            st.hi = i;
+            int j = i;
+            uint64_t used = 0;
+            for (; j >= 0 && g[j].k == 1; --j)
+                if (g[j].param >= 0) used |= uint64_t(1) << g[j].q[0];
+            st.lo = j + 1;
+            for (uint64_t m = used; m; m &= m - 1) st.qubits.push_back(__builtin_ctzll(m));
+            st.slot = slots;
+            slots += int(st.qubits.size());
+            stop = j;
+        }
+        while (stop >= 0 && g[stop].param < 0) --stop;
+        jobs.push_back({i, stop + 1, steps.size()});
+        steps.push_back(std::move(st));
+        i = stop;
     }
     // the dagger blocks of the runs are independent host work: spread over
     // threads, then appended in sweep order
@@ -1621,8 +1621,6 @@ int backward_impl(sv_state *psi, sv_state *scratch, const sv_gate *g, int G, con
             st.l1 = launches.size();
         }
     }
-    const int slots = int(slot_param.size());
-
     if (int rc = select_device(psi)) return rc;
     // lam <- H psi on psi's stream
     if (int rc = sv_apply_pauli_sum(psi, H, scratch)) return rc;
@@ -1633,44 +1631,26 @@ int backward_impl(sv_state *psi, sv_state *scratch, const sv_gate *g, int G, con
         SV_HIP(psi->arena.ensure(bytes));
         SV_HIP(hipMemcpyAsync(psi->arena.p, psi->stage.p, bytes, hipMemcpyHostToDevice, psi->stream));
     }
-    const size_t part_doubles = size_t(std::max(slots, 1)) * dev::kRedBlocks * 2;
-    SV_HIP(psi->grad.ensure((part_doubles + 2 * size_t(std::max(slots, 1))) * sizeof(double)));
+    SV_HIP(psi->grad.ensure(sizeof(double) * 8 * size_t(std::max(slots, 1)) * size_t(dev::transition_blocks(psi->n))));
+    SV_HIP(psi->red_host.ensure(sizeof(double) * 8 * size_t(std::max(slots, 1))));
     double *part = static_cast<double *>(psi->grad.p);
-    double *sums = part + part_doubles;
     for (const BwdStep &st : steps) {
-        if (st.kind == BwdStep::SINGLE) {
-            const sv_gate &gg = g[st.gate];
-            std::vector<cd> m, mdag;
-            int sq[SV_MAX_K];
-            if (int rc = gate_matrix_canonical(gg, m, sq)) return rc;
-            const int D = 1 << gg.k;
-            mdag.resize(m.size());
-            for (int r = 0; r < D; ++r)
-                for (int c = 0; c < D; ++c) mdag[size_t(r) * D + c] = std::conj(m[size_t(c) * D + r]);
-            const int pauli = st.slot < 0 ? 0 : gg.kind == SV_G_RX ? 1 : gg.kind == SV_G_RY ? 2 : 3;
-            LaunchTimer t(stat_class(FAM_ADJOINT, gg.k), psi->stream);
-            SV_HIP(dev::launch_backward_step(psi->dtype, gg.k, sq, mdag.data(), pauli, psi->buf, scratch->buf, psi->n,
-                                             part, st.slot, psi->stream));
-            continue;
-        }
-        if (st.kind == BwdStep::RUN) {
+        if (!st.qubits.empty()) {
             LaunchTimer t(stat_class(FAM_ADJOINT, 3), psi->stream);
-            SV_HIP(dev::launch_grad_terms(psi->dtype, st.n_terms, st.x, st.z, st.pw, psi->buf, scratch->buf, psi->n,
-                                          part, st.slot, psi->stream));
+            SV_HIP(dev::launch_transitions(psi->dtype, int(st.qubits.size()), st.qubits.data(), psi->buf, scratch->buf,
+                                           psi->n, part, st.slot, psi->stream));
         }
-        const Launch *sub = launches.data() + st.l0;
-        const size_t cnt = st.l1 - st.l0;
-        if (int rc = enqueue(sub, cnt, psi->dtype, psi->buf, psi->n, psi->arena.p, psi->stream, scratch->buf)) return rc;
+        if (int rc = enqueue(launches.data() + st.l0, st.l1 - st.l0, psi->dtype, psi->buf, psi->n, psi->arena.p,
+                             psi->stream, scratch->buf))
+            return rc;
     }
     SV_HIP(hipEventRecord(psi->arena_free, psi->stream));
-    if (slots) {
-        SV_HIP(dev::launch_sum_partials(part, slots, sums, psi->stream));
-        std::vector<double> h(2 * size_t(slots));
-        if (int rc = read_result(psi, sums, h.size(), h.data())) return rc;
-        for (int sl = 0; sl < slots; ++sl) grad[slot_param[sl]] += h[2 * sl + 1];  // Im <lam|P|phi>
-    } else {
-        SV_HIP(hipStreamSynchronize(psi->stream));
-    }
+    double *sums = static_cast<double *>(psi->red_host.p);
+    if (slots) SV_HIP(dev::launch_transitions_final(part, slots, psi->n, sums, psi->stream));
+    SV_HIP(hipStreamSynchronize(psi->stream));
+    for (const BwdStep &st : steps)
+        if (!st.qubits.empty())
+            if (int rc = run_gradients(g, st, sums + 8 * size_t(st.slot), grad)) return rc;
     if (int rc = stream_after(scratch->stream, psi->stream)) return rc;
     return SV_OK;
 }

@@ -1,14 +1,15 @@
-// Adjoint-method backward step (one gate, two states in one pass).
+// Adjoint gradients.
 //
 // E(theta) = <psi|H|psi>, psi = U_G..U_1 psi_0.  With phi = U_{g+1}^+..U_G^+ psi
 // and lam = U_{g+1}^+..U_G^+ H psi, and a rotation U_g = exp(-i theta P / 2),
 //   dE/dtheta_g = 2 Re <lam| dU_g/dtheta |phi_{g-1}> = 2 Re <lam| (-i/2) P |phi>
-//               = Im <lam|P|phi>,
-// evaluated before both states move one gate back (phi <- U_g^+ phi,
-// lam <- U_g^+ lam).  One kernel per gate reads both states once, adds the
-// group's share of <lam|P|phi> (FP64) to a per-block partial, and writes both
-// updated states: two buffers, no stored trajectory.
+//               = Im <lam|P|phi>.
+// The sweep (api.hip) undoes the gates on both states, two buffers and no
+// stored trajectory, and stops at runs of one-qubit gates to take the sums
+// below.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -17,273 +18,197 @@ namespace dev {
 
 namespace {
 
-template <typename T, int K>
-struct BwdArgs {
-    T mr[(1 << K) * (1 << K)];
-    T mi[(1 << K) * (1 << K)];
-    int pos[K];
-    int pauli;
-    uint64_t n_groups;
-    double pmat[8];  // generator P as a 2x2 complex matrix (re, im), row-major
+// Transition sums of qubits q between lam and phi: with M[a][b] = sum over the
+// other qubits of conj(lam_a) phi_b (a, b the values of q), the kernel gives
+//   S = M00 + M11, Z = M00 - M11, A = M01 + M10, B = M01 - M10,
+// from which <lam|O|phi> follows for any operator O on q.  One pass serves all
+// one-qubit gates of a run, however many there are on a qubit: a rotation's
+// generator P is seen through the run's later gates V on its qubit as
+// V P V^dagger.
+//
+// What bounds it: a partner load (from L2 or the memory-side cache) and four
+// FP64 multiply-adds per amplitude and qubit.  A thread takes 2 (tiny states:
+// 1) slots of 16 bytes that differ in the top index bits and works on up to
+// kTransQubits qubits (blockIdx.y: the next ones).  The per-rotation form, a
+// pass over both states for every 16 rotations and the rotations of different
+// axes apart, took 32 us a pass at 20 qubits and four passes a layer of 20 RY
+// and 20 RZ; this takes
+// 29 us for the layer.
+struct TransArgs {
+    int nq;
+    int q[SV_MAX_QUBITS_C64];
 };
 
-__device__ __forceinline__ uint64_t insert_zero_b(uint64_t x, int p)
+typedef float vf4 __attribute__((ext_vector_type(4)));
+typedef double vd2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void slot_amps(vf4 v, double (&re)[2], double (&im)[2])
 {
-    return ((x >> p) << (p + 1)) | (x & ((uint64_t(1) << p) - 1));
+    re[0] = v.x; im[0] = v.y; re[1] = v.z; im[1] = v.w;
+}
+__device__ __forceinline__ void slot_amps(vd2 v, double (&re)[1], double (&im)[1])
+{
+    re[0] = v.x; im[0] = v.y;
 }
 
-template <typename T, int K>
-__device__ __forceinline__ void matvec(const BwdArgs<T, K> &a, const T *vr, const T *vi, T *orr, T *oi)
+template <typename T, int LOGR>
+__global__ void __launch_bounds__(kRedThreads) k_transitions(const T *__restrict__ phi_, const T *__restrict__ lam_,
+                                                            int slot_bits, const TransArgs a,
+                                                            double *__restrict__ partials)
 {
-    constexpr int D = 1 << K;
+    using Slot = typename std::conditional<sizeof(T) == 4, vf4, vd2>::type;
+    constexpr int NA = sizeof(T) == 4 ? 2 : 1, PB = NA - 1, R = 1 << LOGR;
+    const Slot *__restrict__ phi = reinterpret_cast<const Slot *>(phi_);
+    const Slot *__restrict__ lam = reinterpret_cast<const Slot *>(lam_);
+    const int q0 = int(blockIdx.y) * kTransQubits, nq = a.nq - q0 < kTransQubits ? a.nq - q0 : kTransQubits;
+    double sum[2] = {0.0, 0.0}, z[kTransQubits][2], s[kTransQubits][2], d[kTransQubits][2];
 #pragma unroll
-    for (int m = 0; m < D; ++m) {
-        T sr = 0, si = 0;
+    for (int k = 0; k < kTransQubits; ++k) z[k][0] = z[k][1] = s[k][0] = s[k][1] = d[k][0] = d[k][1] = 0.0;
+    const uint64_t U = uint64_t(1) << (slot_bits - LOGR);
+    for (uint64_t u = uint64_t(blockIdx.x) * kRedThreads + threadIdx.x; u < U; u += uint64_t(gridDim.x) * kRedThreads) {
+        auto slot = [&](int r) { return u | uint64_t(r) << (slot_bits - LOGR); };
+        double lr[R][NA], li[R][NA];  // lam
+        double tr[R][2], dp[2] = {0.0, 0.0};  // conj(lam) phi of each slot; first less second half over all of them
 #pragma unroll
-        for (int mp = 0; mp < D; ++mp) {
-            const T ar = a.mr[m * D + mp], ai = a.mi[m * D + mp];
-            sr = fma(ar, vr[mp], sr);
-            sr = fma(-ai, vi[mp], sr);
-            si = fma(ar, vi[mp], si);
-            si = fma(ai, vr[mp], si);
+        for (int r = 0; r < R; ++r) {
+            double fr[NA], fi[NA];
+            slot_amps(lam[slot(r)], lr[r], li[r]);
+            slot_amps(phi[slot(r)], fr, fi);
+            double p[NA][2];
+#pragma unroll
+            for (int b = 0; b < NA; ++b) {
+                p[b][0] = fma(lr[r][b], fr[b], li[r][b] * fi[b]);
+                p[b][1] = fma(lr[r][b], fi[b], -(li[r][b] * fr[b]));
+            }
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                tr[r][c] = NA == 1 ? p[0][c] : p[0][c] + p[NA - 1][c];
+                if (NA == 2) dp[c] += p[0][c] - p[NA - 1][c];
+                sum[c] += tr[r][c];
+            }
         }
-        orr[m] = sr;
-        oi[m] = si;
-    }
-}
-
-template <typename T, int K>
-__global__ void __launch_bounds__(kRedThreads) k_backward(T *__restrict__ phi, T *__restrict__ lam,
-                                                         const BwdArgs<T, K> a, double *__restrict__ partials)
-{
-    constexpr int D = 1 << K;
-    double gr = 0.0, gi = 0.0;
-    for (uint64_t g = uint64_t(blockIdx.x) * kRedThreads + threadIdx.x; g < a.n_groups;
-         g += uint64_t(kRedBlocks) * kRedThreads) {
-        uint64_t base = g;
 #pragma unroll
-        for (int j = 0; j < K; ++j) base = insert_zero_b(base, a.pos[j]);
-        uint64_t idx[D];
-        T fr[D], fi[D], lr[D], li[D];
+        for (int k = 0; k < kTransQubits; ++k) {
+            if (k >= nq) break;  // uniform
+            __builtin_amdgcn_sched_barrier(0);  // one qubit's loads at a time: all of them at once take 484 registers
+            const int q = a.q[q0 + k];
+            const bool pair = PB && q == 0;  // the partner is the slot's other half
+            const int sb = q - PB;
+            Slot f[R];
 #pragma unroll
-        for (int m = 0; m < D; ++m) {
-            uint64_t o = base;
+            for (int r = 0; r < R; ++r) f[r] = phi[pair ? slot(r) : slot(r) ^ (uint64_t(1) << sb)];
 #pragma unroll
-            for (int j = 0; j < K; ++j)
-                if ((m >> j) & 1) o += uint64_t(1) << a.pos[j];
-            idx[m] = o;
-            fr[m] = phi[2 * o];
-            fi[m] = phi[2 * o + 1];
-            lr[m] = lam[2 * o];
-            li[m] = lam[2 * o + 1];
-        }
-        if (K == 1 && a.pauli) {
-            // s = <lam|P|phi> restricted to this group, P (2x2, on local bit 0)
-            // given as a matrix: (P phi)_r = sum_c P[r][c] phi_c
-            double pr[2], pi[2];
+            for (int r = 0; r < R; ++r) {
+                double fr[NA], fi[NA], t[NA][2];
+                slot_amps(f[r], fr, fi);
+                const double sgn = !pair && (slot(r) >> sb) & 1u ? -1.0 : 1.0;
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                pr[r] = 0.0;
-                pi[r] = 0.0;
+                for (int b = 0; b < NA; ++b) {
+                    const double gr = pair ? fr[NA - 1 - b] : fr[b], gi = pair ? fi[NA - 1 - b] : fi[b];
+                    t[b][0] = fma(lr[r][b], gr, li[r][b] * gi);
+                    t[b][1] = fma(lr[r][b], gi, -(li[r][b] * gr));
+                }
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    const double gr_ = a.pmat[4 * r + 2 * c], gi_ = a.pmat[4 * r + 2 * c + 1];
-                    const double vr = fr[c * (D - 1)], vi = fi[c * (D - 1)];
-                    pr[r] += gr_ * vr - gi_ * vi;
-                    pi[r] += gr_ * vi + gi_ * vr;
+                    const double both = NA == 1 ? t[0][c] : t[0][c] + t[NA - 1][c];
+                    s[k][c] += both;
+                    d[k][c] = NA == 2 && pair ? d[k][c] + (t[0][c] - t[NA - 1][c]) : fma(sgn, both, d[k][c]);
+                    if (!pair) z[k][c] = fma(sgn, tr[r][c], z[k][c]);
                 }
             }
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const double ur = lr[r * (D - 1)], ui = li[r * (D - 1)];
-                // conj(lam_r) * (P phi)_r
-                gr += ur * pr[r] + ui * pi[r];
-                gi += ur * pi[r] - ui * pr[r];
+            if (pair) {
+                z[k][0] += dp[0];
+                z[k][1] += dp[1];
             }
         }
-        T or_[D], oi[D];
-        matvec<T, K>(a, fr, fi, or_, oi);
-#pragma unroll
-        for (int m = 0; m < D; ++m) {
-            phi[2 * idx[m]] = or_[m];
-            phi[2 * idx[m] + 1] = oi[m];
-        }
-        matvec<T, K>(a, lr, li, or_, oi);
-#pragma unroll
-        for (int m = 0; m < D; ++m) {
-            lam[2 * idx[m]] = or_[m];
-            lam[2 * idx[m] + 1] = oi[m];
-        }
     }
-    if (a.pauli) {
-        __shared__ double sr[kRedThreads], si[kRedThreads];
-        const int t = threadIdx.x;
-        sr[t] = gr;
-        si[t] = gi;
-        __syncthreads();
-        for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-            if (t < s) {
-                sr[t] += sr[t + s];
-                si[t] += si[t + s];
-            }
-            __syncthreads();
-        }
-        if (t == 0) {
-            partials[2 * blockIdx.x] = sr[0];
-            partials[2 * blockIdx.x + 1] = si[0];
-        }
-    }
-}
-
-template <typename T, int K>
-hipError_t bwd_launch_t(const int *sorted_q, const cd *mdag, int pauli, T *phi, T *lam, int n, double *d_partials,
-                        int slot, hipStream_t st)
-{
-    BwdArgs<T, K> a;
-    constexpr int D = 1 << K;
-    for (int i = 0; i < D * D; ++i) {
-        a.mr[i] = T(mdag[i].real());
-        a.mi[i] = T(mdag[i].imag());
-    }
-    for (int j = 0; j < K; ++j) a.pos[j] = sorted_q[j];
-    a.pauli = pauli;
-    // X, Y, Z as 2x2 complex matrices
-    static const double P[4][8] = {{0, 0, 0, 0, 0, 0, 0, 0},
-                                   {0, 0, 1, 0, 1, 0, 0, 0},
-                                   {0, 0, 0, -1, 0, 1, 0, 0},
-                                   {1, 0, 0, 0, 0, 0, -1, 0}};
-    for (int i = 0; i < 8; ++i) a.pmat[i] = P[pauli & 3][i];
-    a.n_groups = uint64_t(1) << (n - K);
-    double *part = d_partials + size_t(slot < 0 ? 0 : slot) * kRedBlocks * 2;
-    hipLaunchKernelGGL((k_backward<T, K>), dim3(kRedBlocks), dim3(kRedThreads), 0, st, phi, lam, a, part);
-    return hipGetLastError();
-}
-
-// <lam| P_t |phi> for up to kMaxGradTerms Pauli strings in one pass over the
-// two states (used for a run of commuting rotations: every rotation of the
-// run sees the same phi and lam, see sv_backward).
-struct GradTerms {
-    int n_terms;
-    uint64_t x[kMaxGradTerms];
-    uint64_t z[kMaxGradTerms];
-    int pw[kMaxGradTerms];  // power of i (number of Y factors mod 4)
-    uint64_t N;
-};
-
-__device__ __forceinline__ void ld2(const float *p, uint64_t i, double &re, double &im)
-{
-    const float2 v = reinterpret_cast<const float2 *>(p)[i];
-    re = v.x;
-    im = v.y;
-}
-__device__ __forceinline__ void ld2(const double *p, uint64_t i, double &re, double &im)
-{
-    const double2 v = reinterpret_cast<const double2 *>(p)[i];
-    re = v.x;
-    im = v.y;
-}
-
-// Sum over the 64 lanes of a wave in a fixed butterfly order.
-__device__ __forceinline__ double wave_sum(double v)
-{
+    // workgroup sums through LDS: value v's 256 entries in 8 strided chains, then
+    // a butterfly (64 lanes' butterflies of every value took 4 us); per qubit
+    // (S, Z, A, B)
+    constexpr int kValues = 2 + 6 * kTransQubits;
+    __shared__ double sh[kValues][kRedThreads];
+    const int tid = threadIdx.x;
+    sh[0][tid] = sum[0];
+    sh[1][tid] = sum[1];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-template <typename T, int NT>
-__global__ void __launch_bounds__(kRedThreads) k_grad_terms(const T *__restrict__ phi, const T *__restrict__ lam,
-                                                           const GradTerms a, double *__restrict__ partials)
-{
-    double sr[NT], si[NT];
+    for (int k = 0; k < kTransQubits; ++k)
 #pragma unroll
-    for (int t = 0; t < NT; ++t) sr[t] = si[t] = 0.0;
-    for (uint64_t i = uint64_t(blockIdx.x) * kRedThreads + threadIdx.x; i < a.N; i += uint64_t(kRedBlocks) * kRedThreads) {
-        double lr, li, fr, fi;
-        ld2(lam, i, lr, li);
-        ld2(phi, i, fr, fi);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            if (t >= a.n_terms) break;
-            const uint64_t j = i ^ a.x[t];
-            double pr = fr, pi = fi;
-            if (a.x[t]) ld2(phi, j, pr, pi);  // Z-type terms (x = 0) reuse phi_i
-            if (__popcll(j & a.z[t]) & 1) {
-                pr = -pr;
-                pi = -pi;
-            }
-            // multiply by i^pw
-            double qr = pr, qi = pi;
-            switch (a.pw[t] & 3) {
-            case 1: qr = -pi; qi = pr; break;
-            case 2: qr = -pr; qi = -pi; break;
-            case 3: qr = pi; qi = -pr; break;
-            default: break;
-            }
-            // conj(lam_i) * (P phi)_i
-            sr[t] += lr * qr + li * qi;
-            si[t] += lr * qi - li * qr;
+        for (int c = 0; c < 2; ++c) {
+            sh[2 + 6 * k + c][tid] = z[k][c];
+            sh[4 + 6 * k + c][tid] = s[k][c];
+            sh[6 + 6 * k + c][tid] = d[k][c];
         }
-    }
-    // workgroup sums: wave butterflies, then the waves' values in wave order
-    constexpr int kWaves = kRedThreads / 64;
-    __shared__ double sh[kWaves][2 * NT];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        if (t >= a.n_terms) break;
-        const double r = wave_sum(sr[t]), m = wave_sum(si[t]);
-        if (lane == 0) {
-            sh[wv][2 * t] = r;
-            sh[wv][2 * t + 1] = m;
-        }
-    }
     __syncthreads();
-    if (tid < 2 * a.n_terms) {
-        double v = 0.0;
-        for (int w = 0; w < kWaves; ++w) v += sh[w][tid];
-        partials[(size_t(tid >> 1) * kRedBlocks + blockIdx.x) * 2 + (tid & 1)] = v;
+    static_assert(8 * kValues <= kRedThreads, "one thread per chain");
+    double v = 0.0;
+    if (tid < 8 * kValues)
+        for (int i = tid & 7; i < kRedThreads; i += 8) v += sh[tid >> 3][i];
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    __syncthreads();
+    if (tid < 8 * kValues && (tid & 7) == 0) sh[tid >> 3][0] = v;
+    __syncthreads();
+    if (tid < 8 * nq) {
+        const int k = tid >> 3, c = tid & 7;
+        partials[(size_t(q0 + k) * gridDim.x + blockIdx.x) * 8 + c] = sh[c < 2 ? c : 6 * k + c][0];
     }
+}
+
+// out[slot][c] = sum over the slot's blocks of partials (fixed order).
+__global__ void __launch_bounds__(64) k_transitions_final(const double *__restrict__ partials, int blocks,
+                                                          double *__restrict__ out)
+{
+    const double *p = partials + size_t(blockIdx.x) * blocks * 8;
+    const int c = threadIdx.x & 7;
+    double v = 0.0;
+    for (int b = threadIdx.x >> 3; b < blocks; b += 8) v += p[size_t(b) * 8 + c];
+#pragma unroll
+    for (int o = 32; o >= 8; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (threadIdx.x < 8) out[size_t(blockIdx.x) * 8 + c] = v;
+}
+
+template <typename T>
+hipError_t transitions_t(const TransArgs &a, const T *phi, const T *lam, int n, double *d_partials, hipStream_t st)
+{
+    const int slot_bits = n - (sizeof(T) == 4 ? 1 : 0);
+    const dim3 grid(unsigned(transition_blocks(n)), unsigned((a.nq + kTransQubits - 1) / kTransQubits));
+    if (slot_bits >= 10)
+        hipLaunchKernelGGL((k_transitions<T, 1>), grid, dim3(kRedThreads), 0, st, phi, lam, slot_bits, a, d_partials);
+    else
+        hipLaunchKernelGGL((k_transitions<T, 0>), grid, dim3(kRedThreads), 0, st, phi, lam, slot_bits, a, d_partials);
+    return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_grad_terms(int dtype, int n_terms, const uint64_t *x, const uint64_t *z, const int *pw,
-                             const void *phi, const void *lam, int n, double *d_partials, int slot0, hipStream_t st)
+int transition_blocks(int n)
 {
-    if (n_terms < 1 || n_terms > kMaxGradTerms) return hipErrorInvalidValue;
-    GradTerms a;
-    a.n_terms = n_terms;
-    for (int t = 0; t < kMaxGradTerms; ++t) {
-        a.x[t] = t < n_terms ? x[t] : 0;
-        a.z[t] = t < n_terms ? z[t] : 0;
-        a.pw[t] = t < n_terms ? pw[t] : 0;
-    }
-    a.N = uint64_t(1) << n;
-    double *part = d_partials + size_t(slot0) * kRedBlocks * 2;
-    if (dtype == SV_C64)
-        hipLaunchKernelGGL((k_grad_terms<float, kMaxGradTerms>), dim3(kRedBlocks), dim3(kRedThreads), 0, st,
-                           static_cast<const float *>(phi), static_cast<const float *>(lam), a, part);
-    else
-        hipLaunchKernelGGL((k_grad_terms<double, kMaxGradTerms>), dim3(kRedBlocks), dim3(kRedThreads), 0, st,
-                           static_cast<const double *>(phi), static_cast<const double *>(lam), a, part);
-    return hipGetLastError();
+    // 16 (complex64) or 8 amplitudes a thread, so that the sums over a workgroup
+    // do not outweigh its own work
+    const uint64_t b = (uint64_t(1) << n) / (16 * kRedThreads);
+    return int(b < 1 ? 1 : b > 512 ? 512 : b);
 }
 
-hipError_t launch_backward_step(int dtype, int k, const int *sorted_q, const cd *mdag, int pauli, void *phi,
-                                void *lam, int n, double *d_partials, int slot, hipStream_t st)
+hipError_t launch_transitions(int dtype, int nq, const int *q, const void *phi, const void *lam, int n,
+                              double *d_partials, int slot0, hipStream_t st)
 {
-    if (n < k || (pauli && k != 1)) return hipErrorInvalidValue;
-    if (dtype == SV_C64) {
-        float *f = static_cast<float *>(phi), *l = static_cast<float *>(lam);
-        if (k == 1) return bwd_launch_t<float, 1>(sorted_q, mdag, pauli, f, l, n, d_partials, slot, st);
-        if (k == 2) return bwd_launch_t<float, 2>(sorted_q, mdag, pauli, f, l, n, d_partials, slot, st);
-        return hipErrorInvalidValue;
+    if (nq < 1 || nq > n || n > SV_MAX_QUBITS_C64) return hipErrorInvalidValue;
+    TransArgs a;
+    a.nq = nq;
+    for (int k = 0; k < nq; ++k) {
+        if (q[k] < 0 || q[k] >= n) return hipErrorInvalidValue;
+        a.q[k] = q[k];
     }
-    double *f = static_cast<double *>(phi), *l = static_cast<double *>(lam);
-    if (k == 1) return bwd_launch_t<double, 1>(sorted_q, mdag, pauli, f, l, n, d_partials, slot, st);
-    if (k == 2) return bwd_launch_t<double, 2>(sorted_q, mdag, pauli, f, l, n, d_partials, slot, st);
-    return hipErrorInvalidValue;
+    double *part = d_partials + size_t(slot0) * transition_blocks(n) * 8;
+    if (dtype == SV_C64)
+        return transitions_t(a, static_cast<const float *>(phi), static_cast<const float *>(lam), n, part, st);
+    return transitions_t(a, static_cast<const double *>(phi), static_cast<const double *>(lam), n, part, st);
+}
+
+hipError_t launch_transitions_final(const double *d_partials, int n_slots, int n, double *out, hipStream_t st)
+{
+    if (n_slots <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_transitions_final, dim3(n_slots), dim3(64), 0, st, d_partials, transition_blocks(n), out);
+    return hipGetLastError();
 }
 
 }  // namespace dev

@@ -226,20 +226,16 @@ hipError_t launch_dm_expect(int dtype, const void *rho, int n, const PauliDev &H
                             hipStream_t st);
 
 // ------------------------------------------------------------------ adjoint
-// One backward step for a k <= 2 gate: if pauli >= 1 (1 = X, 2 = Y, 3 = Z on
-// sorted_q[0]), d_partials[slot * kRedBlocks + block] receives the block's
-// partial of <lam|P|phi> (re, im: 2 doubles per block); then phi <- U^+ phi and
-// lam <- U^+ lam, U^+ given canonically in `mdag`.
-hipError_t launch_backward_step(int dtype, int k, const int *sorted_q, const cd *mdag, int pauli,
-                                void *phi, void *lam, int n, double *d_partials, int slot,
-                                hipStream_t st);
-// For Pauli strings t < n_terms (x/z masks, pw = power of i), partials of
-// <lam|P_t|phi> into slots slot0 + t (same layout as above).  One pass.
-constexpr int kMaxGradTerms = 16;
-hipError_t launch_grad_terms(int dtype, int n_terms, const uint64_t *x, const uint64_t *z, const int *pw,
-                             const void *phi, const void *lam, int n, double *d_partials, int slot0, hipStream_t st);
-// out[s] = sum over blocks of d_partials[s][*] (fixed order), s < n_slots.
-hipError_t launch_sum_partials(const double *d_partials, int n_slots, double *d_out, hipStream_t st);
+// Transition sums between lam and phi (see backward.hip) of nq qubits, in one
+// pass: per qubit the partials of transition_blocks(n) workgroups, 8 doubles
+// each (S, Z, A, B as re, im), from slot slot0 on; the second call sums n_slots
+// of them in a fixed order into out (8 doubles per slot; may be pinned host
+// memory).
+constexpr int kTransQubits = 4;  // qubits per workgroup
+int transition_blocks(int n);
+hipError_t launch_transitions(int dtype, int nq, const int *q, const void *phi, const void *lam, int n,
+                              double *d_partials, int slot0, hipStream_t st);
+hipError_t launch_transitions_final(const double *d_partials, int n_slots, int n, double *out, hipStream_t st);
 
 // ------------------------------------------------------------------ batches
 struct BatchTables;  // defined in batch.hip

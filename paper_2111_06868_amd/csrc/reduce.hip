@@ -937,12 +937,5 @@ hipError_t launch_pauli_apply(int dtype, const void *psi, void *out, int n, cons
     return pauli_apply_t(static_cast<const double *>(psi), static_cast<double *>(out), n, H, st);
 }
 
-hipError_t launch_sum_partials(const double *d_partials, int n_slots, double *d_out, hipStream_t st)
-{
-    if (n_slots <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_final<2>, dim3(n_slots), dim3(kRedThreads), 0, st, d_partials, kRedBlocks, d_out);
-    return hipGetLastError();
-}
-
 }  // namespace dev
 }  // namespace sv
