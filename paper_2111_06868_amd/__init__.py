@@ -404,10 +404,7 @@ class State:
         returns the chosen operator indices."""
         ga = gates if isinstance(gates, GateArray) else GateArray(gates)
         ops = list(ops)
-        arr = (N.sv_super_op * max(len(ops), 1))()
-        keep = []
-        for j, op in enumerate(ops):
-            op.fill(arr[j], keep)
+        arr = _super_op_array(ops)
         u = np.ascontiguousarray(uniforms, dtype=np.float64)
         if u.size != len(ops):
             raise ValueError("one uniform per operator")
@@ -481,6 +478,46 @@ class SuperOp:
         out = np.zeros(2 * D2 * D2, dtype=np.float64)
         N.check(N.lib().sv_super_op_matrix(ctypes.byref(c), out.ctypes.data_as(ctypes.POINTER(ctypes.c_double))))
         return out.view(np.complex128).reshape(D2, D2)
+
+
+_SUPER_OP_WORDS = np.dtype([("i", np.uint32, 8), ("p", np.uint64, 4)])  # sv_super_op, pointers as integers
+
+
+def _super_op_array(ops) -> ctypes.Array:
+    """sv_super_op[len(ops)] of SuperOps (as SuperOp.fill, all at once).  The
+    entries point into the SuperOps' arrays, which the array keeps alive."""
+    arr = (N.sv_super_op * max(len(ops), 1))()
+    plain = lambda a: a is None or (a.dtype.char == "D" and a.flags.c_contiguous)
+    if not all(type(op) is SuperOp and plain(op.left) and (op.right is op.left or plain(op.right)) and plain(op.s)
+               and plain(op.superop) for op in ops):
+        arr.keep = []
+        for j, op in enumerate(ops):
+            op.fill(arr[j], arr.keep)
+        return arr
+    ints, ptrs, held = [], [], []
+    at = lambda a: a.ctypes.data
+    for op in ops:
+        q = op.qubits
+        k = len(q)
+        if not 1 <= k <= 3:
+            raise ValueError("super operator on %d qubits (1..3)" % k)
+        q0, q1, q2 = (q + (0, 0))[:3]
+        left, right, s, superop = op.left, op.right, op.s, op.superop
+        held.append((left, right, s, superop))
+        if superop is not None:
+            ints.append((op.after & 0xFFFFFFFF, k, q0 & 0xFFFFFFFF, q1 & 0xFFFFFFFF, q2 & 0xFFFFFFFF, 0, 0, 0))
+            ptrs.append((0, 0, 0, at(superop)))
+        else:
+            ints.append((op.after & 0xFFFFFFFF, k, q0 & 0xFFFFFFFF, q1 & 0xFFFFFFFF, q2 & 0xFFFFFFFF, len(left),
+                         len(right), 0))
+            p = at(left)
+            ptrs.append((p, p if right is left else at(right), 0 if s is None else at(s), 0))
+    if ops:
+        words = np.frombuffer(arr, dtype=_SUPER_OP_WORDS)
+        words["i"] = ints
+        words["p"] = ptrs
+    arr.keep = held
+    return arr
 
 
 def _super_from_c(c: "N.sv_super_op", mats: np.ndarray, s=None) -> SuperOp:
@@ -598,10 +635,7 @@ class DensityMatrix:
         """Evolve by the gates with the super operators among them (sv_dm_run)."""
         ga = gates if isinstance(gates, GateArray) else GateArray(gates)
         ops = list(ops)
-        arr = (N.sv_super_op * max(len(ops), 1))()
-        keep = []
-        for j, op in enumerate(ops):
-            op.fill(arr[j], keep)
+        arr = _super_op_array(ops)
         o = N.sv_run_opts()
         o.max_k = int(max_k)
         o.precision = (PREC_FP32 if self.dtype == C64 else PREC_FP64) if precision is None else int(precision)

@@ -1381,7 +1381,7 @@ struct BwdStep {
     int lo = 0, hi = -1;      // the run of one-qubit gates lo..hi (hi: a parameterised one), or empty
     std::vector<int> qubits;  // its qubits with parameterised gates
     int slot = -1;            // the first one's slot
-    size_t l0 = 0, l1 = 0;    // launches [l0, l1) that undo gates
+    int first = 0, last = 0;  // the gates it undoes, first down to last
 };
 
 // dE/dtheta of the run's parameterised gates from its qubits' sums v (8 doubles
@@ -1423,26 +1423,29 @@ int dagger_launches(const sv_gate *g, int hi, int lo, const sv_state *s, int pre
 {
     const int cnt = hi - lo + 1;
     std::vector<sv_gate> dg(cnt);
-    std::vector<std::vector<double>> store(cnt);
+    size_t entries = 0;
+    for (int t = lo; t <= hi; ++t) entries += size_t(1) << (2 * g[t].k);
+    std::vector<cd> store(entries);
+    cd *m = store.data();
     int kmax = 1;
     for (int t = 0; t < cnt; ++t) {
         const sv_gate &src = g[hi - t];
-        std::vector<cd> m;
-        if (int rc = gate_matrix_abi(src, m)) return rc;
         const int D = 1 << src.k;
-        store[t].resize(2 * size_t(D) * D);
-        for (int r = 0; r < D; ++r)
-            for (int c = 0; c < D; ++c) {
-                const cd v = std::conj(m[size_t(c) * D + r]);
-                store[t][2 * (size_t(r) * D + c)] = v.real();
-                store[t][2 * (size_t(r) * D + c) + 1] = v.imag();
+        fill_gate_matrix(src, m);
+        for (int r = 0; r < D; ++r) {
+            for (int c = 0; c < r; ++c) {
+                const cd v = m[r * D + c];
+                m[r * D + c] = std::conj(m[c * D + r]);
+                m[c * D + r] = std::conj(v);
             }
-        sv_gate d = src;
-        d.kind = SV_G_MATRIX;
-        d.param = -1;
-        d.m = store[t].data();
-        dg[t] = d;
+            m[r * D + r] = std::conj(m[r * D + r]);
+        }
+        dg[t] = src;
+        dg[t].kind = SV_G_MATRIX;
+        dg[t].param = -1;
+        dg[t].m = reinterpret_cast<const double *>(m);
         kmax = std::max(kmax, src.k);
+        m += D * D;
     }
     std::vector<Block> blocks;
     const CostTable cost = lookup_costs(s->n, prec, nullptr);
@@ -1510,12 +1513,12 @@ int dagger_launches(const sv_gate *g, int hi, int lo, const sv_state *s, int pre
     }
     const int kbest = choice;
     if (int rc = fuse_gates(dg.data(), cnt, s->n, kbest, SV_RULE_ENHANCED, cost, blocks)) return rc;
-    for (const auto &b : blocks) {
+    for (auto &b : blocks) {
         Launch L;
         L.k = b.k;
         std::copy(b.q, b.q + SV_MAX_K, L.q);
         L.path = choose_path(s->dtype, prec, b.k, b.q, s->n);
-        L.m = b.m;
+        L.m = std::move(b.m);
         out.push_back(std::move(L));
     }
     return SV_OK;
@@ -1567,12 +1570,6 @@ int backward_impl(sv_state *psi, sv_state *scratch, const sv_gate *g, int G, con
     // one shares one pass of transition sums; it is undone together with the
     // gates before it, down to the next parameterised one
     std::vector<BwdStep> steps;
-    std::vector<Launch> launches;
-    struct RunJob {
-        int hi, lo;
-        size_t step;
-    };
-    std::vector<RunJob> jobs;  // gates hi..lo, undone at steps[step]
     int slots = 0;
     for (int i = G - 1; i >= 0;) {
         BwdStep st;
@@ -1590,61 +1587,69 @@ int backward_impl(sv_state *psi, sv_state *scratch, const sv_gate *g, int G, con
             stop = j;
         }
         while (stop >= 0 && g[stop].param < 0) --stop;
-        jobs.push_back({i, stop + 1, steps.size()});
+        st.first = i;
+        st.last = stop + 1;
         steps.push_back(std::move(st));
         i = stop;
-    }
-    // the dagger blocks of the runs are independent host work: spread over
-    // threads, then appended in sweep order
-    {
-        std::vector<std::vector<Launch>> outs(jobs.size());
-        std::vector<int> rcs(jobs.size(), SV_OK);
-        std::vector<std::string> msgs(jobs.size());
-        std::atomic<size_t> next(0);
-        auto worker = [&]() {
-            for (size_t t; (t = next.fetch_add(1)) < jobs.size();) {
-                rcs[t] = dagger_launches(g, jobs[t].hi, jobs[t].lo, psi, prec, outs[t]);
-                if (rcs[t]) msgs[t] = last_error_cstr();
-            }
-        };
-        const unsigned hw = std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
-        const unsigned nt = jobs.size() >= 16 ? std::min<unsigned>(hw, unsigned(jobs.size() / 4)) : 1u;
-        std::vector<std::thread> pool;
-        for (unsigned t = 1; t < nt; ++t) pool.emplace_back(worker);
-        worker();
-        for (auto &th : pool) th.join();
-        for (size_t t = 0; t < jobs.size(); ++t) {
-            if (rcs[t]) return fail(rcs[t], "%s", msgs[t].c_str());
-            BwdStep &st = steps[jobs[t].step];
-            st.l0 = launches.size();
-            for (auto &L : outs[t]) launches.push_back(std::move(L));
-            st.l1 = launches.size();
-        }
     }
     if (int rc = select_device(psi)) return rc;
     // lam <- H psi on psi's stream
     if (int rc = sv_apply_pauli_sum(psi, H, scratch)) return rc;
-    SV_HIP(hipEventSynchronize(psi->arena_free));
-    const size_t bytes = pack_operands(launches, psi->dtype, psi->stage);
-    if (bytes == size_t(-1)) return fail(SV_ERR_HIP, "pinned staging allocation failed");
-    if (bytes) {
-        SV_HIP(psi->arena.ensure(bytes));
-        SV_HIP(hipMemcpyAsync(psi->arena.p, psi->stage.p, bytes, hipMemcpyHostToDevice, psi->stream));
-    }
     SV_HIP(psi->grad.ensure(sizeof(double) * 8 * size_t(std::max(slots, 1)) * size_t(dev::transition_blocks(psi->n))));
     SV_HIP(psi->red_host.ensure(sizeof(double) * 8 * size_t(std::max(slots, 1))));
     double *part = static_cast<double *>(psi->grad.p);
-    for (const BwdStep &st : steps) {
-        if (!st.qubits.empty()) {
-            LaunchTimer t(stat_class(FAM_ADJOINT, 3), psi->stream);
-            SV_HIP(dev::launch_transitions(psi->dtype, int(st.qubits.size()), st.qubits.data(), psi->buf, scratch->buf,
-                                           psi->n, part, st.slot, psi->stream));
+    // The first steps are planned and launched before the others are planned,
+    // so that the GPU sweeps while the host forms matrices.  Their operands
+    // lie in the scratch state's arena: psi's holds H's tables until then.
+    for (size_t from = 0; from < steps.size();) {
+        const size_t to = from ? steps.size() : (steps.size() + 3) / 4;
+        sv_state *const at = from ? psi : scratch;
+        // the dagger blocks of the steps are independent host work: spread over
+        // threads where there are many
+        std::vector<std::vector<Launch>> outs(to - from);
+        std::vector<int> rcs(outs.size(), SV_OK);
+        std::vector<std::string> msgs(outs.size());
+        std::atomic<size_t> next(0);
+        auto worker = [&]() {
+            for (size_t t; (t = next.fetch_add(1)) < outs.size();) {
+                rcs[t] = dagger_launches(g, steps[from + t].first, steps[from + t].last, psi, prec, outs[t]);
+                if (rcs[t]) msgs[t] = last_error_cstr();
+            }
+        };
+        const unsigned hw = std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
+        const unsigned nt = outs.size() >= 16 ? std::min<unsigned>(hw, unsigned(outs.size() / 4)) : 1u;
+        std::vector<std::thread> pool;
+        for (unsigned t = 1; t < nt; ++t) pool.emplace_back(worker);
+        worker();
+        for (auto &th : pool) th.join();
+        std::vector<Launch> launches;
+        std::vector<size_t> end;
+        for (size_t t = 0; t < outs.size(); ++t) {
+            if (rcs[t]) return fail(rcs[t], "%s", msgs[t].c_str());
+            for (auto &L : outs[t]) launches.push_back(std::move(L));
+            end.push_back(launches.size());
         }
-        if (int rc = enqueue(launches.data() + st.l0, st.l1 - st.l0, psi->dtype, psi->buf, psi->n, psi->arena.p,
-                             psi->stream, scratch->buf))
-            return rc;
+        SV_HIP(hipEventSynchronize(at->arena_free));
+        const size_t bytes = pack_operands(launches, psi->dtype, at->stage);
+        if (bytes == size_t(-1)) return fail(SV_ERR_HIP, "pinned staging allocation failed");
+        if (bytes) {
+            SV_HIP(at->arena.ensure(bytes));
+            SV_HIP(hipMemcpyAsync(at->arena.p, at->stage.p, bytes, hipMemcpyHostToDevice, psi->stream));
+        }
+        for (size_t t = 0, l = 0; t < outs.size(); l = end[t++]) {
+            const BwdStep &st = steps[from + t];
+            if (!st.qubits.empty()) {
+                LaunchTimer timer(stat_class(FAM_ADJOINT, 3), psi->stream);
+                SV_HIP(dev::launch_transitions(psi->dtype, int(st.qubits.size()), st.qubits.data(), psi->buf,
+                                               scratch->buf, psi->n, part, st.slot, psi->stream));
+            }
+            if (int rc = enqueue(launches.data() + l, end[t] - l, psi->dtype, psi->buf, psi->n, at->arena.p,
+                                 psi->stream, scratch->buf))
+                return rc;
+        }
+        SV_HIP(hipEventRecord(at->arena_free, psi->stream));
+        from = to;
     }
-    SV_HIP(hipEventRecord(psi->arena_free, psi->stream));
     double *sums = static_cast<double *>(psi->red_host.p);
     if (slots) SV_HIP(dev::launch_transitions_final(part, slots, psi->n, sums, psi->stream));
     SV_HIP(hipStreamSynchronize(psi->stream));

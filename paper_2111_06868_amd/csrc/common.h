@@ -26,9 +26,20 @@ int check_gate_shape(const sv_gate &g);
 int check_gate_qubits(const sv_gate &g, int n);
 // 2^k x 2^k matrix in the ABI order (q[0] = most significant local bit).
 int gate_matrix_abi(const sv_gate &g, std::vector<cd> &out);
+// The same of a gate that check_gate_shape accepts, into 4^k entries at out.
+void fill_gate_matrix(const sv_gate &g, cd *out);
+// Whether no entry is an infinity or a NaN.
+bool all_finite(const double *p, size_t count);
+// a b in plain real arithmetic (std::complex multiplication carries inf/nan recovery).
+inline cd mul(cd a, cd b)
+{
+    return cd(a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real());
+}
 // Gate matrix and positions in CANONICAL order: positions sorted ascending,
 // local bit j <-> j-th lowest position.
 int gate_matrix_canonical(const sv_gate &g, std::vector<cd> &m, int *sorted_q);
+// The same of a checked gate, into 4^k entries at m.
+void gate_matrix_canonical(const sv_gate &g, cd *m, int *sorted_q);
 // Split FP16 needs norm-preserving blocks: U^dagger U = I to 1e-6 per entry
 // (check_unitary), for every MATRIX gate of a list (check_fp16_gates).
 int check_unitary(const std::vector<cd> &U, int k, const char *what);

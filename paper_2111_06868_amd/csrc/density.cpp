@@ -27,15 +27,10 @@ int check_super_op(const sv_super_op &op)
     if (op.reserved != 0) return fail(SV_ERR_ARG, "sv_super_op.reserved must be 0");
     if (op.k < 1 || op.k > 3) return fail(SV_ERR_ARG, "super operator on %d qubits (1..3)", op.k);
     const size_t D = size_t(1) << op.k;
-    auto finite = [](const double *p, size_t count) {
-        for (size_t i = 0; i < count; ++i)
-            if (!std::isfinite(p[i])) return false;
-        return true;
-    };
     if (op.superop) {
         if (op.n_left || op.n_right || op.left || op.right || op.s)
             return fail(SV_ERR_ARG, "a matrix super operator takes no left/right/s operands");
-        if (!finite(op.superop, 2 * D * D * D * D)) return fail(SV_ERR_ARG, "non-finite super operator entry");
+        if (!all_finite(op.superop, 2 * D * D * D * D)) return fail(SV_ERR_ARG, "non-finite super operator entry");
         return SV_OK;
     }
     if (op.n_left < 1 || op.n_right < 1 || op.n_left > 64 || op.n_right > 64)
@@ -44,9 +39,10 @@ int check_super_op(const sv_super_op &op)
     if (!op.left || !op.right) return fail(SV_ERR_ARG, "NULL left or right operators");
     if (!op.s && op.n_left != op.n_right)
         return fail(SV_ERR_ARG, "s = NULL (identity) needs n_left == n_right, got %d and %d", op.n_left, op.n_right);
-    if (!finite(op.left, 2 * D * D * op.n_left) || !finite(op.right, 2 * D * D * op.n_right))
+    if (!all_finite(op.left, 2 * D * D * op.n_left) ||
+        (!(op.right == op.left && op.n_right <= op.n_left) && !all_finite(op.right, 2 * D * D * op.n_right)))
         return fail(SV_ERR_ARG, "non-finite operator entry");
-    if (op.s && !finite(op.s, 2 * size_t(op.n_left) * op.n_right)) return fail(SV_ERR_ARG, "non-finite s entry");
+    if (op.s && !all_finite(op.s, 2 * size_t(op.n_left) * op.n_right)) return fail(SV_ERR_ARG, "non-finite s entry");
     return SV_OK;
 }
 
@@ -68,19 +64,21 @@ void super_matrix(const sv_super_op &op, std::vector<cd> &S)
         return cd(p[0], p[1]);
     };
     for (int i = 0; i < op.n_left; ++i)
-        for (int j = 0; j < op.n_right; ++j) {
+        for (int j = op.s ? 0 : i; j < (op.s ? op.n_right : i + 1); ++j) {
             cd s = op.s ? cd(op.s[2 * (size_t(i) * op.n_right + j)], op.s[2 * (size_t(i) * op.n_right + j) + 1])
-                        : cd(i == j ? 1.0 : 0.0);
+                        : cd(1.0);
             if (s == cd(0)) continue;
             // S[(r, c)][(r', c')] += s L_i[r][r'] conj(R_j[c][c'])
             for (size_t r = 0; r < D; ++r)
-                for (size_t c = 0; c < D; ++c)
-                    for (size_t r2 = 0; r2 < D; ++r2) {
-                        const cd lr = s * L(i, r, r2);
-                        if (lr == cd(0)) continue;
-                        cd *row = &S[(r * D + c) * DD + r2 * D];
-                        for (size_t c2 = 0; c2 < D; ++c2) row[c2] += lr * std::conj(R(j, c, c2));
-                    }
+                for (size_t r2 = 0; r2 < D; ++r2) {
+                    const cd lr = mul(s, L(i, r, r2));
+                    if (lr == cd(0)) continue;
+                    for (size_t c = 0; c < D; ++c)
+                        for (size_t c2 = 0; c2 < D; ++c2) {
+                            const cd x = R(j, c, c2);
+                            if (x != cd(0)) S[(r * D + c) * DD + r2 * D + c2] += mul(lr, std::conj(x));
+                        }
+                }
         }
 }
 
@@ -130,9 +128,9 @@ int dm_expand(const sv_gate *g, int G, int n, const sv_super_op *ops, int n_ops,
             out.push_back(h);
         }
     };
+    std::vector<cd> U;
     for (int i = 0; i < G; ++i) {
         emit_ops_until(i);
-        std::vector<cd> U;
         if (int rc = gate_matrix_abi(g[i], U)) return rc;
         if (int rc = check_gate_qubits(g[i], n)) return rc;
         sv_gate row = g[i];  // U on the row positions

@@ -75,7 +75,11 @@ bool tile_union_fits(uint64_t U, int n, int tile_bits, int limit)
     // lowest positions 0 .. tile_bits - u - 1 are then all in the tile
     const int u = __builtin_popcountll(U);
     if (u <= limit) return true;
-    return n >= tile_bits && u <= tile_bits && tile_run_bits(U, tile_bits) >= tile_bits - limit;
+    if (n < tile_bits || u > tile_bits) return false;
+    // the tile_bits - u fillers must close every gap of U among the lowest
+    // tile_bits - limit positions (tile_run_bits(U, tile_bits) >= tile_bits - limit)
+    const int run = tile_bits - limit;
+    return run <= 0 || __builtin_popcountll(~U & ((uint64_t(1) << run) - 1)) <= tile_bits - u;
 }
 
 static std::mutex g_cost_mu;
@@ -139,17 +143,25 @@ uint64_t gate_mask(const sv_gate &g)
 // the order they are applied.  `fits` must accept every gate's own positions.
 class Frontier {
   public:
-    Frontier(const sv_gate *g, const std::vector<int> &idx) : idx_(idx), mask_(idx.size()), queue_(64), head_(64, 0)
+    Frontier(const sv_gate *g, const std::vector<int> &idx) : idx_(idx), mask_(idx.size()), need_(idx.size())
     {
         const int G = int(idx.size());
+        int32_t count[65] = {0};
         for (int t = 0; t < G; ++t) {
             mask_[t] = gate_mask(g[idx[t]]);
             used_ |= mask_[t];
+            for (uint64_t m = mask_[t]; m; m &= m - 1) ++count[__builtin_ctzll(m)];
         }
-        for (uint64_t m = used_; m; m &= m - 1) queue_[__builtin_ctzll(m)].reserve(G);
+        int32_t total = 0;
+        for (int p = 0; p < 64; ++p) {
+            head_[p] = end_[p] = total;
+            total += count[p];
+        }
+        queue_.resize(size_t(total));
         for (int t = 0; t < G; ++t)
-            for (uint64_t m = mask_[t]; m; m &= m - 1) queue_[__builtin_ctzll(m)].push_back(t);
+            for (uint64_t m = mask_[t]; m; m &= m - 1) queue_[size_t(end_[__builtin_ctzll(m)]++)] = t;
         left_ = G;
+        find_ready();
     }
     // The next group (gate indices of the caller's list), or false when none is left.
     template <class Fits>
@@ -163,23 +175,22 @@ class Frontier {
                 again = false;
                 for (uint64_t m = U; m; m &= m - 1) {
                     const int p = __builtin_ctzll(m);
-                    for (int t; (t = at_head(p)) >= 0 && !(mask_[t] & ~U) && ready(t);) {
+                    while ((ready_ >> p) & 1) {
+                        const int t = queue_[size_t(head_[p])];
+                        if (mask_[t] & ~U) break;
                         grp.push_back(idx_[t]);
-                        --left_;
-                        for (uint64_t mm = mask_[t]; mm; mm &= mm - 1) ++head_[__builtin_ctzll(mm)];
+                        take(t);
                         again = true;
                     }
                 }
             }
             int best = -1, best_add = 65;
-            for (uint64_t pm = used_; pm; pm &= pm - 1) {
-                const int t = at_head(__builtin_ctzll(pm));
-                if (t < 0 || !ready(t) || !fits(U | mask_[t])) continue;
+            for (uint64_t pm = ready_; pm; pm &= pm - 1) {
+                const int t = queue_[size_t(head_[__builtin_ctzll(pm)])];
                 const int add = popc(mask_[t] & ~U);
-                if (add < best_add || (add == best_add && t < best)) {
-                    best_add = add;
-                    best = t;
-                }
+                if (add > best_add || (add == best_add && t >= best) || !fits(U | mask_[t])) continue;
+                best_add = add;
+                best = t;
             }
             if (best < 0) break;
             U |= mask_[best];
@@ -190,33 +201,56 @@ class Frontier {
     // last ones taken there.
     void give_back(const std::vector<int> &gates)
     {
-        if (slot_.empty() && !gates.empty()) {  // formed on first use
+        if (gates.empty()) return;
+        if (slot_.empty()) {  // formed on first use
             int top = 0;
             for (int gi : idx_) top = std::max(top, gi);
             slot_.assign(size_t(top) + 1, -1);
             for (size_t t = 0; t < idx_.size(); ++t) slot_[size_t(idx_[t])] = int(t);
         }
         for (int gi : gates) {
-            const int t = slot_.at(size_t(gi));
-            for (uint64_t m = mask_[t]; m; m &= m - 1) --head_[__builtin_ctzll(m)];
+            for (uint64_t m = mask_[size_t(slot_.at(size_t(gi)))]; m; m &= m - 1) --head_[__builtin_ctzll(m)];
             ++left_;
         }
+        find_ready();
     }
 
   private:
-    int at_head(int p) const { return head_[p] < queue_[p].size() ? queue_[p][head_[p]] : -1; }
-    bool ready(int t) const
+    // need_[t]: qubits on which gate t is not the first unapplied one (kept for
+    // gates that are first on one of theirs or were); ready_: the qubits whose
+    // first unapplied gate is first on all of its qubits.
+    void find_ready()
     {
-        for (uint64_t m = mask_[t]; m; m &= m - 1)
-            if (at_head(__builtin_ctzll(m)) != t) return false;
-        return true;
+        for (uint64_t m = used_; m; m &= m - 1) {
+            const int p = __builtin_ctzll(m);
+            for (int32_t i = head_[p]; i < end_[p]; ++i) need_[size_t(queue_[size_t(i)])] = popc(mask_[size_t(queue_[size_t(i)])]);
+        }
+        ready_ = 0;
+        for (uint64_t m = used_; m; m &= m - 1) arrive(__builtin_ctzll(m));
+    }
+    void arrive(int p)  // the gate at p's head becomes first on p
+    {
+        if (head_[p] >= end_[p]) return;
+        const size_t t = size_t(queue_[size_t(head_[p])]);
+        if (--need_[t] == 0) ready_ |= mask_[t];
+    }
+    void take(int t)
+    {
+        --left_;
+        ready_ &= ~mask_[size_t(t)];
+        for (uint64_t m = mask_[size_t(t)]; m; m &= m - 1) {
+            const int p = __builtin_ctzll(m);
+            ++head_[p];
+            arrive(p);
+        }
     }
     const std::vector<int> &idx_;
     std::vector<uint64_t> mask_;
-    std::vector<std::vector<int>> queue_;
-    std::vector<size_t> head_;
+    std::vector<int> need_;
+    std::vector<int> queue_;              // the gates of qubit p, in order, at [head_[p], end_[p])
+    int32_t head_[64] = {0}, end_[64] = {0};
     std::vector<int> slot_;  // caller's gate index -> position in idx (formed by give_back)
-    uint64_t used_ = 0;
+    uint64_t used_ = 0, ready_ = 0;
     int left_ = 0;
 };
 
@@ -332,111 +366,155 @@ double plan_cost(const std::vector<Block> &blocks, const CostTable &cost)
     return s;
 }
 
-// Apply a canonical gate matrix (on block-local bits lb[0..kg-1], ascending)
-// to every column of the D x D canonical block matrix U (in place).  For each
-// group of the 2^kg rows the gate mixes, the new row m is the sum over m' of
-// G[m][m'] times row m', accumulated as whole rows (contiguous re/im pairs,
-// so the inner loop vectorises) in plain real arithmetic: std::complex
+namespace {
+
+typedef double v4d __attribute__((vector_size(32)));
+constexpr int kMaxD = 1 << SV_MAX_K;
+
+// A block matrix under construction: real and imaginary parts apart, rows of
+// kMaxD entries of which 2^m (at least 4, zeros behind 2^m) are in use.
+struct Building {
+    v4d re[kMaxD][kMaxD / 4], im[kMaxD][kMaxD / 4];
+};
+
+// Apply a canonical gate matrix (on the matrix's bits lb[0..kg-1]) to every
+// column of the d x d matrix V (in place).  For each group of the 2^kg
+// rows the gate mixes, the new row m is the sum over m' of G[m][m'] times row
+// m', four columns at a time in plain real arithmetic: std::complex
 // multiplication carries inf/nan recovery that dominates the cost.
-static void apply_to_columns(std::vector<cd> &Uc, int kb, const std::vector<cd> &Gc, int kg, const int *lb)
+__attribute__((target_clones("avx2", "default"))) void apply_to_columns(Building &V, int d, const cd *Gc, int kg,
+                                                                        const int *lb)
 {
-    const int D = 1 << kb, Dg = 1 << kg;
-    double *U = reinterpret_cast<double *>(Uc.data());
-    const double *G = reinterpret_cast<const double *>(Gc.data());
+    const int Dg = 1 << kg, dv = (d + 3) / 4;
+    const double *G = reinterpret_cast<const double *>(Gc);
     int tmask = 0;
     for (int j = 0; j < kg; ++j) tmask |= 1 << lb[j];
-    int off[1 << SV_MAX_K];
+    int off[kMaxD];
     for (int m = 0; m < Dg; ++m) {
         off[m] = 0;
         for (int j = 0; j < kg; ++j)
             if ((m >> j) & 1) off[m] |= 1 << lb[j];
     }
-    std::vector<double> acc(size_t(2) * Dg * D);
-    for (int base = 0; base < D; ++base) {
+    v4d ar[kMaxD][kMaxD / 4], ai[kMaxD][kMaxD / 4];
+    for (int base = 0; base < d; ++base) {
         if (base & tmask) continue;
-        std::fill(acc.begin(), acc.end(), 0.0);
         for (int m = 0; m < Dg; ++m) {
-            double *__restrict__ out = acc.data() + size_t(2) * m * D;
+            v4d *__restrict__ outr = ar[m], *__restrict__ outi = ai[m];
+            for (int c = 0; c < dv; ++c) outr[c] = outi[c] = v4d{0.0, 0.0, 0.0, 0.0};
             for (int mp = 0; mp < Dg; ++mp) {
-                const double gr = G[2 * (size_t(m) * Dg + mp)], gi = G[2 * (size_t(m) * Dg + mp) + 1];
+                const double gr = G[2 * (m * Dg + mp)], gi = G[2 * (m * Dg + mp) + 1];
                 if (gr == 0.0 && gi == 0.0) continue;
-                const double *__restrict__ row = U + size_t(2) * (base | off[mp]) * D;
-                for (int c = 0; c < D; ++c) {
-                    out[2 * c] += gr * row[2 * c] - gi * row[2 * c + 1];
-                    out[2 * c + 1] += gr * row[2 * c + 1] + gi * row[2 * c];
+                const v4d *__restrict__ xr = V.re[base | off[mp]], *__restrict__ xi = V.im[base | off[mp]];
+                for (int c = 0; c < dv; ++c) {
+                    outr[c] += gr * xr[c] - gi * xi[c];
+                    outi[c] += gr * xi[c] + gi * xr[c];
                 }
             }
         }
         for (int m = 0; m < Dg; ++m)
-            std::copy(acc.begin() + size_t(2) * m * D, acc.begin() + size_t(2) * (m + 1) * D,
-                      U + size_t(2) * (base | off[m]) * D);
+            for (int c = 0; c < dv; ++c) {
+                V.re[base | off[m]][c] = ar[m][c];
+                V.im[base | off[m]][c] = ai[m][c];
+            }
     }
 }
 
-// Embed an m-bit operator V (2^m x 2^m) into m + 1 bits with a new identity
-// bit at local position p (bits >= p shift up by one).
-static void insert_identity_bit(std::vector<cd> &V, int m, int p)
-{
-    const int d = 1 << m, d2 = 2 * d;
-    std::vector<cd> W(size_t(d2) * d2, cd(0));
-    const int lo = (1 << p) - 1;
-    auto spread = [&](int x, int bit) { return ((x & ~lo) << 1) | (bit << p) | (x & lo); };
-    for (int r = 0; r < d; ++r)
-        for (int c = 0; c < d; ++c) {
-            const cd v = V[size_t(r) * d + c];
-            if (v == cd(0)) continue;
-            W[size_t(spread(r, 0)) * d2 + spread(c, 0)] = v;
-            W[size_t(spread(r, 1)) * d2 + spread(c, 1)] = v;
-        }
-    V.swap(W);
-}
+}  // namespace
 
 void block_matrix(const sv_gate *g, Block &b)
 {
-    // The product is formed on the block bits touched so far (S, ascending):
-    // the block matrix is V (on S) times the identity on the untouched bits,
-    // so early gates act on a small V.
-    std::vector<int> S;               // block-local bits of V, ascending
-    std::vector<cd> V(1, cd(1));      // 1 x 1 identity
-    std::vector<cd> G;
-    for (int gi : b.members) {
-        int sq[SV_MAX_K];
-        gate_matrix_canonical(g[gi], G, sq);
-        int lb[SV_MAX_K];
-        for (int j = 0; j < g[gi].k; ++j) {
-            int r = 0;
-            while (b.q[r] != sq[j]) ++r;
-            // grow S by block bit r if the gate touches it first
-            auto it = std::lower_bound(S.begin(), S.end(), r);
-            if (it == S.end() || *it != r) {
-                const int p = int(it - S.begin());
-                insert_identity_bit(V, int(S.size()), p);
-                S.insert(it, r);
+    // The product is formed on the block bits touched so far, in the order of
+    // their first touch: the block matrix is V (on those) times the identity on
+    // the others, so early gates act on a small V.  One-qubit gates are held
+    // back as a 2 x 2 product for each bit and, where both bits of the next
+    // two-qubit gate have one, multiplied into that gate first: V is then gone
+    // over once instead of three times.
+    Building V;
+    double Gs[2 * kMaxD * kMaxD];  // not cd: its constructor would clear 64 KiB a block
+    cd *G = reinterpret_cast<cd *>(Gs);
+    cd held[SV_MAX_K][4];
+    bool holds[SV_MAX_K] = {false};
+    int at[SV_MAX_K], S[SV_MAX_K], m = 0;  // V's bit of each block bit (-1: none yet), and back
+    std::fill(at, at + SV_MAX_K, -1);
+    V.re[0][0] = v4d{1.0, 0.0, 0.0, 0.0};
+    V.im[0][0] = v4d{0.0, 0.0, 0.0, 0.0};
+    auto grow = [&](int r) {  // V gets a new top bit: V (x) identity
+        const int d = 1 << m, was = std::max(d, 4), now = std::max(2 * d, 4);
+        for (int x = 0; x < d; ++x)
+            for (int part = 0; part < 2; ++part) {
+                double *lo = reinterpret_cast<double *>(part ? V.im[x] : V.re[x]);
+                double *hi = reinterpret_cast<double *>(part ? V.im[d + x] : V.re[d + x]);
+                std::fill(hi, hi + d, 0.0);
+                std::copy(lo, lo + d, hi + d);
+                std::fill(hi + 2 * d, hi + std::max(now, 2 * d), 0.0);
+                std::fill(lo + was, lo + std::max(now, was), 0.0);
             }
+        S[m] = r;
+        at[r] = m++;
+    };
+    auto release = [&](int r) {  // apply what is held for block bit r
+        if (!holds[r]) return;
+        if (at[r] < 0) grow(r);
+        apply_to_columns(V, 1 << m, held[r], 1, &at[r]);
+        holds[r] = false;
+    };
+    for (int gi : b.members) {
+        int sq[SV_MAX_K], lr[SV_MAX_K], lb[SV_MAX_K];
+        gate_matrix_canonical(g[gi], G, sq);
+        const int kg = g[gi].k;
+        for (int j = 0; j < kg; ++j) {
+            lr[j] = 0;
+            while (b.q[lr[j]] != sq[j]) ++lr[j];
         }
-        for (int j = 0; j < g[gi].k; ++j) {
-            int r = 0;
-            while (b.q[r] != sq[j]) ++r;
-            lb[j] = int(std::lower_bound(S.begin(), S.end(), r) - S.begin());
+        if (kg == 1) {
+            cd *h = held[lr[0]];
+            if (holds[lr[0]]) {
+                const cd a0 = mul(G[0], h[0]) + mul(G[1], h[2]), a1 = mul(G[0], h[1]) + mul(G[1], h[3]);
+                const cd a2 = mul(G[2], h[0]) + mul(G[3], h[2]), a3 = mul(G[2], h[1]) + mul(G[3], h[3]);
+                h[0] = a0, h[1] = a1, h[2] = a2, h[3] = a3;
+            } else {
+                std::copy(G, G + 4, h);
+            }
+            holds[lr[0]] = true;
+            continue;
         }
-        apply_to_columns(V, int(S.size()), G, g[gi].k, lb);
+        if (kg == 2 && holds[lr[0]] && holds[lr[1]]) {  // G (h1 (x) h0), one factor after the other
+            const cd *h0 = held[lr[0]], *h1 = held[lr[1]];
+            cd X[16];
+            for (int r = 0; r < 4; ++r)
+                for (int c = 0; c < 4; ++c)
+                    X[4 * r + c] = mul(G[4 * r + (c & 2)], h0[c & 1]) + mul(G[4 * r + (c & 2) + 1], h0[2 + (c & 1)]);
+            for (int r = 0; r < 4; ++r)
+                for (int c = 0; c < 4; ++c)
+                    G[4 * r + c] = mul(X[4 * r + (c & 1)], h1[c >> 1]) + mul(X[4 * r + 2 + (c & 1)], h1[2 + (c >> 1)]);
+            holds[lr[0]] = holds[lr[1]] = false;
+        }
+        for (int j = 0; j < kg; ++j) {
+            release(lr[j]);
+            if (at[lr[j]] < 0) grow(lr[j]);
+            lb[j] = at[lr[j]];
+        }
+        apply_to_columns(V, 1 << m, G, kg, lb);
     }
+    for (int r = 0; r < b.k; ++r) release(r);
     // embed V into the full block: entries agree on the untouched bits
-    const int D = 1 << b.k, m = int(S.size()), d = 1 << m;
+    const int D = 1 << b.k, d = 1 << m;
     int smask = 0;
-    for (int r : S) smask |= 1 << r;
-    int dep[1 << SV_MAX_K];  // V index -> block index
+    for (int j = 0; j < m; ++j) smask |= 1 << S[j];
+    int dep[kMaxD];  // V index -> block index
     for (int x = 0; x < d; ++x) {
-        int y = 0;
+        dep[x] = 0;
         for (int j = 0; j < m; ++j)
-            if ((x >> j) & 1) y |= 1 << S[j];
-        dep[x] = y;
+            if ((x >> j) & 1) dep[x] |= 1 << S[j];
     }
     b.m.assign(size_t(D) * D, cd(0));
     for (int rest = 0; rest < D; ++rest) {
         if (rest & smask) continue;
-        for (int r = 0; r < d; ++r)
-            for (int c = 0; c < d; ++c) b.m[size_t(rest | dep[r]) * D + (rest | dep[c])] = V[size_t(r) * d + c];
+        for (int r = 0; r < d; ++r) {
+            const double *vr = reinterpret_cast<const double *>(V.re[r]), *vi = reinterpret_cast<const double *>(V.im[r]);
+            cd *row = &b.m[size_t(rest | dep[r]) * D + rest];
+            for (int c = 0; c < d; ++c) row[dep[c]] = cd(vr[c], vi[c]);
+        }
     }
 }
 

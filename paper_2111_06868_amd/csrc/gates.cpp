@@ -4,6 +4,7 @@
 // CX, ISWAP, FSIM, ...) but prints no matrices; these are the textbook ones.
 // Rotations are R_P(t) = exp(-i t P / 2), which the paper's statement that
 // RX(pi)**2.2 is the rotation by 2.2 pi fixes (principal-branch power).
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -47,6 +48,25 @@ int gate_arity(int kind)
     }
 }
 
+bool all_finite(const double *p, size_t count)
+{
+    // an all-ones exponent carries into the top bit; four chains, no branch
+    uint64_t bad[4] = {0, 0, 0, 0};
+    const uint64_t exponent = uint64_t(0x7ff) << 52;
+    size_t i = 0;
+    for (; i + 4 <= count; i += 4) {
+        uint64_t u[4];
+        std::memcpy(u, p + i, sizeof u);
+        for (int j = 0; j < 4; ++j) bad[j] |= (u[j] & exponent) + (uint64_t(1) << 52);
+    }
+    for (; i < count; ++i) {
+        uint64_t u;
+        std::memcpy(&u, p + i, sizeof u);
+        bad[0] |= (u & exponent) + (uint64_t(1) << 52);
+    }
+    return !((bad[0] | bad[1] | bad[2] | bad[3]) >> 63);
+}
+
 int check_gate_shape(const sv_gate &g)
 {
     int a = gate_arity(g.kind);
@@ -56,8 +76,7 @@ int check_gate_shape(const sv_gate &g)
         if (g.k < 1 || g.k > SV_MAX_K) return fail(SV_ERR_ARG, "matrix gate with k=%d (1..%d)", g.k, SV_MAX_K);
         if (!g.m) return fail(SV_ERR_ARG, "matrix gate without a matrix");
         size_t D = size_t(1) << g.k;
-        for (size_t i = 0; i < 2 * D * D; ++i)
-            if (!std::isfinite(g.m[i])) return fail(SV_ERR_ARG, "matrix gate has a non-finite entry");
+        if (!all_finite(g.m, 2 * D * D)) return fail(SV_ERR_ARG, "matrix gate has a non-finite entry");
     } else if (g.k != a) {
         return fail(SV_ERR_ARG, "gate kind %d acts on %d qubits, got k=%d", g.kind, a, g.k);
     }
@@ -80,49 +99,46 @@ int check_gate_qubits(const sv_gate &g, int n)
     return SV_OK;
 }
 
-static void set2(std::vector<cd> &m, cd a, cd b, cd c, cd d)
+void fill_gate_matrix(const sv_gate &g, cd *out)
 {
-    m = {a, b, c, d};
-}
-
-int gate_matrix_abi(const sv_gate &g, std::vector<cd> &out)
-{
-    int rc = check_gate_shape(g);
-    if (rc) return rc;
     const cd I(0, 1);
-    const double s2 = std::sqrt(0.5);
+    static const double s2 = std::sqrt(0.5);
     const cd hp = cd(0.5, 0.5), hm = cd(0.5, -0.5);  // (1+i)/2, (1-i)/2
+    auto set2 = [out](cd a, cd b, cd c, cd d) {
+        out[0] = a;
+        out[1] = b;
+        out[2] = c;
+        out[3] = d;
+    };
     switch (g.kind) {
     case SV_G_MATRIX: {
-        size_t D = size_t(1) << g.k;
-        out.resize(D * D);
+        const size_t D = size_t(1) << g.k;
         for (size_t i = 0; i < D * D; ++i) out[i] = cd(g.m[2 * i], g.m[2 * i + 1]);
-        return SV_OK;
+        return;
     }
-    case SV_G_I: set2(out, 1, 0, 0, 1); return SV_OK;
-    case SV_G_X: set2(out, 0, 1, 1, 0); return SV_OK;
-    case SV_G_Y: set2(out, 0, -I, I, 0); return SV_OK;
-    case SV_G_Z: set2(out, 1, 0, 0, -1); return SV_OK;
-    case SV_G_H: set2(out, s2, s2, s2, -s2); return SV_OK;
+    case SV_G_I: return set2(1, 0, 0, 1);
+    case SV_G_X: return set2(0, 1, 1, 0);
+    case SV_G_Y: return set2(0, -I, I, 0);
+    case SV_G_Z: return set2(1, 0, 0, -1);
+    case SV_G_H: return set2(s2, s2, s2, -s2);
     // sqrt(P) = (1+i)/2 I + (1-i)/2 P
-    case SV_G_SQRT_X: set2(out, hp, hm, hm, hp); return SV_OK;
-    case SV_G_SQRT_Y: set2(out, hp, hm * (-I), hm * I, hp); return SV_OK;
+    case SV_G_SQRT_X: return set2(hp, hm, hm, hp);
+    case SV_G_SQRT_Y: return set2(hp, hm * (-I), hm * I, hp);
     case SV_G_SQRT_W: {
         // W = (X + Y)/sqrt2 = [[0, (1-i)/sqrt2], [(1+i)/sqrt2, 0]]
         cd w01 = cd(s2, -s2), w10 = cd(s2, s2);
-        set2(out, hp, hm * w01, hm * w10, hp);
-        return SV_OK;
+        return set2(hp, hm * w01, hm * w10, hp);
     }
     case SV_G_RX: case SV_G_RY: case SV_G_RZ: {
         double c = std::cos(0.5 * g.params[0]), s = std::sin(0.5 * g.params[0]);
-        if (g.kind == SV_G_RX) set2(out, c, -I * s, -I * s, c);
-        else if (g.kind == SV_G_RY) set2(out, c, -s, s, c);
-        else set2(out, cd(c, -s), 0, 0, cd(c, s));
-        return SV_OK;
+        if (g.kind == SV_G_RX) set2(c, -I * s, -I * s, c);
+        else if (g.kind == SV_G_RY) set2(c, -s, s, c);
+        else set2(cd(c, -s), 0, 0, cd(c, s));
+        return;
     }
     default: break;
     }
-    out.assign(16, cd(0));
+    std::fill(out, out + 16, cd(0));
     auto at = [&](int r, int c) -> cd & { return out[r * 4 + c]; };
     switch (g.kind) {
     case SV_G_CZ: at(0, 0) = at(1, 1) = at(2, 2) = 1; at(3, 3) = -1; break;
@@ -137,17 +153,29 @@ int gate_matrix_abi(const sv_gate &g, std::vector<cd> &out)
         at(3, 3) = std::exp(-I * g.params[1]);
         break;
     }
-    default: return fail(SV_ERR_ARG, "unknown gate kind %d", g.kind);
+    default: break;
     }
+}
+
+int gate_matrix_abi(const sv_gate &g, std::vector<cd> &out)
+{
+    if (int rc = check_gate_shape(g)) return rc;
+    out.resize(size_t(1) << (2 * g.k));
+    fill_gate_matrix(g, out.data());
     return SV_OK;
 }
 
-int gate_matrix_canonical(const sv_gate &g, std::vector<cd> &m, int *sorted_q)
+void gate_matrix_canonical(const sv_gate &g, cd *m, int *sorted_q)
 {
-    std::vector<cd> abi;
-    int rc = gate_matrix_abi(g, abi);
-    if (rc) return rc;
-    const int k = g.k;
+    const int k = g.k, D = 1 << k;
+    if (k == 1) {
+        sorted_q[0] = g.q[0];
+        fill_gate_matrix(g, m);
+        return;
+    }
+    double entries[2 << (2 * SV_MAX_K)];  // not cd: its constructor would clear 64 KiB a gate
+    cd *abi = reinterpret_cast<cd *>(entries);
+    fill_gate_matrix(g, abi);
     // rank[j] = number of positions below q[j] = canonical bit of q[j]
     int rank[SV_MAX_K];
     for (int j = 0; j < k; ++j) {
@@ -155,17 +183,22 @@ int gate_matrix_canonical(const sv_gate &g, std::vector<cd> &m, int *sorted_q)
         for (int i = 0; i < k; ++i) rank[j] += g.q[i] < g.q[j];
         sorted_q[rank[j]] = g.q[j];
     }
-    const int D = 1 << k;
-    std::vector<int> to_can(D);
+    int to_can[1 << SV_MAX_K];
     for (int a = 0; a < D; ++a) {
         int c = 0;
         for (int j = 0; j < k; ++j)
             if ((a >> (k - 1 - j)) & 1) c |= 1 << rank[j];
         to_can[a] = c;
     }
-    m.assign(size_t(D) * D, cd(0));
     for (int a = 0; a < D; ++a)
-        for (int b = 0; b < D; ++b) m[size_t(to_can[a]) * D + to_can[b]] = abi[size_t(a) * D + b];
+        for (int b = 0; b < D; ++b) m[to_can[a] * D + to_can[b]] = abi[a * D + b];
+}
+
+int gate_matrix_canonical(const sv_gate &g, std::vector<cd> &m, int *sorted_q)
+{
+    if (int rc = check_gate_shape(g)) return rc;
+    m.resize(size_t(1) << (2 * g.k));
+    gate_matrix_canonical(g, m.data(), sorted_q);
     return SV_OK;
 }
 

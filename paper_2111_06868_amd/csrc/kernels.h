@@ -4,11 +4,40 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <cstring>
 
 #include "common.h"
 
 namespace sv {
 namespace dev {
+
+// FP32 -> FP16 bits, round to nearest even, and back (host; in integer
+// arithmetic, since without an instruction for it the compiler calls a function
+// for each value).
+inline uint32_t half_bits(float x)
+{
+    uint32_t u, t;
+    std::memcpy(&u, &x, 4);
+    const uint32_t a = u & 0x7FFFFFFFu, sign = (u >> 16) & 0x8000u;
+    if (a >= 0x477FF000u) return sign | (a > 0x7F800000u ? 0x7E00u : 0x7C00u);  // 65520 and above: infinity
+    if (a < 0x38800000u) {  // below 2^-14: the sum with 1/2 rounds to the subnormals' spacing, 2^-24
+        float f;
+        std::memcpy(&f, &a, 4);
+        f += 0.5f;
+        std::memcpy(&t, &f, 4);
+        return sign | (t - 0x3F000000u);
+    }
+    return sign | ((a - 0x38000000u + 0xFFFu + ((a >> 13) & 1u)) >> 13);
+}
+inline float half_value(uint32_t h)
+{
+    const uint32_t e = h & 0x7C00u, m = h & 0x3FFu;
+    if (e == 0) return (h & 0x8000u ? -0x1p-24f : 0x1p-24f) * float(m);
+    const uint32_t u = (h & 0x8000u) << 16 | ((h & 0x7FFFu) << 13) + (e == 0x7C00u ? 0x70000000u : 0x38000000u);
+    float x;
+    std::memcpy(&x, &u, 4);
+    return x;
+}
 
 constexpr int kRedBlocks = 1024;  // fixed first-stage grid of every reduction
 constexpr int kRedThreads = 256;

@@ -453,19 +453,6 @@ float host_bf2f(uint16_t h)
     std::memcpy(&x, &u, 4);
     return x;
 }
-uint16_t host_f2h(float x)
-{
-    _Float16 h = (_Float16)x;
-    uint16_t r;
-    std::memcpy(&r, &h, 2);
-    return r;
-}
-float host_h2f(uint16_t r)
-{
-    _Float16 h;
-    std::memcpy(&h, &r, 2);
-    return (float)h;
-}
 
 }  // namespace
 
@@ -509,8 +496,8 @@ void pack_real_form_split(const cd *m, int k, bool fp16, uint16_t *const *parts)
                         }
                         if (fp16) {  // the second part held times 2^11
                             const double f = p ? 2048.0 : 1.0;
-                            parts[p][o] = host_f2h(float(x * f));
-                            x -= double(host_h2f(parts[p][o])) / f;
+                            parts[p][o] = uint16_t(half_bits(float(x * f)));
+                            x -= double(half_value(parts[p][o])) / f;
                         } else {
                             parts[p][o] = host_f2bf(float(x));
                             x -= double(host_bf2f(parts[p][o]));

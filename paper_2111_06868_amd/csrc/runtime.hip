@@ -363,31 +363,26 @@ size_t pack_operands(std::vector<Launch> &launches, int dtype, PinBuf &stage)
 
 // Canonical 16 x 16 matrix of a block on positions q[0..k-1] (ascending)
 // padded with identity on the extra positions of p4 (ascending, 4 entries).
-static void pad_to_four(const Block &b, const int *p4, std::vector<cd> &out)
+static void pad_to_four(const Block &b, const int *p4, cd *out)
 {
-    int where[4];  // for each of the 4 padded bits: index in b.q, or -1
-    for (int j = 0; j < 4; ++j) {
-        where[j] = -1;
-        for (int i = 0; i < b.k; ++i)
-            if (b.q[i] == p4[j]) where[j] = i;
+    if (b.k == 4) {
+        std::copy(b.m.begin(), b.m.end(), out);
+        return;
+    }
+    int own[16], rest[16];  // each padded index's bits of b, and its other bits
+    for (int r = 0; r < 16; ++r) {
+        own[r] = 0;
+        rest[r] = r;
+        for (int j = 0; j < 4; ++j)
+            for (int i = 0; i < b.k; ++i)
+                if (b.q[i] == p4[j] && ((r >> j) & 1)) {
+                    own[r] |= 1 << i;
+                    rest[r] &= ~(1 << j);
+                }
     }
     const int D = 1 << b.k;
-    out.assign(256, cd(0));
     for (int r = 0; r < 16; ++r)
-        for (int c = 0; c < 16; ++c) {
-            int rr = 0, cc = 0;
-            bool same = true;
-            for (int j = 0; j < 4; ++j) {
-                const int rb = (r >> j) & 1, cb = (c >> j) & 1;
-                if (where[j] >= 0) {
-                    rr |= rb << where[j];
-                    cc |= cb << where[j];
-                } else if (rb != cb) {
-                    same = false;
-                }
-            }
-            if (same) out[size_t(r) * 16 + c] = b.m[size_t(rr) * D + cc];
-        }
+        for (int c = 0; c < 16; ++c) out[r * 16 + c] = rest[r] == rest[c] ? b.m[size_t(own[r]) * D + own[c]] : cd(0);
 }
 
 static uint64_t mask_of(const Block &b)
@@ -435,12 +430,8 @@ static void tile_pass_positions(const Block *const *blocks, int count, int n, in
 void tile_pass_blocks(const Block *const *blocks, int count, int n, int (*sub_pos)[4], std::vector<cd> &mats)
 {
     tile_pass_positions(blocks, count, n, sub_pos);
-    mats.clear();
-    for (int sb = 0; sb < count; ++sb) {
-        std::vector<cd> m4;
-        pad_to_four(*blocks[sb], sub_pos[sb], m4);
-        mats.insert(mats.end(), m4.begin(), m4.end());
-    }
+    mats.resize(size_t(256) * count);
+    for (int sb = 0; sb < count; ++sb) pad_to_four(*blocks[sb], sub_pos[sb], mats.data() + 256 * sb);
 }
 
 void group_tile_passes(const std::vector<Block> &blocks, int n, int precision, std::vector<Launch> &out)

@@ -1317,22 +1317,6 @@ int tile_max_blocks(int tile_bits, int waves, int prec)
                                                                    : max_blocks_of<16>(tile_bits, waves);
 }
 
-static uint32_t f2h_rne(float x)
-{
-    const _Float16 h = static_cast<_Float16>(x);  // round to nearest even
-    uint16_t u;
-    std::memcpy(&u, &h, 2);
-    return u;
-}
-
-static float h2f(uint32_t u16)
-{
-    const uint16_t u = uint16_t(u16);
-    _Float16 h;
-    std::memcpy(&h, &u, 2);
-    return float(h);
-}
-
 static uint32_t f2bf_rne(float x)
 {
     uint32_t u;
@@ -1375,10 +1359,10 @@ void pack_tile_operand(const cd *m, int prec, uint32_t *out)
                 uint32_t hr, hi;
                 if (prec == kTileOperandF16) {
                     const double f = p ? 2048.0 : 1.0;
-                    hr = f2h_rne(float(xr * f));
-                    hi = f2h_rne(float(xi * f));
-                    xr -= double(h2f(hr)) / f;
-                    xi -= double(h2f(hi)) / f;
+                    hr = half_bits(float(xr * f));
+                    hi = half_bits(float(xi * f));
+                    xr -= double(half_value(hr)) / f;
+                    xi -= double(half_value(hi)) / f;
                 } else {
                     hr = f2bf_rne(float(xr));
                     hi = f2bf_rne(float(xi));
