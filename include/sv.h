@@ -243,7 +243,12 @@ int sv_plan_rule(const sv_plan *p, int *out);
  * pass number >= 0 are applied together in one read and one write of the
  * state; -1 means the block is applied on its own. */
 int sv_plan_block_pass(const sv_plan *p, int b, int32_t *pass);
-/* Apply a plan's blocks in order with the given SV_PREC_* arithmetic.  With
+/* Apply a plan's blocks in order with the given SV_PREC_* arithmetic.  Blocks
+ * may share passes over the state with others that they commute with; in FP32
+ * (SV_PREC_SPLIT_BF16X3 likewise) and FP64, a plan of the paper or enhanced rule
+ * with blocks of four and more qubits runs as tile passes of the same gates
+ * (every qubit keeps its gate order) where the cost table prices those lower,
+ * on states of >= 14 qubits and with no gate of more than four.  With
  * use_graph = 1 the launches are captured into a hipGraph and launched as one;
  * the state keeps the instantiated graph, and a later call whose launches have
  * the same structure (block positions, kernels, launch shapes; the matrices

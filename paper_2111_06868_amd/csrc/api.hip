@@ -152,7 +152,40 @@ int blocks_to_launches(const std::vector<Block> &blocks, const sv_state *s, int 
         L.m = b.m;
         out.push_back(std::move(L));
     }
+    if (int rc = group_dense_passes(out, s->n, precision)) return rc;
     return group_gate_passes(out, s->n, s->dtype);
+}
+
+// Dense blocks of four and more qubits cost a pass over the state each.  In FP32
+// and FP64 a plan that has some runs as tile passes of the same gates instead
+// (in an order that keeps every qubit's own), where those are priced lower.
+// Eight cycles on a two-row ladder, k = 4, dense blocks against tile passes:
+// FP32 139 to 113 us at 14 qubits, 280 to 191 at 20 and 1316 to 627 at 24, FP64
+// 496 to 132, 802 to 240 and 3520 to 1491, so from the smallest state a tile
+// takes.
+// The 16-bit splits keep their blocks (group_dense_passes for FP16), since they
+// round the state once a block, and blocks of at most three qubits share passes as they
+// are (group_gate_passes).
+bool takes_tiles(int rule, int precision, int n)
+{
+    return (rule == SV_RULE_PAPER || rule == SV_RULE_ENHANCED) && n >= dev::kMinTileQubits &&
+           (precision == SV_PREC_FP32 || precision == SV_PREC_SPLIT_BF16X3 || precision == SV_PREC_FP64);
+}
+bool tiles_are_cheaper(const std::vector<Block> &blocks, const std::vector<Block> &tiled, int n, int precision)
+{
+    const CostTable cost = lookup_costs(n, precision, nullptr);
+    return tiled_plan_cost(tiled, n, cost) < plan_cost(blocks, cost) - 1e-12;
+}
+// The tile passes of the gates of a plan (positions and members, no matrices),
+// or none where one of its gates or all of its blocks rule them out.
+int gates_as_tiles(const sv_gate *g, int G, int n, int precision, const std::vector<Block> &blocks,
+                   std::vector<Block> &tiled)
+{
+    tiled.clear();
+    bool wide = false;
+    for (const auto &b : blocks) wide = wide || b.k >= 4;
+    for (int i = 0; i < G; ++i) wide = wide && g[i].k <= 4;
+    return wide ? fuse_gates(g, G, n, 4, SV_RULE_TILED, default_costs(), tiled, false, precision) : SV_OK;
 }
 
 int choose_plan_uncached(const sv_gate *g, int G, int n, int dtype, int precision, int rule, int max_k, bool found,
@@ -474,6 +507,8 @@ int fuse_plan(const sv_gate *g, int G, int n, int max_k, int rule, int precision
     p->max_k = max_k;
     p->rule = rule;
     int rc = fuse_gates(g, G, n, max_k, rule, lookup_costs(n, cost_prec, nullptr), p->blocks, true, precision);
+    if (!rc && takes_tiles(rule, cost_prec, n)) rc = gates_as_tiles(g, G, n, precision, p->blocks, p->tiled);
+    if (!rc) block_matrices(g, p->tiled);
     if (rc) {
         delete p;
         return rc;
@@ -589,7 +624,10 @@ extern "C" int sv_apply_plan(sv_state *s, const sv_plan *p, int precision, int u
             if (int rc = check_unitary(p->blocks[i].m, p->blocks[i].k, what.c_str())) return rc;
         }
     std::vector<Launch> L;
-    if (int rc = blocks_to_launches(p->blocks, s, precision, p->rule, L)) return rc;
+    const bool tiles = !p->tiled.empty() && takes_tiles(p->rule, precision, s->n) &&
+                       tiles_are_cheaper(p->blocks, p->tiled, s->n, precision);
+    if (int rc = blocks_to_launches(tiles ? p->tiled : p->blocks, s, precision, tiles ? SV_RULE_TILED : p->rule, L))
+        return rc;
     if (int rc = select_device(s)) return rc;
     return run_launches(s, L, use_graph != 0);
 }
@@ -619,10 +657,18 @@ int run_circuit_impl(sv_state *s, const sv_gate *g, int G, const sv_run_opts *o,
     if (max_k == -1 || rule == SV_RULE_AUTO) {
         if (int rc = choose_plan(g, G, s->n, s->dtype, o->precision, rule, max_k, &rule, &max_k)) return rc;
     }
-    std::vector<Block> blocks;
-    if (int rc = fuse_gates(g, G, s->n, max_k, rule, lookup_costs(s->n, o->precision, nullptr), blocks, true,
+    std::vector<Block> blocks, tiled;
+    if (int rc = fuse_gates(g, G, s->n, max_k, rule, lookup_costs(s->n, o->precision, nullptr), blocks, false,
                             o->precision))
         return rc;
+    if (takes_tiles(rule, o->precision, s->n)) {
+        if (int rc = gates_as_tiles(g, G, s->n, o->precision, blocks, tiled)) return rc;
+        if (!tiled.empty() && tiles_are_cheaper(blocks, tiled, s->n, o->precision)) {
+            blocks.swap(tiled);
+            rule = SV_RULE_TILED;
+        }
+    }
+    block_matrices(g, blocks);
     std::vector<Launch> L;
     if (int rc = blocks_to_launches(blocks, s, o->precision, rule, L)) return rc;
     if (int rc = select_device(s)) return rc;

@@ -119,6 +119,8 @@ double tiled_plan_cost(const std::vector<Block> &blocks, int n, const CostTable 
 
 // Canonical matrix of a block from its member gates.
 void block_matrix(const sv_gate *g, Block &b);
+// Of all blocks, on several threads for large jobs.
+void block_matrices(const sv_gate *g, std::vector<Block> &blocks);
 
 // ---------------------------------------------------------------- density matrices
 // Rewrite gates g (on qubits 0..n-1) with super operators among them as a
@@ -150,6 +152,7 @@ struct sv_plan {
     int max_k = 0;
     int rule = 0;
     std::vector<sv::Block> blocks;
+    std::vector<sv::Block> tiled;  // the same gates as tile passes, or empty (gates_as_tiles)
     // device-side cache (filled by the runtime when the plan is applied)
     void *cache = nullptr;
 };

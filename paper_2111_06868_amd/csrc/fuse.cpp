@@ -425,15 +425,10 @@ void block_matrix(const sv_gate *g, Block &b)
 {
     // The product is formed on the block bits touched so far, in the order of
     // their first touch: the block matrix is V (on those) times the identity on
-    // the others, so early gates act on a small V.  One-qubit gates are held
-    // back as a 2 x 2 product for each bit and, where both bits of the next
-    // two-qubit gate have one, multiplied into that gate first: V is then gone
-    // over once instead of three times.
+    // the others, so early gates act on a small V.
     Building V;
     double Gs[2 * kMaxD * kMaxD];  // not cd: its constructor would clear 64 KiB a block
     cd *G = reinterpret_cast<cd *>(Gs);
-    cd held[SV_MAX_K][4];
-    bool holds[SV_MAX_K] = {false};
     int at[SV_MAX_K], S[SV_MAX_K], m = 0;  // V's bit of each block bit (-1: none yet), and back
     std::fill(at, at + SV_MAX_K, -1);
     V.re[0][0] = v4d{1.0, 0.0, 0.0, 0.0};
@@ -452,51 +447,17 @@ void block_matrix(const sv_gate *g, Block &b)
         S[m] = r;
         at[r] = m++;
     };
-    auto release = [&](int r) {  // apply what is held for block bit r
-        if (!holds[r]) return;
-        if (at[r] < 0) grow(r);
-        apply_to_columns(V, 1 << m, held[r], 1, &at[r]);
-        holds[r] = false;
-    };
     for (int gi : b.members) {
-        int sq[SV_MAX_K], lr[SV_MAX_K], lb[SV_MAX_K];
+        int sq[SV_MAX_K], lb[SV_MAX_K];
         gate_matrix_canonical(g[gi], G, sq);
-        const int kg = g[gi].k;
-        for (int j = 0; j < kg; ++j) {
-            lr[j] = 0;
-            while (b.q[lr[j]] != sq[j]) ++lr[j];
+        for (int j = 0; j < g[gi].k; ++j) {
+            int r = 0;
+            while (b.q[r] != sq[j]) ++r;
+            if (at[r] < 0) grow(r);
+            lb[j] = at[r];
         }
-        if (kg == 1) {
-            cd *h = held[lr[0]];
-            if (holds[lr[0]]) {
-                const cd a0 = mul(G[0], h[0]) + mul(G[1], h[2]), a1 = mul(G[0], h[1]) + mul(G[1], h[3]);
-                const cd a2 = mul(G[2], h[0]) + mul(G[3], h[2]), a3 = mul(G[2], h[1]) + mul(G[3], h[3]);
-                h[0] = a0, h[1] = a1, h[2] = a2, h[3] = a3;
-            } else {
-                std::copy(G, G + 4, h);
-            }
-            holds[lr[0]] = true;
-            continue;
-        }
-        if (kg == 2 && holds[lr[0]] && holds[lr[1]]) {  // G (h1 (x) h0), one factor after the other
-            const cd *h0 = held[lr[0]], *h1 = held[lr[1]];
-            cd X[16];
-            for (int r = 0; r < 4; ++r)
-                for (int c = 0; c < 4; ++c)
-                    X[4 * r + c] = mul(G[4 * r + (c & 2)], h0[c & 1]) + mul(G[4 * r + (c & 2) + 1], h0[2 + (c & 1)]);
-            for (int r = 0; r < 4; ++r)
-                for (int c = 0; c < 4; ++c)
-                    G[4 * r + c] = mul(X[4 * r + (c & 1)], h1[c >> 1]) + mul(X[4 * r + 2 + (c & 1)], h1[2 + (c >> 1)]);
-            holds[lr[0]] = holds[lr[1]] = false;
-        }
-        for (int j = 0; j < kg; ++j) {
-            release(lr[j]);
-            if (at[lr[j]] < 0) grow(lr[j]);
-            lb[j] = at[lr[j]];
-        }
-        apply_to_columns(V, 1 << m, G, kg, lb);
+        apply_to_columns(V, 1 << m, G, g[gi].k, lb);
     }
-    for (int r = 0; r < b.k; ++r) release(r);
     // embed V into the full block: entries agree on the untouched bits
     const int D = 1 << b.k, d = 1 << m;
     int smask = 0;
@@ -520,7 +481,7 @@ void block_matrix(const sv_gate *g, Block &b)
 
 // Matrices of all blocks; they are independent, so large jobs are spread
 // over host threads.
-static int block_matrices(const sv_gate *g, std::vector<Block> &blocks)
+void block_matrices(const sv_gate *g, std::vector<Block> &blocks)
 {
     size_t work = 0;
     for (const auto &B : blocks) work += B.members.size() << (2 * B.k);
@@ -534,7 +495,6 @@ static int block_matrices(const sv_gate *g, std::vector<Block> &blocks)
     for (unsigned t = 1; t < nt; ++t) pool.emplace_back(worker);
     worker();
     for (auto &th : pool) th.join();
-    return SV_OK;
 }
 
 int fuse_gates(const sv_gate *g, int G, int n, int max_k, int rule, const CostTable &cost,
@@ -577,7 +537,8 @@ int fuse_gates(const sv_gate *g, int G, int n, int max_k, int rule, const CostTa
             passes.give_back(back);
         }
         merge_small_blocks(g, max_k, pass_fits, blocks);
-        return with_matrices ? block_matrices(g, blocks) : SV_OK;
+        if (with_matrices) block_matrices(g, blocks);
+    return SV_OK;
     }
     std::vector<WBlock> wb;
     wb.reserve(G);
@@ -653,7 +614,8 @@ int fuse_gates(const sv_gate *g, int G, int n, int max_k, int rule, const CostTa
         const double ca = plan_cost(alt, cost), cb = plan_cost(blocks, cost);
         if (ca < cb - 1e-12 || (ca <= cb + 1e-12 && alt.size() < blocks.size())) blocks.swap(alt);
     }
-    return with_matrices ? block_matrices(g, blocks) : SV_OK;
+    if (with_matrices) block_matrices(g, blocks);
+    return SV_OK;
 }
 
 

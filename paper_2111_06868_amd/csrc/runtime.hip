@@ -474,6 +474,42 @@ void group_tile_passes(const std::vector<Block> &blocks, int n, int precision, s
         }
 }
 
+int group_dense_passes(std::vector<Launch> &launches, int n, int precision)
+{
+    if (n < dev::kMinTileQubits) return SV_OK;
+    auto takes = [](const Launch &L) { return L.k == 4 && L.path == PATH_SPLIT_FP16; };
+    const CostTable cost = lookup_costs(n, precision, nullptr);
+    std::vector<Launch> out, passes;
+    for (size_t at = 0; at < launches.size();) {
+        size_t end = at;
+        while (end < launches.size() && takes(launches[end])) ++end;
+        if (end - at < 2) {
+            out.push_back(std::move(launches[at++]));
+            continue;
+        }
+        std::vector<sv_gate> g(end - at);
+        for (size_t i = at; i < end; ++i) {
+            sv_gate &x = g[i - at];
+            x.kind = SV_G_MATRIX;
+            x.k = 4;
+            for (int j = 0; j < 4; ++j) x.q[j] = launches[i].q[3 - j];  // canonical order: the lowest position is the lowest bit
+            x.param = -1;
+            x.m = reinterpret_cast<const double *>(launches[i].m.data());
+        }
+        std::vector<Block> blocks;
+        if (int rc = fuse_gates(g.data(), int(g.size()), n, 4, SV_RULE_TILED, cost, blocks, true, precision)) return rc;
+        if (tiled_plan_cost(blocks, n, cost) < cost.ms[4] * double(end - at) - 1e-12) {
+            group_tile_passes(blocks, n, precision, passes);
+            for (auto &L : passes) out.push_back(std::move(L));
+        } else {
+            for (size_t i = at; i < end; ++i) out.push_back(std::move(launches[i]));
+        }
+        at = end;
+    }
+    launches.swap(out);
+    return SV_OK;
+}
+
 int group_gate_passes(std::vector<Launch> &launches, int n, int dtype)
 {
     if (n < dev::kMinTileQubits) return SV_OK;
