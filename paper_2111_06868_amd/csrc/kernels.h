@@ -68,7 +68,8 @@ hipError_t launch_mfma_split(int k, bool fp16, const int *sorted_q, const uint16
 // tile_max_blocks() 4-qubit blocks whose positions have a union of at most
 // tile_bits positions, applied in one HBM pass over tiles of
 // 2^tile_bits amplitudes held by workgroups of `waves` waves; shapes
-// (14, 8), (14, 16), (13, 4), (13, 8).  sub_pos rows ascending.  d_a = the
+// (14, 8), (14, 16), (13, 4), (13, 8) and, for small states, (12, 4).  sub_pos
+// rows ascending.  d_a = the
 // blocks' operands (pack_tile_operand), back to back.  Needs n >= tile_bits.
 constexpr int kMaxTileSubBlocks = kTilePassMaxBlocks;
 constexpr int kMinTileQubits = 14;
@@ -96,8 +97,8 @@ struct TileArgs {
 constexpr int kTileOperandWords = 768, kTileOperandWordsF64 = 1024;
 constexpr int kTileOperandF32 = 0, kTileOperandBF16 = 1, kTileOperandF16 = 2, kTileOperandBF16X3 = 3, kTileOperandF64 = 4;
 constexpr int tile_operand_words(int prec) { return prec == kTileOperandF64 ? kTileOperandWordsF64 : kTileOperandWords; }
-// FP64 passes have one launch shape: tiles of 2^14 8-byte units (2^13
-// amplitudes), 8 waves; their unions have at most 13 positions.
+// FP64 passes: tiles of 2^14 8-byte units (2^13 amplitudes), 8 waves, or the
+// small shapes; their unions have at most 13 positions.
 constexpr int kF64TileBits = 14, kF64TileWaves = 8, kF64MaxUnion = 13;
 void pack_tile_operand(const cd *m, int prec, uint32_t *out);
 // Tile arguments of n_sub blocks (positions ascending per block) on an

@@ -565,6 +565,34 @@ int group_gate_passes(std::vector<Launch> &launches, int n, int dtype)
     return SV_OK;
 }
 
+// The launch shape of blocks [first, first + m) of a tile pass over one state,
+// or two.  A state of few tiles leaves CUs idle, and a workgroup's time is that
+// of its blocks one after another: smaller tiles spread the state over more
+// CUs with fewer waves each.  Tiles of 2^12 up to 256 of them, else 2^13, else
+// the shape that is set; a pass of more positions than the small tile has
+// takes the next one.  Seven blocks, (14, 16) against the small shape: FP32 at 14
+// qubits 27.8 to 19.0 us, at 20 30.5 to 20.9, at 21 (2^13) 32.7 to 24.5; FP16 at 20 26.4
+// to 18.9; FP64 (virtual position 0, 2^14 units of 8 bytes) at 20 45.9 to 30.3; one
+// size further on the small tiles lose (FP32, 22 qubits: 35.9 to 39.7).  A shape
+// other than the default is kept: the caller or the tuner chose it.
+struct TileShape {
+    int bits, waves;
+};
+static TileShape tile_shape_for(const Launch &L, int first, int m, int n, bool two)
+{
+    const Tuning &T = tuning();
+    const bool f64 = L.path == PATH_TILE_FP64;
+    if (!f64 && (T.tile_bits != 14 || T.tile_waves != 16)) return {T.tile_bits, T.tile_waves};
+    uint64_t u = 1;  // position 0 is in every tile
+    for (int s = first; s < first + m; ++s)
+        for (int j = 0; j < 4; ++j) u |= uint64_t(1) << (L.sub_pos[s][j] + (f64 ? 1 : 0));
+    const int small = n + (f64 ? 1 : 0) + (two ? 1 : 0) - 8;  // 2^8 tiles
+    const int bits = std::max(std::max(small, 12), __builtin_popcountll(u));
+    if (bits == 12) return {12, 4};
+    if (bits == 13) return {13, 8};
+    return f64 ? TileShape{dev::kF64TileBits, dev::kF64TileWaves} : TileShape{T.tile_bits, T.tile_waves};
+}
+
 int enqueue(const std::vector<Launch> &launches, int dtype, void *psi, int n, const void *arena, hipStream_t st)
 {
     return enqueue(launches.data(), launches.size(), dtype, psi, n, arena, st);
@@ -582,17 +610,11 @@ int enqueue(const Launch *first, size_t count, int dtype, void *psi, int n, cons
     // copy-in, the last unscales it at copy-out, the ones between copy it as
     // it is.  Launches in between act on it linearly; the state is plain again
     // when this call's launches end.
-    const uint64_t norm_tiles = n >= T.tile_bits ? uint64_t(1) << (n - T.tile_bits) : 0;  // no tile passes below
-    const int norm_grid_cap = T.tile_grid_cap * dev::tile_wgs_per_cu(T.tile_bits, T.tile_waves);
-    const uint64_t norm_grid_size =
-        norm_grid_cap > 0 && norm_tiles > uint64_t(norm_grid_cap) ? uint64_t(norm_grid_cap) : norm_tiles;
     int norm_launches = 0;  // split-FP16 tile launches of this call that take part
-    if (!psi2 && norm_grid_size <= uint64_t(kTileNormSlots))
+    const int norm_cap = dev::tile_max_blocks(T.tile_bits, T.tile_waves, dev::kTileOperandF16);
+    if (!psi2)
         for (const Launch *it = first; it != first + count; ++it)
-            if (it->path == PATH_TILE_FP16) {
-                const int cap = dev::tile_max_blocks(T.tile_bits, T.tile_waves, dev::kTileOperandF16);
-                norm_launches += (it->k + cap - 1) / cap;
-            }
+            if (it->path == PATH_TILE_FP16) norm_launches += (it->k + norm_cap - 1) / norm_cap;
     int norm_grid = 0, norm_done = 0;
     for (const Launch *it = first; it != first + count; ++it) {
         const Launch &L = *it;
@@ -604,16 +626,16 @@ int enqueue(const Launch *first, size_t count, int dtype, void *psi, int n, cons
             continue;
         }
         if (is_tile_path(L.path)) {
-            // one launch per chunk of blocks whose operands fit the shape's LDS
+            // one launch per chunk of blocks whose operands fit the set shape's
+            // LDS (the smaller shapes hold more)
             const int cap = dev::tile_max_blocks(T.tile_bits, T.tile_waves, tile_operand_prec(L.path));
             const size_t op_bytes = 4 * dev::tile_operand_words(tile_operand_prec(L.path));
-            const int grid_cap =
-                T.tile_grid_cap * (L.path == PATH_TILE_FP64 ? 1 : dev::tile_wgs_per_cu(T.tile_bits, T.tile_waves));
-            const uint64_t n_tiles = uint64_t(1) << (n - T.tile_bits);
-            const uint64_t grid = grid_cap > 0 && n_tiles > uint64_t(grid_cap) ? uint64_t(grid_cap) : n_tiles;
-            const bool use_norm = L.path == PATH_TILE_FP16 && !psi2 && grid <= uint64_t(kTileNormSlots);
+            const bool use_norm = L.path == PATH_TILE_FP16 && !psi2;
             for (int c = 0; c < L.k; c += cap) {
                 const int m = std::min(cap, L.k - c);
+                const TileShape shape = tile_shape_for(L, c, m, n, psi2 != nullptr);
+                const int per_cu = L.path == PATH_TILE_FP64 ? 1 : dev::tile_wgs_per_cu(shape.bits, shape.waves);
+                const int grid_cap = std::min(kTileNormSlots, T.tile_grid_cap * per_cu);
                 dev::TileNorm norm;
                 int launched = 0;
                 if (use_norm) {
@@ -630,8 +652,8 @@ int enqueue(const Launch *first, size_t count, int dtype, void *psi, int n, cons
                 if (c == 0 && L.basis >= 0) norm.basis = L.basis;  // reads nothing: the state starts here
                 LaunchTimer timer(stat_class(path_family(L.path), m), st);
                 hipError_t e = dev::launch_tile_pass(m, L.sub_pos + c, A + L.arena_off + c * op_bytes,
-                                                     tile_operand_prec(L.path), psi, n, st, grid_cap, T.tile_bits,
-                                                     T.tile_waves, psi2, norm, &launched);
+                                                     tile_operand_prec(L.path), psi, n, st, grid_cap, shape.bits,
+                                                     shape.waves, psi2, norm, &launched);
                 if (e != hipSuccess)
                     return fail(SV_ERR_HIP, "tile pass launch (%d blocks): %s", m, hipGetErrorString(e));
                 if (norm.out) norm_grid = launched;

@@ -104,7 +104,8 @@ __device__ __forceinline__ uint32_t frag_swz(uint32_t lane)
 // columns per 4-qubit block, in blocks of 32 split evenly over the waves.
 // Shapes: (14, 8) and (14, 16) one 128 KiB tile per CU, with 2 or 4 waves
 // per SIMD; (13, 4) two 64 KiB workgroups per CU, so one can copy while the
-// other computes; (13, 8).  MAX_SUB blocks' operands of LW words per lane
+// other computes; (13, 8).  (12, 4): small states (tile_shape_for), two
+// workgroups per CU.  MAX_SUB blocks' operands of LW words per lane
 // fit in the LDS left beside the tile.
 template <int TB, int WAVES, int LW = 24>
 struct TileCfg {
@@ -116,7 +117,7 @@ struct TileCfg {
     static constexpr int CHUNKS = N / 2 / THREADS;  // 16-byte copies per thread
     static constexpr int TABLE_WORDS = CBLOCKS + 32;
     // two (13, 4) workgroups share a CU; the others hold the CU alone
-    static constexpr int LDS_BUDGET = (TB == 13 && WAVES == 4) ? 160 * 1024 / 2 : 160 * 1024;
+    static constexpr int LDS_BUDGET = (TB == 13 && WAVES == 4) || TB == 12 ? 160 * 1024 / 2 : 160 * 1024;
     static constexpr int OPERAND_WORDS = 64 * LW;
     static constexpr int FIT = (LDS_BUDGET - N * 8 - 8 * WAVES) / (4 * (OPERAND_WORDS + TABLE_WORDS));
     static constexpr int MAX_SUB = FIT < kMaxTileSubBlocks ? FIT : kMaxTileSubBlocks;
@@ -1227,8 +1228,16 @@ __global__ void __launch_bounds__(64 * WAVES) k_tile_pass(float *__restrict__ ps
                                                           const TileNorm norm)
 {
     __shared__ TileShared<TB, WAVES, lane_words(PREC)> sh;
-    tile_loop<TB, WAVES, PREC, SCALE, WHOLE>(sh, blockIdx.y ? psi2 : psi, A, args, blockIdx.x, args.n_tiles, gridDim.x,
-                                      norm);
+    // Consecutive workgroups go to different XCDs.  The 2^g tiles that share
+    // 128-byte lines (tiles of short runs: g positions below 4 lie outside
+    // the tile) go to one, or each of its lines would be read by 2^g L2s (three
+    // blocks on eleven high positions, 2^12 tiles of 16-byte runs at 20 qubits:
+    // 19.5 to 11.7 us).
+    uint32_t g = 0, T = blockIdx.x;
+    if constexpr (TB < kMaxTileBits)
+        for (int e = 0; e < 3 && e < args.n_ext; ++e) g += args.ext_pos[e] < 4;
+    if (g && !(gridDim.x & ((8u << g) - 1))) T = (((T >> 3 >> g) * 8 + (T & 7u)) << g) | ((T >> 3) & ((1u << g) - 1));
+    tile_loop<TB, WAVES, PREC, SCALE, WHOLE>(sh, blockIdx.y ? psi2 : psi, A, args, T, args.n_tiles, gridDim.x, norm);
 }
 
 // Passes of many states in one grid: workgroup i takes tiles [t0, t1) of
@@ -1258,7 +1267,7 @@ hipError_t tile_launch(const TileArgs &a, const void *d_a, int prec, float *psi,
     TileNorm plain;  // the variants without the norm take only the basis start
     plain.basis = norm.basis;
     if (prec == kPrecF64) {
-        if constexpr (TB == kF64TileBits && WAVES == kF64TileWaves)
+        if constexpr ((TB == kF64TileBits && WAVES == kF64TileWaves) || (TB == 13 && WAVES == 8) || TB == 12)
             hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF64, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
         else
             return hipErrorInvalidValue;
@@ -1305,14 +1314,15 @@ template <int LW>
 static int max_blocks_of(int tile_bits, int waves)
 {
     if (tile_bits == 14) return waves == 16 ? TileCfg<14, 16, LW>::MAX_SUB : TileCfg<14, 8, LW>::MAX_SUB;
+    if (tile_bits == 12) return TileCfg<12, 4, LW>::MAX_SUB;
     return waves == 4 ? TileCfg<13, 4, LW>::MAX_SUB : TileCfg<13, 8, LW>::MAX_SUB;
 }
 
 int tile_max_blocks(int tile_bits, int waves, int prec)
 {
-    if (!tile_shape_supported(tile_bits, waves)) return 0;
+    if (!tile_shape_supported(tile_bits, waves) && !(tile_bits == 12 && waves == 4)) return 0;
     // BF16X3's limit is that of split BF16, though its operands are smaller
-    if (prec == kTileOperandF64) return max_blocks_of<16>(kF64TileBits, kF64TileWaves);
+    if (prec == kTileOperandF64) return max_blocks_of<16>(kF64TileBits, kF64TileWaves);  // the fewest of its shapes
     return prec == kTileOperandBF16 || prec == kTileOperandBF16X3 ? max_blocks_of<24>(tile_bits, waves)
                                                                    : max_blocks_of<16>(tile_bits, waves);
 }
@@ -1378,7 +1388,7 @@ hipError_t make_tile_args(int n_sub, const int (*sub_pos)[4], int n, int tile_bi
                           TileArgs *out)
 {
     const int kTileBits = tile_bits;
-    if ((tile_bits != 13 && tile_bits != 14) || n_sub < 1 || n_sub > kMaxTileSubBlocks || n < kTileBits)
+    if (tile_bits < 12 || tile_bits > kMaxTileBits || n_sub < 1 || n_sub > kMaxTileSubBlocks || n < kTileBits)
         return hipErrorInvalidValue;
     TileArgs &a = *out;
     std::memset(&a, 0, sizeof a);
@@ -1430,22 +1440,27 @@ hipError_t launch_tile_pass(int n_sub, const int (*sub_pos)[4], const void *d_a,
     if (prec == kTileOperandF64) {
         // virtual position 0 is re / im: every position moves up by one
         if (n_sub < 1 || n_sub > tile_max_blocks(kF64TileBits, kF64TileWaves, prec)) return hipErrorInvalidValue;
+        if (tile_bits != kF64TileBits && tile_bits != 13 && tile_bits != 12) return hipErrorInvalidValue;
         int pos[kMaxTileSubBlocks][4];
         for (int s = 0; s < n_sub; ++s)
             for (int i = 0; i < 4; ++i) pos[s][i] = sub_pos[s][i] + 1;
         TileArgs a;
-        if (hipError_t e = make_tile_args(n_sub, pos, n + 1, kF64TileBits, kF64TileWaves, prec, &a)) return e;
+        const int w = tile_bits == 12 ? 4 : 8;
+        if (hipError_t e = make_tile_args(n_sub, pos, n + 1, tile_bits, w, prec, &a)) return e;
         if (a.ubit[0] != 0) return hipErrorInvalidValue;  // a union of 14 positions leaves no place for it
         TileNorm nv = norm;
         if (nv.basis >= 0) nv.basis <<= 1;
-        return tile_launch<kF64TileBits, kF64TileWaves>(a, d_a, prec, static_cast<float *>(psi), static_cast<float *>(psi2),
-                                                        st, grid_cap, nv, grid_out);
+        float *p = static_cast<float *>(psi), *p2 = static_cast<float *>(psi2);
+        if (tile_bits == 12) return tile_launch<12, 4>(a, d_a, prec, p, p2, st, grid_cap, nv, grid_out);
+        if (tile_bits == 13) return tile_launch<13, 8>(a, d_a, prec, p, p2, st, grid_cap, nv, grid_out);
+        return tile_launch<kF64TileBits, kF64TileWaves>(a, d_a, prec, p, p2, st, grid_cap, nv, grid_out);
     }
-    if (!tile_shape_supported(tile_bits, waves)) return hipErrorInvalidValue;
+    if (!tile_shape_supported(tile_bits, waves) && !(tile_bits == 12 && waves == 4)) return hipErrorInvalidValue;
     if (n_sub < 1 || n_sub > tile_max_blocks(tile_bits, waves, prec)) return hipErrorInvalidValue;
     TileArgs a;
     if (hipError_t e = make_tile_args(n_sub, sub_pos, n, tile_bits, waves, prec, &a)) return e;
     float *p = static_cast<float *>(psi), *p2 = static_cast<float *>(psi2);
+    if (tile_bits == 12) return tile_launch<12, 4>(a, d_a, prec, p, p2, st, grid_cap, norm, grid_out);
     if (tile_bits == 14)
         return waves == 16 ? tile_launch<14, 16>(a, d_a, prec, p, p2, st, grid_cap, norm, grid_out)
                            : tile_launch<14, 8>(a, d_a, prec, p, p2, st, grid_cap, norm, grid_out);
