@@ -37,6 +37,7 @@ namespace {
 
 constexpr int kSmallMaxN = 13;
 constexpr int kThreads = 256;
+constexpr int kSmallThreads = 512;
 constexpr int kZ0ChunkBits = 16;  // amplitudes per <Z_0> partial sum (2^16)
 
 struct BBlock {
@@ -128,14 +129,15 @@ __device__ __forceinline__ void apply_group_k(float2 *st, const BBlock &b, const
     }
 }
 
+template <int THREADS>
 __device__ double block_sum(double v)
 {
-    __shared__ double sh[kThreads];
+    __shared__ double sh[THREADS];
     const int t = threadIdx.x;
     __syncthreads();
     sh[t] = v;
     __syncthreads();
-    for (int s = kThreads / 2; s > 0; s >>= 1) {
+    for (int s = THREADS / 2; s > 0; s >>= 1) {
         if (t < s) sh[t] += sh[t + s];
         __syncthreads();
     }
@@ -144,8 +146,11 @@ __device__ double block_sum(double v)
     return r;
 }
 
-// One persistent workgroup per slot; trajectories taken in turn.
-__global__ void __launch_bounds__(kThreads) k_batch_small(const BSmall *__restrict__ small, int n_small,
+// One persistent workgroup per slot; trajectories taken in turn.  A workgroup's
+// time is its blocks' one after another, so it has as many waves as the
+// registers of a six-qubit group allow (23 trajectories of 10 to 13 qubits:
+// 759 us with 256 threads, 600 with 512).
+__global__ void __launch_bounds__(kSmallThreads) k_batch_small(const BSmall *__restrict__ small, int n_small,
                                                           const BBlock *__restrict__ blocks,
                                                           const float2 *__restrict__ mats, float2 *__restrict__ buf,
                                                           double *__restrict__ z0)
@@ -154,56 +159,52 @@ __global__ void __launch_bounds__(kThreads) k_batch_small(const BSmall *__restri
     for (int s = blockIdx.x; s < n_small; s += gridDim.x) {
         const BSmall tr = small[s];
         const uint32_t N = 1u << tr.n;
-        for (uint32_t i = threadIdx.x; i < N; i += kThreads) lds[i] = make_float2(i == 0 ? 1.f : 0.f, 0.f);
+        for (uint32_t i = threadIdx.x; i < N; i += kSmallThreads) lds[i] = make_float2(i == 0 ? 1.f : 0.f, 0.f);
         __syncthreads();
         for (int bi = 0; bi < tr.n_blocks; ++bi) {
             const BBlock b = blocks[tr.first_block + bi];
             const uint32_t groups = N >> b.k;
-            for (uint32_t g = threadIdx.x; g < groups; g += kThreads) apply_group_k(lds, b, mats + b.mat_off, g);
+            for (uint32_t g = threadIdx.x; g < groups; g += kSmallThreads) apply_group_k(lds, b, mats + b.mat_off, g);
             __syncthreads();
         }
         double acc = 0.0;
-        for (uint32_t i = threadIdx.x; i < N; i += kThreads) {
+        for (uint32_t i = threadIdx.x; i < N; i += kSmallThreads) {
             const float2 v = lds[i];
             const double p = double(v.x) * v.x + double(v.y) * v.y;
             acc += (i & 1) ? -p : p;
         }
-        const double z = block_sum(acc);
+        const double z = block_sum<kSmallThreads>(acc);
         if (threadIdx.x == 0) z0[tr.out] = z;
         float2 *dst = buf + tr.state_off;
-        for (uint32_t i = threadIdx.x; i < N; i += kThreads) dst[i] = lds[i];
+        for (uint32_t i = threadIdx.x; i < N; i += kSmallThreads) dst[i] = lds[i];
         __syncthreads();
     }
 }
 
-__global__ void k_batch_zero(float2 *__restrict__ buf, uint64_t begin, uint64_t end)
-{
-    const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-    for (uint64_t i = begin + uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < end; i += stride)
-        buf[i] = make_float2(0.f, 0.f);
-}
-
-__global__ void k_batch_one(const BLarge *__restrict__ large, int n_large, float2 *__restrict__ buf)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n_large) buf[large[t].state_off] = make_float2(1.f, 0.f);
-}
-
 // <Z_0> partial sums: one workgroup per chunk of one state (chunks start at
 // even indices, so the parity of the local index is that of the state index).
+// Bound by HBM: four 16-byte loads in flight a thread (713 MiB of states: 197 to 170 us
+// against 8-byte loads one after another).
 __global__ void __launch_bounds__(kThreads) k_batch_z0_part(const BZUnit *__restrict__ units,
                                                             const float2 *__restrict__ buf,
                                                             double *__restrict__ partial)
 {
     const BZUnit u = units[blockIdx.x];
-    const float2 *st = buf + u.off;
-    double acc = 0.0;
-    for (uint32_t i = threadIdx.x; i < u.count; i += kThreads) {
-        const float2 v = st[i];
-        const double p = double(v.x) * v.x + double(v.y) * v.y;
-        acc += (i & 1) ? -p : p;
+    const float4 *st = reinterpret_cast<const float4 *>(buf + u.off);  // states start 256-byte aligned
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    const uint32_t pairs = u.count / 2;  // states of >= 14 qubits: even
+    for (uint32_t i = threadIdx.x; i < pairs; i += 4 * kThreads) {
+        float4 v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (i + j * kThreads < pairs) v[j] = st[i + j * kThreads];
+            else v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            acc[j] += (double(v[j].x) * v[j].x + double(v[j].y) * v[j].y) -
+                      (double(v[j].z) * v[j].z + double(v[j].w) * v[j].w);
     }
-    const double z = block_sum(acc);
+    const double z = block_sum<kThreads>((acc[0] + acc[1]) + (acc[2] + acc[3]));
     if (threadIdx.x == 0) partial[blockIdx.x] = z;
 }
 
@@ -237,7 +238,7 @@ struct sv_batch {
     DevBuf d_blocks, d_mats, d_small, d_large, d_z0;
     DevBuf d_passes, d_units, d_pool, d_zunits, d_partial;
     int n_small = 0, n_large = 0, small_max_n = 0, n_zunits = 0;
-    uint64_t large_begin = 0, large_end = 0;
+    std::vector<std::pair<uint64_t, int>> unchanged;  // (offset, n) of large states without a gate: filled instead
     std::vector<std::pair<size_t, int>> steps;  // per layer: (offset into units, count)
     PinBuf h_z0;
     hipGraph_t graph = nullptr;
@@ -345,6 +346,7 @@ int build_schedule(sv_batch *b, const sv_batch_desc *d, int k)
                 passes.push_back(tp);
             }
         }
+        if (!mine.empty()) passes[size_t(mine.back())].last = 1;
         BLarge L;
         L.state_off = b->state_off[t];
         L.n = n;
@@ -357,7 +359,8 @@ int build_schedule(sv_batch *b, const sv_batch_desc *d, int k)
         large_passes.push_back(mine);
     }
     // layered launches: layer s holds pass s of every large trajectory, as
-    // tile ranges (a quarter of the tiles of the largest states per unit)
+    // tile ranges (a quarter of the tiles of the largest states per unit;
+    // longer ranges, longest first, made no difference)
     std::vector<dev::TileUnit> units;
     b->steps.clear();
     size_t layers = 0;
@@ -378,15 +381,10 @@ int build_schedule(sv_batch *b, const sv_batch_desc *d, int k)
     b->n_zunits = int(zunits.size());
     b->small_max_n = 0;
     for (auto &s : small) b->small_max_n = std::max(b->small_max_n, s.n);
-    // large states are laid out after the small ones, contiguously
-    b->large_begin = b->large_end = 0;
-    if (!large.empty()) {
-        b->large_begin = large.front().state_off;
-        for (auto &l : large) {
-            b->large_begin = std::min(b->large_begin, l.state_off);
-            b->large_end = std::max(b->large_end, l.state_off + (uint64_t(1) << l.n));
-        }
-    }
+    // the first passes start their states from |0..0> themselves
+    b->unchanged.clear();
+    for (size_t t = 0; t < large.size(); ++t)
+        if (large_passes[t].empty()) b->unchanged.push_back({large[t].state_off, large[t].n});
     auto upload = [](DevBuf &dst, const void *src, size_t bytes) -> hipError_t {
         hipError_t e = dst.ensure(std::max(bytes, size_t(256)));
         if (e == hipSuccess && bytes) e = hipMemcpy(dst.p, src, bytes, hipMemcpyHostToDevice);
@@ -425,26 +423,22 @@ int enqueue_run(sv_batch *b, hipStream_t main, hipStream_t side)
         LaunchTimer t(stat_class(FAM_BATCH, 1), side);
         const unsigned grid = unsigned(std::min(b->n_small, 2048));
         const size_t lds = size_t(sizeof(float2)) << b->small_max_n;
-        hipLaunchKernelGGL(k_batch_small, dim3(grid), dim3(kThreads), lds, side,
+        hipLaunchKernelGGL(k_batch_small, dim3(grid), dim3(kSmallThreads), lds, side,
                            static_cast<const BSmall *>(b->d_small.p), b->n_small, blocks, mats, b->buf, z0);
         SV_HIP(hipGetLastError());
     }
     if (b->n_large) {
-        {
+        for (const auto &u : b->unchanged) {
             LaunchTimer t(stat_class(FAM_BATCH, 2), main);
-            const uint64_t cnt = b->large_end - b->large_begin;
-            const unsigned grid = unsigned(std::min<uint64_t>((cnt + 255) / 256, 16384));
-            hipLaunchKernelGGL(k_batch_zero, dim3(grid), dim3(256), 0, main, b->buf, b->large_begin, b->large_end);
-            hipLaunchKernelGGL(k_batch_one, dim3((b->n_large + 255) / 256), dim3(256), 0, main,
-                               static_cast<const BLarge *>(b->d_large.p), b->n_large, b->buf);
-            SV_HIP(hipGetLastError());
+            SV_HIP(dev::launch_fill_basis(SV_C64, b->buf + u.first, u.second, 0, main));
         }
         const auto *units = static_cast<const dev::TileUnit *>(b->d_units.p);
         const auto *passes = static_cast<const dev::TilePass *>(b->d_passes.p);
         const auto *pool = static_cast<const uint32_t *>(b->d_pool.p);
         for (const auto &st : b->steps) {
             LaunchTimer t(stat_class(FAM_BATCH, 3), main);
-            SV_HIP(dev::launch_tile_batch(units + st.first, st.second, passes, pool, b->buf, main, b->tile_prec));
+            SV_HIP(dev::launch_tile_batch(units + st.first, st.second, passes, pool, b->buf, main, b->tile_prec,
+                                          &st == b->steps.data()));
         }
         LaunchTimer t(stat_class(FAM_BATCH, 4), main);
         double *partial = static_cast<double *>(b->d_partial.p);

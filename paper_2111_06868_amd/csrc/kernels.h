@@ -124,6 +124,8 @@ constexpr int kBatchTileWaves = 16;
 struct TilePass {
     uint64_t state_off;  // complex elements from the start of the batch buffer
     uint64_t op_off;     // 32-bit words into the operand pool
+    int32_t last;        // the state's last pass
+    int32_t pad;
     TileArgs args;
 };
 struct TileUnit {
@@ -131,8 +133,9 @@ struct TileUnit {
     int32_t pad;
     uint64_t t0, t1;     // tiles [t0, t1)
 };
+// start: the passes read nothing, their states start from |0..0>.
 hipError_t launch_tile_batch(const TileUnit *units, int n_units, const TilePass *passes, const uint32_t *pool,
-                             void *buf, hipStream_t st, int prec);
+                             void *buf, hipStream_t st, int prec, bool start);
 bool tile_supported(int n, int union_bits);
 bool tile_shape_supported(int tile_bits, int waves);
 int tile_wgs_per_cu(int tile_bits, int waves);
