@@ -228,6 +228,56 @@ __global__ void __launch_bounds__(256) k_apply_generic(T *__restrict__ psi0, con
     }
 }
 
+// Blocks of three and more qubits, one output a thread: a workgroup stages the
+// matrix (columns first) and its groups' amplitudes in LDS.  One thread for the
+// 2^K outputs of a group, as above, leaves a state of few groups to one wave
+// that walks through the whole matrix, and spills from K = 6 on; same order of
+// the same multiply-adds.  FP64, before and after (with 5 us of events): K = 4
+// 15 to 6 us at 9 qubits, K = 5 69 to 6 at 10, 86 to 23 at 20 and 257 to 240 at
+// 24, K = 6 430 to 13, 369 to 65 and 1359 to 877.  The LDS reads, two of 16 bytes
+// for four multiply-adds, bound it at the large end, where K = 4 stays with its
+// groups in registers (22 qubits: 45 to 40; 24: 121 against 134).
+template <typename T, int K>
+__global__ void __launch_bounds__(256) k_apply_rows(T *__restrict__ psi0, const T *__restrict__ m, const GenArgs<K> a)
+{
+    constexpr int D = 1 << K;
+    extern __shared__ __align__(16) char rows_lds[];
+    T *M = reinterpret_cast<T *>(rows_lds);  // [column][row] (re, im)
+    T *X = M + 2 * D * D;                    // the amplitudes of this workgroup's groups
+    T *__restrict__ psi = blockIdx.y ? static_cast<T *>(a.psi2) : psi0;
+    const int t = threadIdx.x, row = t & (D - 1);
+    for (int e = t; e < D * D; e += 256) {
+        const int r = e / D, c = e % D;
+        M[2 * (c * D + r)] = m[2 * e];
+        M[2 * (c * D + r) + 1] = m[2 * e + 1];
+    }
+    const uint64_t g = (uint64_t(blockIdx.x) * 256 + t) >> K;
+    const bool in = g < a.n_groups;
+    uint64_t o = g;
+#pragma unroll
+    for (int j = 0; j < K; ++j) o = insert_zero(o, a.pos[j]);
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+        if ((row >> j) & 1) o += uint64_t(1) << a.pos[j];
+    X[2 * t] = in ? psi[2 * o] : T(0);
+    X[2 * t + 1] = in ? psi[2 * o + 1] : T(0);
+    __syncthreads();
+    T sr = 0, si = 0;
+#pragma unroll 8
+    for (int c = 0; c < D; ++c) {
+        const T ar = M[2 * (c * D + row)], ai = M[2 * (c * D + row) + 1];
+        const T vr = X[2 * ((t & ~(D - 1)) | c)], vi = X[2 * ((t & ~(D - 1)) | c) + 1];
+        sr = fma(ar, vr, sr);
+        sr = fma(-ai, vi, sr);
+        si = fma(ar, vi, si);
+        si = fma(ai, vr, si);
+    }
+    if (in) {
+        psi[2 * o] = sr;
+        psi[2 * o + 1] = si;
+    }
+}
+
 template <typename T, int K>
 hipError_t generic_launch_t(const int *sorted_q, const T *d_m, T *psi, T *psi2, int n, hipStream_t st)
 {
@@ -235,9 +285,19 @@ hipError_t generic_launch_t(const int *sorted_q, const T *d_m, T *psi, T *psi2, 
     a.psi2 = psi2;
     for (int j = 0; j < K; ++j) a.pos[j] = sorted_q[j];
     a.n_groups = uint64_t(1) << (n - K);
-    uint64_t blocks = (a.n_groups + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL((k_apply_generic<T, K>), dim3(unsigned(blocks), psi2 ? 2 : 1), dim3(256), 0, st, psi, d_m, a);
+    if constexpr (K >= 3) {
+        if (K != 4 || n <= 22) {
+            const unsigned grid = unsigned(((uint64_t(1) << n) + 255) / 256);  // n <= SV_MAX_QUBITS_C64: fits
+            hipLaunchKernelGGL((k_apply_rows<T, K>), dim3(grid, psi2 ? 2 : 1), dim3(256),
+                               sizeof(T) * 2 * ((1 << (2 * K)) + 256), st, psi, d_m, a);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (K <= 4 && K != 3) {
+        uint64_t blocks = (a.n_groups + 255) / 256;
+        if (blocks > 65536) blocks = 65536;
+        hipLaunchKernelGGL((k_apply_generic<T, K>), dim3(unsigned(blocks), psi2 ? 2 : 1), dim3(256), 0, st, psi, d_m, a);
+    }
     return hipGetLastError();
 }
 
