@@ -168,13 +168,13 @@ int blocks_to_launches(const std::vector<Block> &blocks, const sv_state *s, int 
 // are (group_gate_passes).
 bool takes_tiles(int rule, int precision, int n)
 {
-    return (rule == SV_RULE_PAPER || rule == SV_RULE_ENHANCED) && n >= dev::kMinTileQubits &&
+    return (rule == SV_RULE_PAPER || rule == SV_RULE_ENHANCED) && n >= tile_min_qubits(precision) &&
            (precision == SV_PREC_FP32 || precision == SV_PREC_SPLIT_BF16X3 || precision == SV_PREC_FP64);
 }
 bool tiles_are_cheaper(const std::vector<Block> &blocks, const std::vector<Block> &tiled, int n, int precision)
 {
     const CostTable cost = lookup_costs(n, precision, nullptr);
-    return tiled_plan_cost(tiled, n, cost) < plan_cost(blocks, cost) - 1e-12;
+    return tiled_plan_cost(tiled, n, precision, cost) < plan_cost(blocks, cost) - 1e-12;
 }
 // The tile passes of the gates of a plan (positions and members, no matrices),
 // or none where one of its gates or all of its blocks rule them out.
@@ -253,7 +253,7 @@ int choose_plan_uncached(const sv_gate *g, int G, int n, int dtype, int precisio
     std::vector<int> rules;
     if (rule == SV_RULE_AUTO) {
         rules.push_back(SV_RULE_ENHANCED);
-        if (n >= dev::kMinTileQubits) rules.push_back(SV_RULE_TILED);
+        if (n >= tile_min_qubits(precision)) rules.push_back(SV_RULE_TILED);
     } else {
         rules.push_back(rule == SV_RULE_NONE ? SV_RULE_PAPER : rule);
     }
@@ -265,7 +265,7 @@ int choose_plan_uncached(const sv_gate *g, int G, int n, int dtype, int precisio
             if (!found && k == SV_MAX_K) break;  // untuned: stay below the MFMA-bound size
             std::vector<Block> blocks;
             if (int rc = fuse_gates(g, G, n, k, r, cost, blocks, false, precision)) return rc;
-            const double c = r == SV_RULE_TILED ? tiled_plan_cost(blocks, n, cost) : plan_cost(blocks, cost);
+            const double c = r == SV_RULE_TILED ? tiled_plan_cost(blocks, n, precision, cost) : plan_cost(blocks, cost);
             if (c < best - 1e-12) {
                 best = c;
                 best_rule = r;
@@ -1048,7 +1048,7 @@ class KrausSampler {
         sv_run_opts o;
         o.max_k = 4;
         o.precision = s_->dtype == SV_C64 ? SV_PREC_FP32 : SV_PREC_FP64;
-        o.rule = s_->n >= dev::kMinTileQubits ? SV_RULE_TILED : SV_RULE_ENHANCED;
+        o.rule = s_->n >= tile_min_qubits(o.precision) ? SV_RULE_TILED : SV_RULE_ENHANCED;
         o.use_graph = 0;
         return run_circuit_impl(s_, g.data(), int(g.size()), &o);
     }
@@ -1538,13 +1538,13 @@ int dagger_launches(const sv_gate *g, int hi, int lo, const sv_state *s, int pre
             }
         }
         choice = kbest;
-        if (kmax <= 4 && dev::tile_supported(s->n, 4)) {
+        if (kmax <= 4 && s->n >= tile_min_qubits(prec)) {
             if (best > 1e299) {
                 if (int rc = fuse_gates(dg.data(), cnt, s->n, kbest, SV_RULE_ENHANCED, cost, blocks, false)) return rc;
                 best = plan_cost(blocks, cost);
             }
             if (int rc = fuse_gates(dg.data(), cnt, s->n, 4, SV_RULE_TILED, cost, blocks, false, prec)) return rc;
-            if (tiled_plan_cost(blocks, s->n, cost) < best - 1e-12) choice = 0;
+            if (tiled_plan_cost(blocks, s->n, prec, cost) < best - 1e-12) choice = 0;
         }
         std::lock_guard<std::mutex> lk(memo_mu);
         if (memo.size() > 65536) memo.clear();

@@ -324,7 +324,7 @@ int build_schedule(sv_batch *b, const sv_batch_desc *d, int k)
         std::vector<Block> fb;
         if (int rc = fuse_gates(g, G, n, std::min(kk, 4), SV_RULE_TILED, cost, fb, true, d->precision)) return rc;
         std::vector<int> mine;
-        for (const auto &grp : tile_groups(fb, n)) {
+        for (const auto &grp : tile_groups(fb, n, d->precision)) {
             for (size_t c = 0; c < grp.size(); c += size_t(max_sub)) {
                 const int cnt = int(std::min(grp.size() - c, size_t(max_sub)));
                 std::vector<const Block *> bp;

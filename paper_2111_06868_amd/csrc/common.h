@@ -113,9 +113,15 @@ double plan_cost(const std::vector<Block> &blocks, const CostTable &cost);
 // Tile grouping (see group_tile_passes): groups of block indices, in
 // application order (consecutive blocks of one tile pass); a group of one is
 // applied on its own.
-std::vector<std::vector<size_t>> tile_groups(const std::vector<Block> &blocks, int n);
+std::vector<std::vector<size_t>> tile_groups(const std::vector<Block> &blocks, int n, int precision);
 // Cost of the tiled plan of `blocks` with the table's tile and block costs.
-double tiled_plan_cost(const std::vector<Block> &blocks, int n, const CostTable &cost);
+double tiled_plan_cost(const std::vector<Block> &blocks, int n, int precision, const CostTable &cost);
+// The smallest state that tile passes in `precision` take: 10 qubits in FP32
+// and FP64, 14 in the 16-bit splits, whose roundings would change.
+inline int tile_min_qubits(int precision)
+{
+    return precision == SV_PREC_FP32 || precision == SV_PREC_SPLIT_BF16X3 || precision == SV_PREC_FP64 ? 10 : 14;
+}
 
 // Canonical matrix of a block from its member gates.
 void block_matrix(const sv_gate *g, Block &b);

@@ -522,7 +522,10 @@ int fuse_gates(const sv_gate *g, int G, int n, int max_k, int rule, const CostTa
         std::vector<int> pg;
         int pass = 0;
         const int tile_bits = tile_pass_bits(precision), limit = tile_union_limit();
-        auto pass_fits = [n, tile_bits, limit](uint64_t u) { return tile_union_fits(u, n, tile_bits, limit); };
+        const bool one_tile = n < tile_bits && n >= tile_min_qubits(precision);  // whatever the union
+        auto pass_fits = [n, tile_bits, limit, one_tile](uint64_t u) {
+            return one_tile || tile_union_fits(u, n, tile_bits, limit);
+        };
         while (passes.next(pass_fits, pg)) {
             const auto sub = frontier_groups(g, pg, max_k);
             const size_t e = std::min(sub.size(), cap);
@@ -619,14 +622,13 @@ int fuse_gates(const sv_gate *g, int G, int n, int max_k, int rule, const CostTa
 }
 
 
-std::vector<std::vector<size_t>> tile_groups(const std::vector<Block> &blocks, int n)
+std::vector<std::vector<size_t>> tile_groups(const std::vector<Block> &blocks, int n, int precision)
 {
-    // consecutive blocks of one tile pass; states below 14 qubits (one tile
-    // would hold the whole state several times over) apply every block alone
-    constexpr int kMinQubits = 14;
+    // consecutive blocks of one tile pass; smaller states apply every block alone
+    const int min_qubits = tile_min_qubits(precision);
     std::vector<std::vector<size_t>> out;
     for (size_t i = 0; i < blocks.size(); ++i) {
-        if (n >= kMinQubits && blocks[i].pass >= 0 && !out.empty() && blocks[out.back().back()].pass == blocks[i].pass)
+        if (n >= min_qubits && blocks[i].pass >= 0 && !out.empty() && blocks[out.back().back()].pass == blocks[i].pass)
             out.back().push_back(i);
         else
             out.push_back({i});
@@ -634,10 +636,10 @@ std::vector<std::vector<size_t>> tile_groups(const std::vector<Block> &blocks, i
     return out;
 }
 
-double tiled_plan_cost(const std::vector<Block> &blocks, int n, const CostTable &cost)
+double tiled_plan_cost(const std::vector<Block> &blocks, int n, int precision, const CostTable &cost)
 {
     double c = 0;
-    for (const auto &grp : tile_groups(blocks, n)) {
+    for (const auto &grp : tile_groups(blocks, n, precision)) {
         if (grp.size() > 1) {
             c += cost.tile[grp.size()];
             continue;

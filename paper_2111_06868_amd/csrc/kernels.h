@@ -68,11 +68,13 @@ hipError_t launch_mfma_split(int k, bool fp16, const int *sorted_q, const uint16
 // tile_max_blocks() 4-qubit blocks whose positions have a union of at most
 // tile_bits positions, applied in one HBM pass over tiles of
 // 2^tile_bits amplitudes held by workgroups of `waves` waves; shapes
-// (14, 8), (14, 16), (13, 4), (13, 8) and, for small states, (12, 4).  sub_pos
-// rows ascending.  d_a = the
+// (14, 8), (14, 16), (13, 4), (13, 8) and, for small states, (12, 4), (11, 2)
+// and (10, 1), the last two in FP32 and FP64.  sub_pos rows ascending.  d_a = the
 // blocks' operands (pack_tile_operand), back to back.  Needs n >= tile_bits.
 constexpr int kMaxTileSubBlocks = kTilePassMaxBlocks;
 constexpr int kMinTileQubits = 14;
+// From here on FP32 and FP64 passes hold a state of one tile (tile_min_qubits).
+constexpr int kMinTileQubitsSmall = 10;
 constexpr int kMaxTileBits = 14;
 constexpr int kMaxTileUnion = kMaxTileBits;
 // Layout and blocks of one tile pass over one state.

@@ -443,7 +443,7 @@ void group_tile_passes(const std::vector<Block> &blocks, int n, int precision, s
     out.clear();
     const CostTable cost = lookup_costs(n, precision, nullptr);
     const bool fp64 = precision == SV_PREC_FP64;
-    for (const auto &grp : tile_groups(blocks, n))
+    for (const auto &grp : tile_groups(blocks, n, precision))
         for (size_t at = 0; at < grp.size();) {
             // a pass planned for another arithmetic may cover more positions
             // than an FP64 tile holds: as many of its blocks as fit
@@ -457,10 +457,12 @@ void group_tile_passes(const std::vector<Block> &blocks, int n, int precision, s
                 }
             }
             // a block alone: its own dense launch, or a tile pass of one block
-            // where that is priced lower
+            // where that is priced lower (below 14 qubits, where launches are
+            // short, only for FP64's four-qubit blocks)
+            const bool one = dev::tile_supported(n, 4) || (fp64 && n >= dev::kMinTileQubitsSmall && blocks[grp[at]].k == 4);
             const Block &b0 = blocks[grp[at]];
             Launch L;
-            if (end - at == 1 && !(b0.k <= 4 && dev::tile_supported(n, 4) && cost.tile[1] < cost.ms[b0.k])) {
+            if (end - at == 1 && !(b0.k <= 4 && one && cost.tile[1] < cost.ms[b0.k])) {
                 L.k = b0.k;
                 std::copy(b0.q, b0.q + SV_MAX_K, L.q);
                 L.path = choose_path(fp64 ? SV_C128 : SV_C64, precision, b0.k, b0.q, n);
@@ -502,7 +504,7 @@ int group_dense_passes(std::vector<Launch> &launches, int n, int precision)
         }
         std::vector<Block> blocks;
         if (int rc = fuse_gates(g.data(), int(g.size()), n, 4, SV_RULE_TILED, cost, blocks, true, precision)) return rc;
-        if (tiled_plan_cost(blocks, n, cost) < cost.ms[4] * double(end - at) - 1e-12) {
+        if (tiled_plan_cost(blocks, n, precision, cost) < cost.ms[4] * double(end - at) - 1e-12) {
             group_tile_passes(blocks, n, precision, passes);
             for (auto &L : passes) out.push_back(std::move(L));
         } else {
@@ -536,7 +538,7 @@ int group_gate_passes(std::vector<Launch> &launches, int n, int dtype)
         std::vector<Block> blocks;
         if (int rc = fuse_gates(g.data(), int(g.size()), n, 4, SV_RULE_TILED, default_costs(), blocks, false, precision)) return rc;
         const size_t cap = size_t(dev::tile_max_blocks(14, 8, dev::kTileOperandF32));
-        for (const auto &grp : tile_groups(blocks, n))
+        for (const auto &grp : tile_groups(blocks, n, precision))
             for (size_t c = 0; c < grp.size(); c += cap) {
                 const size_t stop = std::min(grp.size(), c + cap);
                 if (stop - c == 1 && blocks[grp[c]].members.size() == 1) {  // a gate alone
@@ -577,7 +579,10 @@ int group_gate_passes(std::vector<Launch> &launches, int n, int dtype)
 // takes the next one.  Seven blocks, (14, 16) against the small shape: FP32 at 14
 // qubits 27.8 to 19.0 us, at 20 30.5 to 20.9, at 21 (2^13) 32.7 to 24.5; FP16 at 20 26.4
 // to 18.9; FP64 (virtual position 0, 2^14 units of 8 bytes) at 20 45.9 to 30.3; one
-// size further on the small tiles lose (FP32, 22 qubits: 35.9 to 39.7).  A shape
+// size further on the small tiles lose (FP32, 22 qubits: 35.9 to 39.7).  States of
+// 10 and 11 qubits are one tile of 2^10 or 2^11, where a launch for every block
+// costs more (eight cycles on a ladder, dense blocks against tiles: FP32 at 10
+// qubits 124 to 76 us, at 12 152 to 79, FP64 375 to 67 and 425 to 87).  A shape
 // other than the default is kept: the caller or the tuner chose it.
 struct TileShape {
     int bits, waves;
@@ -586,13 +591,13 @@ static TileShape tile_shape_for(const Launch &L, int first, int m, int n, bool t
 {
     const Tuning &T = tuning();
     const bool f64 = L.path == PATH_TILE_FP64;
-    if (!f64 && (T.tile_bits != 14 || T.tile_waves != 16)) return {T.tile_bits, T.tile_waves};
+    if (!f64 && n >= dev::kMinTileQubits && (T.tile_bits != 14 || T.tile_waves != 16)) return {T.tile_bits, T.tile_waves};
     uint64_t u = 1;  // position 0 is in every tile
     for (int s = first; s < first + m; ++s)
         for (int j = 0; j < 4; ++j) u |= uint64_t(1) << (L.sub_pos[s][j] + (f64 ? 1 : 0));
     const int small = n + (f64 ? 1 : 0) + (two ? 1 : 0) - 8;  // 2^8 tiles
-    const int bits = std::max(std::max(small, 12), __builtin_popcountll(u));
-    if (bits == 12) return {12, 4};
+    const int bits = std::max(std::max(small, std::min(12, n + (f64 ? 1 : 0))), __builtin_popcountll(u));
+    if (bits <= 12) return {bits, 1 << (bits - 10)};
     if (bits == 13) return {13, 8};
     return f64 ? TileShape{dev::kF64TileBits, dev::kF64TileWaves} : TileShape{T.tile_bits, T.tile_waves};
 }

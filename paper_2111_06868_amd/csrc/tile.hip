@@ -104,8 +104,8 @@ __device__ __forceinline__ uint32_t frag_swz(uint32_t lane)
 // columns per 4-qubit block, in blocks of 32 split evenly over the waves.
 // Shapes: (14, 8) and (14, 16) one 128 KiB tile per CU, with 2 or 4 waves
 // per SIMD; (13, 4) two 64 KiB workgroups per CU, so one can copy while the
-// other computes; (13, 8).  (12, 4): small states (tile_shape_for), two
-// workgroups per CU.  MAX_SUB blocks' operands of LW words per lane
+// other computes; (13, 8).  (12, 4), (11, 2) and (10, 1): small states
+// (tile_shape_for), the last two as one tile.  MAX_SUB blocks' operands of LW words per lane
 // fit in the LDS left beside the tile.
 template <int TB, int WAVES, int LW = 24>
 struct TileCfg {
@@ -117,14 +117,14 @@ struct TileCfg {
     static constexpr int CHUNKS = N / 2 / THREADS;  // 16-byte copies per thread
     static constexpr int TABLE_WORDS = CBLOCKS + 32;
     // two (13, 4) workgroups share a CU; the others hold the CU alone
-    static constexpr int LDS_BUDGET = (TB == 13 && WAVES == 4) || TB == 12 ? 160 * 1024 / 2 : 160 * 1024;
+    static constexpr int LDS_BUDGET = (TB == 13 && WAVES == 4) || TB <= 12 ? 160 * 1024 / 2 : 160 * 1024;
     static constexpr int OPERAND_WORDS = 64 * LW;
     static constexpr int FIT = (LDS_BUDGET - N * 8 - 8 * WAVES) / (4 * (OPERAND_WORDS + TABLE_WORDS));
     static constexpr int MAX_SUB = FIT < kMaxTileSubBlocks ? FIT : kMaxTileSubBlocks;
     // X3 (LW = 16) keeps all three parts expanded where the launch's blocks leave room
     static constexpr int OP_AREA = LW == 16 ? (LDS_BUDGET - N * 8 - 8 * WAVES - 4 * MAX_SUB * TABLE_WORDS) / 16 * 4
                                             : MAX_SUB * OPERAND_WORDS;
-    static_assert(THREADS % 256 == 0 && THREADS <= 1024 && NB_PER_WAVE >= 1 && OP_AREA >= MAX_SUB * OPERAND_WORDS,
+    static_assert(THREADS <= 1024 && NB_PER_WAVE >= 1 && OP_AREA >= MAX_SUB * OPERAND_WORDS,
                   "tile shape");
 };
 
@@ -402,9 +402,9 @@ __device__ __forceinline__ void stage_blocks(TileShared<TB, WAVES, lane_words(PR
         }
         return x;
     };
-    // four loads in flight per thread: the operands come from HBM, and word
-    // by word their latency alone was 2 us of a launch
-    constexpr int DEPTH = 4;
+    // four loads in flight per thread (more where the threads are few): the
+    // operands come from HBM, and word by word their latency alone was 2 us of a launch
+    constexpr int DEPTH = C::THREADS >= 256 ? 4 : 16;
     for (int u0 = tid; u0 < units && !GATES; u0 += DEPTH * C::THREADS) {
         vu4 v[DEPTH];
 #pragma unroll
@@ -1277,21 +1277,23 @@ hipError_t tile_launch(const TileArgs &a, const void *d_a, int prec, float *psi,
     TileNorm plain;  // the variants without the norm take only the basis start
     plain.basis = norm.basis;
     if (prec == kPrecF64) {
-        if constexpr ((TB == kF64TileBits && WAVES == kF64TileWaves) || (TB == 13 && WAVES == 8) || TB == 12)
+        if constexpr ((TB == kF64TileBits && WAVES == kF64TileWaves) || (TB == 13 && WAVES == 8) || TB == 12 || TB == 11)
             hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF64, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
         else
             return hipErrorInvalidValue;
-    } else if (prec == kPrecBF16)
-        hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecBF16, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
-    else if (prec == kPrecF16 && norm.in && norm.in_scaled && norm.out_scaled)
-        hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF16, 3>), grid, block, 0, st, psi, A, a, psi2, norm);
-    else if (prec == kPrecF16 && norm.in)
-        hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF16, 1>), grid, block, 0, st, psi, A, a, psi2, norm);
-    else if (prec == kPrecF16 && norm.out)
-        hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF16, 2>), grid, block, 0, st, psi, A, a, psi2, norm);
-    else if (prec == kPrecF16)
-        hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF16, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
-    else if (x3_whole<TileCfg<TB, WAVES, lane_words(kPrecX3)>>(a.n_sub)) {
+    } else if (prec == kPrecBF16 || prec == kPrecF16) {
+        if constexpr (TB < 12) return hipErrorInvalidValue;
+        else if (prec == kPrecBF16)
+            hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecBF16, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
+        else if (norm.in && norm.in_scaled && norm.out_scaled)
+            hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF16, 3>), grid, block, 0, st, psi, A, a, psi2, norm);
+        else if (norm.in)
+            hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF16, 1>), grid, block, 0, st, psi, A, a, psi2, norm);
+        else if (norm.out)
+            hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF16, 2>), grid, block, 0, st, psi, A, a, psi2, norm);
+        else
+            hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecF16, 0>), grid, block, 0, st, psi, A, a, psi2, plain);
+    } else if (x3_whole<TileCfg<TB, WAVES, lane_words(kPrecX3)>>(a.n_sub)) {
         if (norm.basis >= 0)
             hipLaunchKernelGGL((k_tile_pass<TB, WAVES, kPrecX3, 4, 1>), grid, block, 0, st, psi, A, a, psi2, plain);
         else
@@ -1305,6 +1307,12 @@ hipError_t tile_launch(const TileArgs &a, const void *d_a, int prec, float *psi,
 }
 
 }  // namespace
+
+// The shapes of small states, (12, 4), (11, 2) and (10, 1).
+static bool small_shape(int tile_bits, int waves)
+{
+    return tile_bits >= kMinTileQubitsSmall && tile_bits <= 12 && waves == 1 << (tile_bits - 10);
+}
 
 bool tile_supported(int n, int union_bits) { return n >= kMinTileQubits && union_bits <= kMaxTileUnion; }
 
@@ -1325,12 +1333,14 @@ static int max_blocks_of(int tile_bits, int waves)
 {
     if (tile_bits == 14) return waves == 16 ? TileCfg<14, 16, LW>::MAX_SUB : TileCfg<14, 8, LW>::MAX_SUB;
     if (tile_bits == 12) return TileCfg<12, 4, LW>::MAX_SUB;
+    if (tile_bits == 11) return TileCfg<11, 2, LW>::MAX_SUB;
+    if (tile_bits == 10) return TileCfg<10, 1, LW>::MAX_SUB;
     return waves == 4 ? TileCfg<13, 4, LW>::MAX_SUB : TileCfg<13, 8, LW>::MAX_SUB;
 }
 
 int tile_max_blocks(int tile_bits, int waves, int prec)
 {
-    if (!tile_shape_supported(tile_bits, waves) && !(tile_bits == 12 && waves == 4)) return 0;
+    if (!tile_shape_supported(tile_bits, waves) && !small_shape(tile_bits, waves)) return 0;
     // BF16X3's limit is that of split BF16, though its operands are smaller
     if (prec == kTileOperandF64) return max_blocks_of<16>(kF64TileBits, kF64TileWaves);  // the fewest of its shapes
     return prec == kTileOperandBF16 || prec == kTileOperandBF16X3 ? max_blocks_of<24>(tile_bits, waves)
@@ -1398,7 +1408,7 @@ hipError_t make_tile_args(int n_sub, const int (*sub_pos)[4], int n, int tile_bi
                           TileArgs *out)
 {
     const int kTileBits = tile_bits;
-    if (tile_bits < 12 || tile_bits > kMaxTileBits || n_sub < 1 || n_sub > kMaxTileSubBlocks || n < kTileBits)
+    if (tile_bits < kMinTileQubitsSmall || tile_bits > kMaxTileBits || n_sub < 1 || n_sub > kMaxTileSubBlocks || n < kTileBits)
         return hipErrorInvalidValue;
     TileArgs &a = *out;
     std::memset(&a, 0, sizeof a);
@@ -1450,26 +1460,30 @@ hipError_t launch_tile_pass(int n_sub, const int (*sub_pos)[4], const void *d_a,
     if (prec == kTileOperandF64) {
         // virtual position 0 is re / im: every position moves up by one
         if (n_sub < 1 || n_sub > tile_max_blocks(kF64TileBits, kF64TileWaves, prec)) return hipErrorInvalidValue;
-        if (tile_bits != kF64TileBits && tile_bits != 13 && tile_bits != 12) return hipErrorInvalidValue;
+        if (tile_bits != kF64TileBits && tile_bits != 13 && !small_shape(tile_bits, waves)) return hipErrorInvalidValue;
         int pos[kMaxTileSubBlocks][4];
         for (int s = 0; s < n_sub; ++s)
             for (int i = 0; i < 4; ++i) pos[s][i] = sub_pos[s][i] + 1;
         TileArgs a;
-        const int w = tile_bits == 12 ? 4 : 8;
+        const int w = tile_bits >= 13 ? 8 : waves;
         if (hipError_t e = make_tile_args(n_sub, pos, n + 1, tile_bits, w, prec, &a)) return e;
         if (a.ubit[0] != 0) return hipErrorInvalidValue;  // a union of 14 positions leaves no place for it
         TileNorm nv = norm;
         if (nv.basis >= 0) nv.basis <<= 1;
         float *p = static_cast<float *>(psi), *p2 = static_cast<float *>(psi2);
+        if (tile_bits == 10) return tile_launch<10, 1>(a, d_a, prec, p, p2, st, grid_cap, nv, grid_out);
+        if (tile_bits == 11) return tile_launch<11, 2>(a, d_a, prec, p, p2, st, grid_cap, nv, grid_out);
         if (tile_bits == 12) return tile_launch<12, 4>(a, d_a, prec, p, p2, st, grid_cap, nv, grid_out);
         if (tile_bits == 13) return tile_launch<13, 8>(a, d_a, prec, p, p2, st, grid_cap, nv, grid_out);
         return tile_launch<kF64TileBits, kF64TileWaves>(a, d_a, prec, p, p2, st, grid_cap, nv, grid_out);
     }
-    if (!tile_shape_supported(tile_bits, waves) && !(tile_bits == 12 && waves == 4)) return hipErrorInvalidValue;
+    if (!tile_shape_supported(tile_bits, waves) && !small_shape(tile_bits, waves)) return hipErrorInvalidValue;
     if (n_sub < 1 || n_sub > tile_max_blocks(tile_bits, waves, prec)) return hipErrorInvalidValue;
     TileArgs a;
     if (hipError_t e = make_tile_args(n_sub, sub_pos, n, tile_bits, waves, prec, &a)) return e;
     float *p = static_cast<float *>(psi), *p2 = static_cast<float *>(psi2);
+    if (tile_bits == 10) return tile_launch<10, 1>(a, d_a, prec, p, p2, st, grid_cap, norm, grid_out);
+    if (tile_bits == 11) return tile_launch<11, 2>(a, d_a, prec, p, p2, st, grid_cap, norm, grid_out);
     if (tile_bits == 12) return tile_launch<12, 4>(a, d_a, prec, p, p2, st, grid_cap, norm, grid_out);
     if (tile_bits == 14)
         return waves == 16 ? tile_launch<14, 16>(a, d_a, prec, p, p2, st, grid_cap, norm, grid_out)
