@@ -263,8 +263,9 @@ int sv_apply_plan(sv_state *s, const sv_plan *p, int precision, int use_graph);
  * 'evolution')).  Nothing is applied if any gate is invalid.  Asynchronous
  * (use_graph as for sv_apply_plan).  o == NULL means plain per-gate
  * application: {SV_MAX_K, FP32 or FP64 by amplitude type, SV_RULE_NONE, 0}.
- * With SV_RULE_TILED on a state of >= 14 qubits (complex64 below; complex128
- * likewise, with FP64 MFMA and tiles of 2^13 amplitudes), the gates are
+ * With SV_RULE_TILED on a state of >= 14 qubits, in FP32 (SV_PREC_SPLIT_BF16X3
+ * likewise) and FP64 of >= 10 (complex64 below; complex128 likewise, with FP64
+ * MFMA and tiles of 2^13 amplitudes; small states take smaller tiles), the gates are
  * grouped into passes whose positions U leave contiguous HBM runs no shorter
  * than those of a union of sv_set_tile_union() positions (default 10): the
  * tile of a pass is U plus the lowest positions outside it, 14 (or 13) in
