@@ -602,6 +602,23 @@ static TileShape tile_shape_for(const Launch &L, int first, int m, int n, bool t
     return f64 ? TileShape{dev::kF64TileBits, dev::kF64TileWaves} : TileShape{T.tile_bits, T.tile_waves};
 }
 
+// How many blocks of a tile pass, from the first one on, share one launch, and
+// the launch's shape: no more than the set shape holds in LDS, which is what
+// passes are planned for, and no more than the shape they then take, whose own
+// limit may be lower ((13, 8) holds 16 FP32 blocks, (12, 4) 11).
+static int tile_chunk(const Launch &L, int first, int n, bool two, TileShape &shape)
+{
+    const Tuning &T = tuning();
+    const int prec = tile_operand_prec(L.path);
+    int m = std::min(dev::tile_max_blocks(T.tile_bits, T.tile_waves, prec), L.k - first);
+    shape = tile_shape_for(L, first, m, n, two);
+    for (int fit; (fit = dev::tile_max_blocks(shape.bits, shape.waves, prec)) < m;) {
+        m = fit;
+        shape = tile_shape_for(L, first, m, n, two);  // fewer positions may take a smaller shape
+    }
+    return m;
+}
+
 int enqueue(const std::vector<Launch> &launches, int dtype, void *psi, int n, const void *arena, hipStream_t st)
 {
     return enqueue(launches.data(), launches.size(), dtype, psi, n, arena, st);
@@ -620,10 +637,12 @@ int enqueue(const Launch *first, size_t count, int dtype, void *psi, int n, cons
     // it is.  Launches in between act on it linearly; the state is plain again
     // when this call's launches end.
     int norm_launches = 0;  // split-FP16 tile launches of this call that take part
-    const int norm_cap = dev::tile_max_blocks(T.tile_bits, T.tile_waves, dev::kTileOperandF16);
     if (!psi2)
         for (const Launch *it = first; it != first + count; ++it)
-            if (it->path == PATH_TILE_FP16) norm_launches += (it->k + norm_cap - 1) / norm_cap;
+            if (it->path == PATH_TILE_FP16) {
+                TileShape shape;
+                for (int c = 0; c < it->k; c += tile_chunk(*it, c, n, false, shape)) ++norm_launches;
+            }
     int norm_grid = 0, norm_done = 0;
     for (const Launch *it = first; it != first + count; ++it) {
         const Launch &L = *it;
@@ -635,14 +654,12 @@ int enqueue(const Launch *first, size_t count, int dtype, void *psi, int n, cons
             continue;
         }
         if (is_tile_path(L.path)) {
-            // one launch per chunk of blocks whose operands fit the set shape's
-            // LDS (the smaller shapes hold more)
-            const int cap = dev::tile_max_blocks(T.tile_bits, T.tile_waves, tile_operand_prec(L.path));
+            // one launch per chunk of blocks (tile_chunk)
             const size_t op_bytes = 4 * dev::tile_operand_words(tile_operand_prec(L.path));
             const bool use_norm = L.path == PATH_TILE_FP16 && !psi2;
-            for (int c = 0; c < L.k; c += cap) {
-                const int m = std::min(cap, L.k - c);
-                const TileShape shape = tile_shape_for(L, c, m, n, psi2 != nullptr);
+            for (int c = 0, m = 0; c < L.k; c += m) {
+                TileShape shape;
+                m = tile_chunk(L, c, n, psi2 != nullptr, shape);
                 const int per_cu = L.path == PATH_TILE_FP64 ? 1 : dev::tile_wgs_per_cu(shape.bits, shape.waves);
                 const int grid_cap = std::min(kTileNormSlots, T.tile_grid_cap * per_cu);
                 dev::TileNorm norm;
