@@ -445,16 +445,14 @@ void group_tile_passes(const std::vector<Block> &blocks, int n, int precision, s
     const bool fp64 = precision == SV_PREC_FP64;
     for (const auto &grp : tile_groups(blocks, n, precision))
         for (size_t at = 0; at < grp.size();) {
-            // a pass planned for another arithmetic may cover more positions
-            // than an FP64 tile holds: as many of its blocks as fit
-            size_t end = grp.size();
-            if (fp64) {
-                uint64_t u = 0;
-                for (end = at; end < grp.size(); ++end) {
-                    const uint64_t v = u | mask_of(blocks[grp[end]]);
-                    if (end > at && __builtin_popcountll(v) > dev::kF64MaxUnion) break;
-                    u = v;
-                }
+            // a pass planned for another arithmetic or another tile shape may
+            // cover more positions than a tile holds now: as many of its blocks
+            // as fit (position 0 lies in every tile of complex64, and FP64's
+            // count leaves it out)
+            size_t end = at;
+            for (uint64_t u = fp64 ? 0 : 1; end < grp.size(); ++end) {
+                u |= mask_of(blocks[grp[end]]);
+                if (end > at && __builtin_popcountll(u) > tile_pass_bits(precision)) break;
             }
             // a block alone: its own dense launch, or a tile pass of one block
             // where that is priced lower (below 14 qubits, where launches are
