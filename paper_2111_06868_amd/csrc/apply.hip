@@ -22,6 +22,8 @@
 // register indexing is static.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace sv {
@@ -251,30 +253,35 @@ __global__ void __launch_bounds__(256) k_apply_rows(T *__restrict__ psi0, const 
         M[2 * (c * D + r)] = m[2 * e];
         M[2 * (c * D + r) + 1] = m[2 * e + 1];
     }
-    const uint64_t g = (uint64_t(blockIdx.x) * 256 + t) >> K;
-    const bool in = g < a.n_groups;
-    uint64_t o = g;
+    const uint64_t step = (uint64_t(gridDim.x) * 256) >> K;
+    // uniform trip count (K <= 6: a workgroup holds whole groups)
+    for (uint64_t g0 = (uint64_t(blockIdx.x) * 256) >> K; g0 < a.n_groups; g0 += step) {
+        const uint64_t g = g0 + (uint32_t(t) >> K);
+        const bool in = g < a.n_groups;
+        uint64_t o = g;
 #pragma unroll
-    for (int j = 0; j < K; ++j) o = insert_zero(o, a.pos[j]);
+        for (int j = 0; j < K; ++j) o = insert_zero(o, a.pos[j]);
 #pragma unroll
-    for (int j = 0; j < K; ++j)
-        if ((row >> j) & 1) o += uint64_t(1) << a.pos[j];
-    X[2 * t] = in ? psi[2 * o] : T(0);
-    X[2 * t + 1] = in ? psi[2 * o + 1] : T(0);
-    __syncthreads();
-    T sr = 0, si = 0;
+        for (int j = 0; j < K; ++j)
+            if ((row >> j) & 1) o += uint64_t(1) << a.pos[j];
+        __syncthreads();  // the matrix is staged (first time), the last groups' amplitudes are read
+        X[2 * t] = in ? psi[2 * o] : T(0);
+        X[2 * t + 1] = in ? psi[2 * o + 1] : T(0);
+        __syncthreads();
+        T sr = 0, si = 0;
 #pragma unroll 8
-    for (int c = 0; c < D; ++c) {
-        const T ar = M[2 * (c * D + row)], ai = M[2 * (c * D + row) + 1];
-        const T vr = X[2 * ((t & ~(D - 1)) | c)], vi = X[2 * ((t & ~(D - 1)) | c) + 1];
-        sr = fma(ar, vr, sr);
-        sr = fma(-ai, vi, sr);
-        si = fma(ar, vi, si);
-        si = fma(ai, vr, si);
-    }
-    if (in) {
-        psi[2 * o] = sr;
-        psi[2 * o + 1] = si;
+        for (int c = 0; c < D; ++c) {
+            const T ar = M[2 * (c * D + row)], ai = M[2 * (c * D + row) + 1];
+            const T vr = X[2 * ((t & ~(D - 1)) | c)], vi = X[2 * ((t & ~(D - 1)) | c) + 1];
+            sr = fma(ar, vr, sr);
+            sr = fma(-ai, vi, sr);
+            si = fma(ar, vi, si);
+            si = fma(ai, vr, si);
+        }
+        if (in) {
+            psi[2 * o] = sr;
+            psi[2 * o + 1] = si;
+        }
     }
 }
 
@@ -287,7 +294,8 @@ hipError_t generic_launch_t(const int *sorted_q, const T *d_m, T *psi, T *psi2, 
     a.n_groups = uint64_t(1) << (n - K);
     if constexpr (K >= 3) {
         if (K != 4 || n <= 22) {
-            const unsigned grid = unsigned(((uint64_t(1) << n) + 255) / 256);  // n <= SV_MAX_QUBITS_C64: fits
+            // a launch has fewer than 2^32 work-items; larger states take several groups a thread
+            const unsigned grid = unsigned(std::min(((uint64_t(1) << n) + 255) / 256, uint64_t(1) << 23));
             hipLaunchKernelGGL((k_apply_rows<T, K>), dim3(grid, psi2 ? 2 : 1), dim3(256),
                                sizeof(T) * 2 * ((1 << (2 * K)) + 256), st, psi, d_m, a);
             return hipGetLastError();
