@@ -161,7 +161,8 @@ class Frontier {
         for (int t = 0; t < G; ++t)
             for (uint64_t m = mask_[t]; m; m &= m - 1) queue_[size_t(end_[__builtin_ctzll(m)]++)] = t;
         left_ = G;
-        find_ready();
+        for (int t = 0; t < G; ++t) need_[size_t(t)] = popc(mask_[size_t(t)]);
+        for (uint64_t m = used_; m; m &= m - 1) arrive(__builtin_ctzll(m));
     }
     // The next group (gate indices of the caller's list), or false when none is left.
     template <class Fits>
@@ -208,31 +209,35 @@ class Frontier {
             slot_.assign(size_t(top) + 1, -1);
             for (size_t t = 0; t < idx_.size(); ++t) slot_[size_t(idx_[t])] = int(t);
         }
+        // only the qubits of the returned gates change: what was first on them
+        // no longer is
+        uint64_t on = 0;
+        for (int gi : gates) on |= mask_[size_t(slot_.at(size_t(gi)))];
+        for (uint64_t m = on; m; m &= m - 1) leave(__builtin_ctzll(m));
         for (int gi : gates) {
-            for (uint64_t m = mask_[size_t(slot_.at(size_t(gi)))]; m; m &= m - 1) --head_[__builtin_ctzll(m)];
+            const size_t t = size_t(slot_.at(size_t(gi)));
+            for (uint64_t m = mask_[t]; m; m &= m - 1) --head_[__builtin_ctzll(m)];
+            need_[t] = popc(mask_[t]);
             ++left_;
         }
-        find_ready();
+        for (uint64_t m = on; m; m &= m - 1) arrive(__builtin_ctzll(m));
     }
 
   private:
     // need_[t]: qubits on which gate t is not the first unapplied one (kept for
     // gates that are first on one of theirs or were); ready_: the qubits whose
     // first unapplied gate is first on all of its qubits.
-    void find_ready()
-    {
-        for (uint64_t m = used_; m; m &= m - 1) {
-            const int p = __builtin_ctzll(m);
-            for (int32_t i = head_[p]; i < end_[p]; ++i) need_[size_t(queue_[size_t(i)])] = popc(mask_[size_t(queue_[size_t(i)])]);
-        }
-        ready_ = 0;
-        for (uint64_t m = used_; m; m &= m - 1) arrive(__builtin_ctzll(m));
-    }
     void arrive(int p)  // the gate at p's head becomes first on p
     {
         if (head_[p] >= end_[p]) return;
         const size_t t = size_t(queue_[size_t(head_[p])]);
         if (--need_[t] == 0) ready_ |= mask_[t];
+    }
+    void leave(int p)  // the gate at p's head is first on p no more
+    {
+        if (head_[p] >= end_[p]) return;
+        const size_t t = size_t(queue_[size_t(head_[p])]);
+        if (need_[t]++ == 0) ready_ &= ~mask_[t];
     }
     void take(int t)
     {
