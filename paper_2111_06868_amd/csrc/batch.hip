@@ -346,7 +346,6 @@ int build_schedule(sv_batch *b, const sv_batch_desc *d, int k)
                 passes.push_back(tp);
             }
         }
-        if (!mine.empty()) passes[size_t(mine.back())].last = 1;
         BLarge L;
         L.state_off = b->state_off[t];
         L.n = n;

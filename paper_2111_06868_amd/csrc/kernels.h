@@ -126,8 +126,6 @@ constexpr int kBatchTileWaves = 16;
 struct TilePass {
     uint64_t state_off;  // complex elements from the start of the batch buffer
     uint64_t op_off;     // 32-bit words into the operand pool
-    int32_t last;        // the state's last pass
-    int32_t pad;
     TileArgs args;
 };
 struct TileUnit {

@@ -353,7 +353,7 @@ struct TileShared {
     alignas(16) uint32_t op[C::OP_AREA];  // the blocks' operands, C::op_words(n_sub) apart
     uint32_t cq[C::MAX_SUB][C::CBLOCKS];
     uint32_t cl[C::MAX_SUB][32];
-    float red[WAVES];  // per-wave partial of the next tile's scale (FP16 passes)
+    float red[WAVES];  // per-wave partial of a tile's scale (FP16 passes)
     float nrm[WAVES];  // per-wave sum of squares read so far (FP16 passes that report the norm)
 };
 
@@ -1040,8 +1040,8 @@ __device__ __forceinline__ void apply_stage(TileShared<TB, WAVES, lane_words(kPr
 // 32 x 32 x 16 MFMA with FP32 accumulation.  The dropped terms are about
 // 2^-17 (BF16: the state's third part, A_1 X_1), 2^-22 (FP16) and 2^-25
 // (X3) relative to the result.  FP16 passes scale the values per tile
-// (tile_scale; SCALE 0, and SCALE 2, which also reports the workgroup's sum
-// of squares to norm.out) or per pass from the state's norm (norm_scale;
+// (tile_scale; SCALE 0, SCALE 5, which holds the tile scaled in LDS, and SCALE 2,
+// which is SCALE 0 and also reports the workgroup's sum of squares to norm.out) or per pass from the state's norm (norm_scale;
 // SCALE 1, from the sums an earlier pass of the run reported; SCALE 3, the
 // same scale with the state already held scaled in HBM, copied as it is).
 template <int TB, int WAVES, int PREC, int SCALE, int WHOLE>
@@ -1094,7 +1094,7 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
     // copies it as it is.
     float pscale = 1.f, punscale = 1.f;
     if (F16 && SCALE == 1) {
-        double r2 = norm.n_in == 0 && lane == 0 ? 1.0 : 0.0;  // no sums: a norm of 1
+        double r2 = 0.0;
         for (int i = lane; i < norm.n_in; i += 64) r2 += norm.in[i];
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) r2 += __shfl_xor(r2, o, 64);
@@ -1105,6 +1105,10 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
         punscale = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, punscale)));
     }
     constexpr bool PER_TILE = F16 && (SCALE == 0 || SCALE == 2);  // scales from each tile's maximum
+    // SCALE 5: the same scales, but multiplied in at copy-in and out at copy-out
+    // instead of around every block (exact powers of two: the same bits), for a
+    // barrier more a tile
+    constexpr bool HELD = F16 && SCALE == 5;
     // SCALE 2: per-tile scales as SCALE 0, and the workgroup's sum of squares to norm.out
     constexpr bool want_norm = F16 && SCALE == 2;
     if (T >= T_end) {  // uniform over the workgroup
@@ -1160,11 +1164,19 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
     uint64_t prev = 0;
     for (bool first = true; T < T_end; T += step, first = false) {
         const uint64_t base = tile_base(T, args);
-        if (F16 && SCALE == 1) {
+        float unscale_prev = punscale;
+        if (HELD) {
+            wave_max_to_red(buf);
+            __syncthreads();
+            tile_scale(red_max(), pscale, punscale);
+            pscale = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, pscale)));
+            punscale = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, punscale)));
+        }
+        if (F16 && (SCALE == 1 || HELD)) {
             if (first)
                 cp.to_lds_scaled(sh.X4, buf, pscale);
             else
-                cp.swap_scaled(psi, prev, sh.X4, buf, pscale, punscale);
+                cp.swap_scaled(psi, prev, sh.X4, buf, pscale, unscale_prev);
         } else {
             if (first)
                 cp.to_lds(sh.X4, buf);
@@ -1209,7 +1221,7 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
         prev = base;
     }
     // the last tile of this workgroup
-    if (F16 && SCALE == 1)
+    if (F16 && (SCALE == 1 || HELD))
         cp.store_scaled(psi, prev, sh.X4, punscale);
     else
         cp.store(psi, prev, sh.X4);
@@ -1249,10 +1261,9 @@ __global__ void __launch_bounds__(64 * WAVES) k_tile_pass(float *__restrict__ ps
 // the pass units[i] names (states of a batch, each with its own tile layout,
 // blocks and operands).
 // START: the states' first passes, which read nothing and start from |0..0>.
-// FP16: the norm is 1 and its scale known, so the states are held scaled from
-// their first pass to their last; a scale from each tile's maximum costs a
-// multiplication per value and block (12 layers of 46407 tiles in all: 3687 to
-// 3533 us).
+// FP16 scales by each tile's maximum and holds the tile scaled in LDS (SCALE 5).
+// One scale for a whole state, from its norm, would need no maximum, but leaves
+// amplitudes below 2^-28 of the norm one part and those below 2^-38 nothing.
 template <int TB, int WAVES, int PREC, bool START>
 __global__ void __launch_bounds__(64 * WAVES) k_tile_batch(const TileUnit *__restrict__ units,
                                                            const TilePass *__restrict__ passes,
@@ -1263,9 +1274,7 @@ __global__ void __launch_bounds__(64 * WAVES) k_tile_batch(const TileUnit *__res
     const TilePass &p = passes[u.pass];
     TileNorm norm;
     norm.basis = START ? 0 : -1;
-    norm.in_scaled = !START;
-    norm.out_scaled = !p.last;
-    constexpr int SCALE = PREC == kPrecF16 ? 1 : START ? 4 : 0;
+    constexpr int SCALE = PREC == kPrecF16 ? 5 : START ? 4 : 0;
     tile_loop<TB, WAVES, PREC, SCALE, -1>(sh, buf + 2 * p.state_off, pool + p.op_off, p.args, u.t0, u.t1, 1, norm);
 }
 
