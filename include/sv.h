@@ -445,8 +445,10 @@ int sv_dm_expectation(sv_state *rho, const sv_pauli_sum *H, double *out);
  * sv_run_trajectory: applies the gates g with the operators ops sampled among
  * them (operator j after the first ops[j].after gates, `after`
  * nondecreasing) using uniforms[j]; the gate runs between operators are fused
- * and applied as by sv_run_circuit with options o.  outcomes (may be NULL)
- * receives the n_ops chosen indices.
+ * and applied as by sv_run_circuit with options o.  The chosen operators are
+ * applied in FP32 or FP64 by the amplitude type, whatever o's arithmetic; where
+ * that is FP32, BF16X3 or FP64 and its rule fuses, they join the blocks of the
+ * gates that follow.  outcomes (may be NULL) receives the n_ops chosen indices.
  *
  * Errors: SV_ERR_ARG (not a Kraus channel, more than 16 operators, u outside
  * [0, 1), all weights zero), SV_ERR_QUBIT. */

@@ -1258,10 +1258,12 @@ extern "C" int sv_run_trajectory(sv_state *s, const sv_gate *g, int G, const sv_
         if (!(uniforms[j] >= 0.0 && uniforms[j] < 1.0))
             return fail(SV_ERR_ARG, "uniform %d = %g outside [0, 1)", j, uniforms[j]);
     }
-    // Drawn operators join the gates that follow them where those are fused;
-    // split FP16 takes only unitary gates, and an unfused run would give each
-    // operator a pass of its own.
-    const bool join = o && o->rule != SV_RULE_NONE && o->precision != SV_PREC_SPLIT_FP16;
+    // Drawn operators join the gates that follow them where those are fused in
+    // FP32 or FP64 (the blocks' matrices are formed in FP64).  The 16-bit splits
+    // would hold the operators in fewer bits, and an unfused run would give
+    // each operator a pass of its own.
+    const bool join = o && o->rule != SV_RULE_NONE &&
+                      (o->precision == SV_PREC_FP32 || o->precision == SV_PREC_SPLIT_BF16X3 || o->precision == SV_PREC_FP64);
     KrausSampler sampler(s);
     for (int j = 0, done = 0;;) {
         const int upto = j < n_ops ? ops[j].after : G;
