@@ -1250,9 +1250,9 @@ extern "C" int sv_run_trajectory(sv_state *s, const sv_gate *g, int G, const sv_
     if (int rc = check_state(s)) return rc;
     if (int rc = validate_gates(g, G, s->n)) return rc;
     if (n_ops < 0 || (n_ops && (!ops || !uniforms))) return fail(SV_ERR_ARG, "NULL operator or uniform array");
-    std::vector<KrausSet> ks(static_cast<size_t>(n_ops));
     for (int j = 0; j < n_ops; ++j) {
-        if (int rc = kraus_canonical(ops[j], s->n, ks[size_t(j)])) return rc;
+        KrausSet ks;
+        if (int rc = kraus_canonical(ops[j], s->n, ks)) return rc;
         if (ops[j].after < 0 || ops[j].after > G || (j && ops[j].after < ops[j - 1].after))
             return fail(SV_ERR_ARG, "operator %d: after = %d out of order (0..%d, nondecreasing)", j, ops[j].after, G);
         if (!(uniforms[j] >= 0.0 && uniforms[j] < 1.0))
@@ -1281,10 +1281,17 @@ extern "C" int sv_run_trajectory(sv_state *s, const sv_gate *g, int G, const sv_
             done = upto;
         }
         if (j == n_ops) break;
+        // channels of one place in the circuit, as long as their matrices stay
+        // below 4 MiB (three-qubit depolarizing takes 128 KiB)
+        std::vector<KrausSet> ks;
         int end = j;
-        while (end < n_ops && ops[end].after == upto) ++end;
+        for (size_t held = 0; end < n_ops && ops[end].after == upto && held < (size_t(4) << 20); ++end) {
+            ks.emplace_back();
+            if (int rc = kraus_canonical(ops[end], s->n, ks.back())) return rc;
+            held += 2 * sizeof(cd) * ks.back().canon.size();
+        }
         std::vector<int32_t> picks(size_t(end - j), -1);
-        const int rc = sampler.run(ks.data() + j, end - j, uniforms + j, picks.data(), nullptr);
+        const int rc = sampler.run(ks.data(), end - j, uniforms + j, picks.data(), nullptr);
         for (int i = 0; outcomes && i < end - j; ++i)
             if (picks[size_t(i)] >= 0) outcomes[j + i] = picks[size_t(i)];
         if (rc) return rc;
