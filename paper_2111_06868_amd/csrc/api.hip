@@ -1480,17 +1480,25 @@ int run_gradients(const sv_gate *g, const BwdStep &st, const double *v, double *
     return SV_OK;
 }
 
-// Fuse the daggers of gates hi, hi-1, .., lo (in that order) into blocks and
-// append their launches.
-int dagger_launches(const sv_gate *g, int hi, int lo, const sv_state *s, int prec, std::vector<Launch> &out)
+// The daggers of a run of gates, fused into blocks: tile passes or dense ones.
+struct DaggerPlan {
+    std::vector<cd> store;    // the daggers' matrices
+    std::vector<sv_gate> dg;  // point into store
+    int kmax = 1;             // qubits of the widest
+    std::vector<Block> blocks;
+    bool tiled = false;
+};
+
+// The daggers of gates hi, hi-1, .., lo (in that order) of a run.
+void form_daggers(const sv_gate *g, int hi, int lo, DaggerPlan &p)
 {
     const int cnt = hi - lo + 1;
-    std::vector<sv_gate> dg(cnt);
+    std::vector<sv_gate> &dg = p.dg;
+    dg.resize(size_t(cnt));
     size_t entries = 0;
     for (int t = lo; t <= hi; ++t) entries += size_t(1) << (2 * g[t].k);
-    std::vector<cd> store(entries);
-    cd *m = store.data();
-    int kmax = 1;
+    p.store.resize(entries);
+    cd *m = p.store.data();
     for (int t = 0; t < cnt; ++t) {
         const sv_gate &src = g[hi - t];
         const int D = 1 << src.k;
@@ -1507,10 +1515,27 @@ int dagger_launches(const sv_gate *g, int hi, int lo, const sv_state *s, int pre
         dg[t].kind = SV_G_MATRIX;
         dg[t].param = -1;
         dg[t].m = reinterpret_cast<const double *>(m);
-        kmax = std::max(kmax, src.k);
+        p.kmax = std::max(p.kmax, src.k);
         m += D * D;
     }
-    std::vector<Block> blocks;
+}
+
+// Whether two runs of gates have the same positions.
+bool same_positions(const sv_gate *g, const BwdStep &a, const BwdStep &b)
+{
+    if (a.first - a.last != b.first - b.last) return false;
+    for (int i = a.first, j = b.first; i >= a.last; --i, --j)
+        if (g[i].k != g[j].k || !std::equal(g[i].q, g[i].q + g[i].k, g[j].q)) return false;
+    return true;
+}
+
+// Plan the daggers: positions and members of the blocks, no matrices yet
+// (dagger_launches).
+int plan_daggers(const sv_state *s, int prec, DaggerPlan &p)
+{
+    const std::vector<sv_gate> &dg = p.dg;
+    const int cnt = int(dg.size()), kmax = p.kmax;
+    std::vector<Block> &blocks = p.blocks;
     const CostTable cost = lookup_costs(s->n, prec, nullptr);
     // The plan of a run (dense blocks of the cheapest k, or tile passes)
     // depends on its gates' positions and the cost table only; it is
@@ -1567,16 +1592,35 @@ int dagger_launches(const sv_gate *g, int hi, int lo, const sv_state *s, int pre
         if (memo.size() > 65536) memo.clear();
         memo[key] = choice;
     }
-    if (choice == 0) {
-        if (int rc = fuse_gates(dg.data(), cnt, s->n, 4, SV_RULE_TILED, cost, blocks, true, prec)) return rc;
-        std::vector<Launch> tl;
-        group_tile_passes(blocks, s->n, prec, tl);
-        for (auto &L : tl) out.push_back(std::move(L));
-        return SV_OK;
+    p.tiled = choice == 0;
+    if (p.tiled) return fuse_gates(dg.data(), cnt, s->n, 4, SV_RULE_TILED, cost, blocks, false, prec);
+    return fuse_gates(dg.data(), cnt, s->n, choice, SV_RULE_ENHANCED, cost, blocks, false);
+}
+
+// No less than the device operands of a plan's blocks take (operand sizes of
+// pack_operands), on whatever path.
+size_t operand_bound(const DaggerPlan &p, int prec)
+{
+    const bool split = prec == SV_PREC_SPLIT_BF16 || prec == SV_PREC_SPLIT_FP16;
+    const size_t tile = p.tiled ? 4 * size_t(dev::tile_operand_words(tile_operand_prec(tile_path(prec)))) : 0;
+    size_t total = 0;
+    for (const auto &b : p.blocks) {
+        const size_t D2 = size_t(1) << (2 * b.k), form = dev::real_form_elems(b.k);
+        total += 256 + std::max({tile, split ? 6 * form + 512 : 4 * form, 16 * D2});
     }
-    const int kbest = choice;
-    if (int rc = fuse_gates(dg.data(), cnt, s->n, kbest, SV_RULE_ENHANCED, cost, blocks)) return rc;
-    for (auto &b : blocks) {
+    return total;
+}
+
+// The launches of a plan, whose blocks' matrices are formed here.
+std::vector<Launch> dagger_launches(DaggerPlan &p, const sv_state *s, int prec)
+{
+    std::vector<Launch> out;
+    block_matrices(p.dg.data(), p.blocks);
+    if (p.tiled) {
+        group_tile_passes(p.blocks, s->n, prec, out);
+        return out;
+    }
+    for (auto &b : p.blocks) {
         Launch L;
         L.k = b.k;
         std::copy(b.q, b.q + SV_MAX_K, L.q);
@@ -1584,7 +1628,7 @@ int dagger_launches(const sv_gate *g, int hi, int lo, const sv_state *s, int pre
         L.m = std::move(b.m);
         out.push_back(std::move(L));
     }
-    return SV_OK;
+    return out;
 }
 
 }  // namespace
@@ -1658,60 +1702,96 @@ int backward_impl(sv_state *psi, sv_state *scratch, const sv_gate *g, int G, con
     if (int rc = select_device(psi)) return rc;
     // lam <- H psi on psi's stream
     if (int rc = sv_apply_pauli_sum(psi, H, scratch)) return rc;
-    SV_HIP(psi->grad.ensure(sizeof(double) * 8 * size_t(std::max(slots, 1)) * size_t(dev::transition_blocks(psi->n))));
-    SV_HIP(psi->red_host.ensure(sizeof(double) * 8 * size_t(std::max(slots, 1))));
-    double *part = static_cast<double *>(psi->grad.p);
-    // The first steps are planned and launched before the others are planned,
-    // so that the GPU sweeps while the host forms matrices.  Their operands
-    // lie in the scratch state's arena: psi's holds H's tables until then.
-    for (size_t from = 0; from < steps.size();) {
-        const size_t to = from ? steps.size() : (steps.size() + 3) / 4;
-        sv_state *const at = from ? psi : scratch;
-        // the dagger blocks of the steps are independent host work: spread over
-        // threads where there are many
-        std::vector<std::vector<Launch>> outs(to - from);
-        std::vector<int> rcs(outs.size(), SV_OK);
-        std::vector<std::string> msgs(outs.size());
-        std::atomic<size_t> next(0);
+    // All that can fail short of a launch comes before the sweep changes psi:
+    // the plans of all steps, and room for their operands.  H psi is computed
+    // meanwhile.  A step of the same positions as the one before it has that
+    // one's plan; the others are independent host work: spread over threads
+    // where there are many.
+    std::vector<DaggerPlan> plans(steps.size());
+    std::vector<size_t> plan_of(steps.size());
+    auto spread = [&](size_t from, size_t to, auto &&work) {
+        std::atomic<size_t> next(from);
         auto worker = [&]() {
-            for (size_t t; (t = next.fetch_add(1)) < outs.size();) {
-                rcs[t] = dagger_launches(g, steps[from + t].first, steps[from + t].last, psi, prec, outs[t]);
-                if (rcs[t]) msgs[t] = last_error_cstr();
-            }
+            for (size_t t; (t = next.fetch_add(1)) < to;) work(t);
         };
-        const unsigned hw = std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
-        const unsigned nt = outs.size() >= 16 ? std::min<unsigned>(hw, unsigned(outs.size() / 4)) : 1u;
+        unsigned nt = 1;
+        if (to - from >= 16)
+            nt = std::min(std::max(1u, std::min(8u, std::thread::hardware_concurrency())), unsigned((to - from) / 4));
         std::vector<std::thread> pool;
         for (unsigned t = 1; t < nt; ++t) pool.emplace_back(worker);
         worker();
         for (auto &th : pool) th.join();
-        std::vector<Launch> launches;
-        std::vector<size_t> end;
-        for (size_t t = 0; t < outs.size(); ++t) {
+    };
+    {
+        std::vector<int> rcs(steps.size(), SV_OK);
+        std::vector<std::string> msgs(steps.size());
+        for (size_t t = 0; t < steps.size(); ++t)
+            plan_of[t] = t && same_positions(g, steps[t], steps[t - 1]) ? plan_of[t - 1] : t;
+        spread(0, steps.size(), [&](size_t t) {
+            if (plan_of[t] != t) return;
+            form_daggers(g, steps[t].first, steps[t].last, plans[t]);
+            rcs[t] = plan_daggers(psi, prec, plans[t]);
+            if (rcs[t]) msgs[t] = last_error_cstr();
+        });
+        for (size_t t = 0; t < steps.size(); ++t)
             if (rcs[t]) return fail(rcs[t], "%s", msgs[t].c_str());
-            for (auto &L : outs[t]) launches.push_back(std::move(L));
+    }
+    // The first quarter of the steps is launched before the others' matrices
+    // are formed, so that the GPU sweeps meanwhile.  Its operands lie in the
+    // scratch state's arena: psi's holds H's tables until then.
+    const size_t ahead = (steps.size() + 3) / 4;
+    for (sv_state *at : {scratch, psi}) {
+        size_t bytes = prec == SV_PREC_SPLIT_FP16 ? 8 * kTileNormSlots + 256 : 0;
+        for (size_t t = at == psi ? ahead : 0; t < (at == psi ? steps.size() : ahead); ++t) bytes += operand_bound(plans[plan_of[t]], prec);
+        if (bytes > at->stage.cap || bytes > at->arena.cap) SV_HIP(hipEventSynchronize(at->arena_free));
+        SV_HIP(at->stage.ensure(bytes));
+        SV_HIP(at->arena.ensure(bytes));
+    }
+    SV_HIP(psi->grad.ensure(sizeof(double) * 8 * size_t(std::max(slots, 1)) * size_t(dev::transition_blocks(psi->n))));
+    SV_HIP(psi->red_host.ensure(sizeof(double) * 8 * size_t(std::max(slots, 1))));
+    double *part = static_cast<double *>(psi->grad.p);
+    auto sweep = [&](size_t from, size_t to, sv_state *at) -> int {
+        std::vector<std::vector<Launch>> outs(to - from);
+        spread(from, to, [&](size_t t) {
+            DaggerPlan p;
+            form_daggers(g, steps[t].first, steps[t].last, p);
+            p.blocks = plans[plan_of[t]].blocks;
+            p.tiled = plans[plan_of[t]].tiled;
+            outs[t - from] = dagger_launches(p, psi, prec);
+        });
+        std::vector<Launch> launches;
+        std::vector<size_t> end;  // of each step's launches
+        for (auto &out : outs) {
+            for (auto &L : out) launches.push_back(std::move(L));
             end.push_back(launches.size());
         }
         SV_HIP(hipEventSynchronize(at->arena_free));
         const size_t bytes = pack_operands(launches, psi->dtype, at->stage);
-        if (bytes == size_t(-1)) return fail(SV_ERR_HIP, "pinned staging allocation failed");
-        if (bytes) {
-            SV_HIP(at->arena.ensure(bytes));
-            SV_HIP(hipMemcpyAsync(at->arena.p, at->stage.p, bytes, hipMemcpyHostToDevice, psi->stream));
-        }
-        for (size_t t = 0, l = 0; t < outs.size(); l = end[t++]) {
-            const BwdStep &st = steps[from + t];
+        if (bytes > at->arena.cap) return fail(SV_ERR_HIP, "operands of %zu bytes in an arena of %zu", bytes, at->arena.cap);
+        if (bytes) SV_HIP(hipMemcpyAsync(at->arena.p, at->stage.p, bytes, hipMemcpyHostToDevice, psi->stream));
+        for (size_t t = from, l = 0; t < to; l = end[t++ - from]) {
+            const BwdStep &st = steps[t];
             if (!st.qubits.empty()) {
                 LaunchTimer timer(stat_class(FAM_ADJOINT, 3), psi->stream);
                 SV_HIP(dev::launch_transitions(psi->dtype, int(st.qubits.size()), st.qubits.data(), psi->buf,
                                                scratch->buf, psi->n, part, st.slot, psi->stream));
             }
-            if (int rc = enqueue(launches.data() + l, end[t] - l, psi->dtype, psi->buf, psi->n, at->arena.p,
+            if (int rc = enqueue(launches.data() + l, end[t - from] - l, psi->dtype, psi->buf, psi->n, at->arena.p,
                                  psi->stream, scratch->buf))
                 return rc;
         }
-        SV_HIP(hipEventRecord(at->arena_free, psi->stream));
-        from = to;
+        return SV_OK;
+    };
+    int swept = sweep(0, ahead, scratch);
+    // after a failed launch too, nothing may touch the arenas or the scratch
+    // state before what is in flight
+    SV_HIP(hipEventRecord(scratch->arena_free, psi->stream));
+    if (!swept) swept = sweep(ahead, steps.size(), psi);
+    SV_HIP(hipEventRecord(psi->arena_free, psi->stream));
+    if (swept) {
+        const std::string msg = last_error_cstr();
+        (void)stream_after(scratch->stream, psi->stream);
+        return fail(swept, "%s", msg.c_str());
     }
     double *sums = static_cast<double *>(psi->red_host.p);
     if (slots) SV_HIP(dev::launch_transitions_final(part, slots, psi->n, sums, psi->stream));
