@@ -243,6 +243,11 @@ int sv_plan_rule(const sv_plan *p, int *out);
  * pass number >= 0 are applied together in one read and one write of the
  * state; -1 means the block is applied on its own. */
 int sv_plan_block_pass(const sv_plan *p, int b, int32_t *pass);
+/* on = 1: sv_apply_plan applies the plan's blocks as they are, a launch each in
+ * their order (tile passes of SV_RULE_TILED as planned), for instance to time
+ * a rule's own blocks; on = 0 (the default): as sv_apply_plan says.  Not to be
+ * called while another thread applies the plan. */
+int sv_plan_own_blocks(sv_plan *p, int on);
 /* Apply a plan's blocks in order with the given SV_PREC_* arithmetic.  Blocks
  * may share passes over the state with others that they commute with; in FP32
  * (SV_PREC_SPLIT_BF16X3 likewise) and FP64, a plan of the paper or enhanced rule

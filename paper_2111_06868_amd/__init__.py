@@ -711,6 +711,12 @@ class Plan:
         N.check(N.lib().sv_plan_max_k(self.h, ctypes.byref(out)))
         return out.value
 
+    def own_blocks(self, on: bool = True) -> "Plan":
+        """Apply the plan's blocks as they are, a launch each, instead of letting
+        them share passes or run as tile passes of the same gates."""
+        N.check(N.lib().sv_plan_own_blocks(self.h, int(bool(on))))
+        return self
+
     def __len__(self) -> int:
         out = ctypes.c_int()
         N.check(N.lib().sv_plan_num_blocks(self.h, ctypes.byref(out)))

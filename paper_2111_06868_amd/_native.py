@@ -110,6 +110,7 @@ SIGNATURES = {
     "sv_plan_block": (_I, [_P, _I, _I32P, _I32P, _I32P]),
     "sv_plan_block_members": (_I, [_P, _I, _I32P]),
     "sv_plan_block_pass": (_I, [_P, _I, _I32P]),
+    "sv_plan_own_blocks": (_I, [_P, _I]),
     "sv_plan_block_matrix": (_I, [_P, _I, _D]),
     "sv_plan_max_k": (_I, [_P, ctypes.POINTER(_I)]),
     "sv_plan_rule": (_I, [_P, ctypes.POINTER(_I)]),

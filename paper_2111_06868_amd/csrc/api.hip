@@ -136,7 +136,7 @@ int run_launches(sv_state *s, std::vector<Launch> &launches, bool use_graph)
 }
 
 int blocks_to_launches(const std::vector<Block> &blocks, const sv_state *s, int precision, int rule,
-                       std::vector<Launch> &out)
+                       std::vector<Launch> &out, bool own_blocks = false)
 {
     if (rule == SV_RULE_TILED) {
         group_tile_passes(blocks, s->n, precision, out);
@@ -152,6 +152,7 @@ int blocks_to_launches(const std::vector<Block> &blocks, const sv_state *s, int 
         L.m = b.m;
         out.push_back(std::move(L));
     }
+    if (own_blocks) return SV_OK;
     if (int rc = group_dense_passes(out, s->n, precision)) return rc;
     return group_gate_passes(out, s->n, s->dtype);
 }
@@ -575,6 +576,14 @@ extern "C" int sv_plan_block(const sv_plan *p, int b, int32_t *k, int32_t *q, in
     return SV_OK;
 }
 
+extern "C" int sv_plan_own_blocks(sv_plan *p, int on)
+{
+    clear_error();
+    if (!p) return fail(SV_ERR_ARG, "NULL argument");
+    p->own_blocks = on != 0;
+    return SV_OK;
+}
+
 extern "C" int sv_plan_block_pass(const sv_plan *p, int b, int32_t *pass)
 {
     clear_error();
@@ -624,9 +633,10 @@ extern "C" int sv_apply_plan(sv_state *s, const sv_plan *p, int precision, int u
             if (int rc = check_unitary(p->blocks[i].m, p->blocks[i].k, what.c_str())) return rc;
         }
     std::vector<Launch> L;
-    const bool tiles = !p->tiled.empty() && takes_tiles(p->rule, precision, s->n) &&
+    const bool tiles = !p->own_blocks && !p->tiled.empty() && takes_tiles(p->rule, precision, s->n) &&
                        tiles_are_cheaper(p->blocks, p->tiled, s->n, precision);
-    if (int rc = blocks_to_launches(tiles ? p->tiled : p->blocks, s, precision, tiles ? SV_RULE_TILED : p->rule, L))
+    if (int rc = blocks_to_launches(tiles ? p->tiled : p->blocks, s, precision, tiles ? SV_RULE_TILED : p->rule, L,
+                                    p->own_blocks))
         return rc;
     if (int rc = select_device(s)) return rc;
     return run_launches(s, L, use_graph != 0);

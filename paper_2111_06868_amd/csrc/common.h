@@ -159,6 +159,7 @@ struct sv_plan {
     int rule = 0;
     std::vector<sv::Block> blocks;
     std::vector<sv::Block> tiled;  // the same gates as tile passes, or empty (gates_as_tiles)
+    bool own_blocks = false;       // apply `blocks` as they are, one launch each (sv_plan_own_blocks)
     // device-side cache (filled by the runtime when the plan is applied)
     void *cache = nullptr;
 };
