@@ -1044,7 +1044,7 @@ __device__ __forceinline__ void apply_stage(TileShared<TB, WAVES, lane_words(kPr
 // which is SCALE 0 and also reports the workgroup's sum of squares to norm.out) or per pass from the state's norm (norm_scale;
 // SCALE 1, from the sums an earlier pass of the run reported; SCALE 3, the
 // same scale with the state already held scaled in HBM, copied as it is).
-template <int TB, int WAVES, int PREC, int SCALE, int WHOLE>
+template <int TB, int WAVES, int PREC, int SCALE, int WHOLE, bool SPREAD>
 __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)> &sh, float *__restrict__ psi,
                                           const uint32_t *__restrict__ A, const TileArgs &args, uint64_t T,
                                           uint64_t T_end, uint64_t step, const TileNorm &norm)
@@ -1155,9 +1155,13 @@ __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)
     };
     // Workgroups that start together copy together and compute together, tile
     // after tile: the memory idles while all of them compute.  A long pass
-    // spreads their starts over about one tile's period, 2 us apart (20 passes
-    // at 30 qubits, interleaved runs: 95.7 against 97.2 ms).
-    if (T_end - T > 16 * step)
+    // (SPREAD) spreads their starts over about one tile's period, 2 us apart.
+    // Ladder circuits, without and with (lowest of four interleaved runs, which
+    // differ by 0.5 %): FP16 3705 and 3649 us at 27 qubits, 32983 and 32870 at 30;
+    // FP64 11554 and 11469 at 27; gate passes 16722 and 16577 at 28; split BF16
+    // 3932 and 3918 at 27.  X3 passes gain nothing (4497 and 4519; 41977 and
+    // 41958), and the workgroups of a batch do not start together.
+    if (SPREAD && T_end - T > 16 * step)
         for (uint32_t i = 0; i < ((blockIdx.x >> 3) & 7u); ++i) __builtin_amdgcn_s_sleep(75);
     vf4 buf[C::CHUNKS];
     fetch(buf, tile_base(T, args));
@@ -1254,7 +1258,7 @@ __global__ void __launch_bounds__(64 * WAVES) k_tile_pass(float *__restrict__ ps
     if constexpr (TB < kMaxTileBits)
         for (int e = 0; e < 3 && e < args.n_ext; ++e) g += args.ext_pos[e] < 4;
     if (g && !(gridDim.x & ((8u << g) - 1))) T = (((T >> 3 >> g) * 8 + (T & 7u)) << g) | ((T >> 3) & ((1u << g) - 1));
-    tile_loop<TB, WAVES, PREC, SCALE, WHOLE>(sh, blockIdx.y ? psi2 : psi, A, args, T, args.n_tiles, gridDim.x, norm);
+    tile_loop<TB, WAVES, PREC, SCALE, WHOLE, PREC != kPrecX3>(sh, blockIdx.y ? psi2 : psi, A, args, T, args.n_tiles, gridDim.x, norm);
 }
 
 // Passes of many states in one grid: workgroup i takes tiles [t0, t1) of
@@ -1275,7 +1279,7 @@ __global__ void __launch_bounds__(64 * WAVES) k_tile_batch(const TileUnit *__res
     TileNorm norm;
     norm.basis = START ? 0 : -1;
     constexpr int SCALE = PREC == kPrecF16 ? 5 : START ? 4 : 0;
-    tile_loop<TB, WAVES, PREC, SCALE, -1>(sh, buf + 2 * p.state_off, pool + p.op_off, p.args, u.t0, u.t1, 1, norm);
+    tile_loop<TB, WAVES, PREC, SCALE, -1, false>(sh, buf + 2 * p.state_off, pool + p.op_off, p.args, u.t0, u.t1, 1, norm);
 }
 
 template <int TB, int WAVES>
