@@ -123,6 +123,11 @@ inline int tile_min_qubits(int precision)
     return precision == SV_PREC_FP32 || precision == SV_PREC_SPLIT_BF16X3 || precision == SV_PREC_FP64 ? 10 : 14;
 }
 
+// Whether a block of k qubits on its own may run as a tile pass of one block.
+// Below 14 qubits a launch is host time, and a dense block's is shorter (FP64,
+// four qubits, 10 to 13 qubits: 16.4 us a call against 19.2 to 20.0).
+inline bool lone_block_may_tile(int k, int n) { return k <= 4 && n >= 14; }
+
 // Canonical matrix of a block from its member gates.
 void block_matrix(const sv_gate *g, Block &b);
 // Of all blocks, on several threads for large jobs.

@@ -546,7 +546,7 @@ int fuse_gates(const sv_gate *g, int G, int n, int max_k, int rule, const CostTa
         }
         merge_small_blocks(g, max_k, pass_fits, blocks);
         if (with_matrices) block_matrices(g, blocks);
-    return SV_OK;
+        return SV_OK;
     }
     std::vector<WBlock> wb;
     wb.reserve(G);
@@ -651,7 +651,7 @@ double tiled_plan_cost(const std::vector<Block> &blocks, int n, int precision, c
         }
         // a block alone runs as a one-block tile pass where that is cheaper
         const int k = blocks[grp[0]].k;
-        c += k <= 4 && n >= 14 ? std::min(cost.ms[k], cost.tile[1]) : cost.ms[k];
+        c += lone_block_may_tile(k, n) ? std::min(cost.ms[k], cost.tile[1]) : cost.ms[k];
     }
     return c;
 }

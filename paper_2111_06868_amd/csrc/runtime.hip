@@ -455,12 +455,10 @@ void group_tile_passes(const std::vector<Block> &blocks, int n, int precision, s
                 if (end > at && __builtin_popcountll(u) > tile_pass_bits(precision)) break;
             }
             // a block alone: its own dense launch, or a tile pass of one block
-            // where that is priced lower (below 14 qubits, where launches are
-            // short, only for FP64's four-qubit blocks)
-            const bool one = dev::tile_supported(n, 4) || (fp64 && n >= dev::kMinTileQubitsSmall && blocks[grp[at]].k == 4);
+            // where that is priced lower
             const Block &b0 = blocks[grp[at]];
             Launch L;
-            if (end - at == 1 && !(b0.k <= 4 && one && cost.tile[1] < cost.ms[b0.k])) {
+            if (end - at == 1 && !(lone_block_may_tile(b0.k, n) && cost.tile[1] < cost.ms[b0.k])) {
                 L.k = b0.k;
                 std::copy(b0.q, b0.q + SV_MAX_K, L.q);
                 L.path = choose_path(fp64 ? SV_C128 : SV_C64, precision, b0.k, b0.q, n);
