@@ -106,6 +106,8 @@ struct Tuning {
 };
 Tuning &tuning();
 Path choose_path(int dtype, int precision, int k, const int *sorted_q, int n);
+// Whether choose_path takes one output a thread where the register kernel could run.
+bool rows_beat_registers(int dtype, int k, int n);
 int path_family(Path p);
 
 // One block (or, for a tile path, a group of 4-qubit blocks) prepared for launch.

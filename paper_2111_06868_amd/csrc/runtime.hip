@@ -205,20 +205,24 @@ int tile_pass_capacity(int precision)
     return dev::tile_max_blocks(t.tile_bits, t.tile_waves, prec);
 }
 
+// Below the gate passes, and where MFMA does not reach, the register kernel's
+// few threads lose to one output a thread: FP64 k = 3 23 to 6 us, FP32 k = 4
+// (at most 8 qubits) 82 to 6.
+bool rows_beat_registers(int dtype, int k, int n)
+{
+    return k >= (dtype == SV_C128 ? 3 : 4) && n < dev::kMinTileQubits;
+}
+
 Path choose_path(int dtype, int precision, int k, const int *q, int n)
 {
-    // below the gate passes, and where MFMA does not reach, the register kernel's
-    // few threads lose to one output a thread: FP64 k = 3 23 to 6 us, FP32 k = 4
-    // (at most 8 qubits) 82 to 6
-    if (dtype == SV_C128)
-        return dev::reg_supported(dtype, k, q, n) && !(k >= 3 && n < dev::kMinTileQubits) ? PATH_REG : PATH_GENERIC;
+    const bool reg = dev::reg_supported(dtype, k, q, n) && !rows_beat_registers(dtype, k, n);
+    if (dtype == SV_C128) return reg ? PATH_REG : PATH_GENERIC;
     if (k >= 4 && dev::mfma_supported(k, n)) {
         if (precision == SV_PREC_SPLIT_BF16) return PATH_SPLIT_BF16;
         if (precision == SV_PREC_SPLIT_FP16) return PATH_SPLIT_FP16;
         if (!(k == 4 && tuning().k4_reg && dev::reg_supported(dtype, k, q, n))) return PATH_MFMA32;
     }
-    if (dev::reg_supported(dtype, k, q, n) && !(k >= 4 && n < dev::kMinTileQubits)) return PATH_REG;
-    return PATH_GENERIC;
+    return reg ? PATH_REG : PATH_GENERIC;
 }
 
 int path_family(Path p)

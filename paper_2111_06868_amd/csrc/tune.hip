@@ -331,14 +331,16 @@ extern "C" int sv_autotune(sv_state *s, int precision, double *cost_ms)
     cost_ms[0] = 0;
     Tuning best_tuning = tuning();
     for (int k = 1; k <= SV_MAX_K && !rc; ++k) {
-        std::vector<Cand> cands;
+        std::vector<Cand> cands;  // what choose_path can take
+        const bool rows = rows_beat_registers(s->dtype, k, s->n);
         if (s->dtype == SV_C128) {
-            if (k <= 3)
+            if (k <= 3 && !rows)
                 for (int c : caps) cands.push_back({PATH_REG, c, 0});
             else
                 cands.push_back({PATH_GENERIC, 0, 0});
         } else {
-            if (k <= 4)
+            if (k <= 4 && rows) cands.push_back({PATH_GENERIC, 0, 0});
+            else if (k <= 4)
                 for (int c : caps) cands.push_back({PATH_REG, c, 0});
             if (k >= 4 && dev::mfma_supported(k, s->n)) {
                 Path p = precision == SV_PREC_SPLIT_BF16 ? PATH_SPLIT_BF16
@@ -375,17 +377,19 @@ extern "C" int sv_autotune(sv_state *s, int precision, double *cost_ms)
             best_tuning.split_tc_log[k] = bc.tc_log;
             best_tuning.mfma_grid_cap[k] = bc.grid_cap;
         }
-        if (k == 4 && s->dtype == SV_C64 && precision == SV_PREC_FP32) best_tuning.k4_reg = bc.path == PATH_REG;
+        if (k == 4 && s->dtype == SV_C64 && precision == SV_PREC_FP32) best_tuning.k4_reg = bc.path != PATH_MFMA32;
     }
     double tile_ms[kTilePassMaxBlocks + 1] = {0};
-    const bool tiles = !rc && s->dtype == SV_C64 && dev::tile_supported(s->n, 8);
+    const bool tiles = !rc && s->n >= tile_min_qubits(precision);
     if (tiles) {
         tuning() = best_tuning;
         const Path tp = tile_path(precision);
-        // tile shape: the fastest pass of 4 blocks
+        // tile shape: the fastest pass of 4 blocks (FP64 passes and states below
+        // 14 qubits have shapes of their own)
         const int shapes[][2] = {{14, 8}, {14, 16}, {13, 4}, {13, 8}};
         double best_shape = 1e30;
         for (const auto &sh : shapes) {
+            if (s->dtype != SV_C64 || !dev::tile_supported(s->n, 8)) break;
             if (rc || !dev::tile_shape_supported(sh[0], sh[1]) || s->n < sh[0]) continue;
             tuning().tile_bits = sh[0];
             tuning().tile_waves = sh[1];
