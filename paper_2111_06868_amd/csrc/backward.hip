@@ -11,6 +11,7 @@
 
 #include <type_traits>
 
+#include "device.h"
 #include "kernels.h"
 
 namespace sv {
@@ -38,17 +39,6 @@ struct TransArgs {
     int nq;
     int q[SV_MAX_QUBITS_C64];
 };
-
-typedef float vf4 __attribute__((ext_vector_type(4)));
-typedef double vd2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void slot_amps(vf4 v, double (&re)[2], double (&im)[2])
-{
-    re[0] = v.x; im[0] = v.y; re[1] = v.z; im[1] = v.w;
-}
-__device__ __forceinline__ void slot_amps(vd2 v, double (&re)[1], double (&im)[1])
-{
-    re[0] = v.x; im[0] = v.y;
-}
 
 template <typename T, int LOGR>
 __global__ void __launch_bounds__(kRedThreads) k_transitions(const T *__restrict__ phi_, const T *__restrict__ lam_,

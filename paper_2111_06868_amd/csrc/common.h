@@ -83,15 +83,14 @@ int tile_pass_bits(int precision = -1);
 int tile_union_limit();
 void set_tile_union_limit(int u);
 // The tile of a pass whose blocks cover the positions U is U plus the lowest
-// positions outside it, tile_bits in all; its amplitudes lie in runs of
-// 2^tile_run_bits(U, tile_bits) consecutive ones (its positions 0, 1, .. in a
-// row).
-int tile_run_bits(uint64_t U, int tile_bits);
+// positions outside it, tile_bits in all; its amplitudes lie in runs of 2^r
+// consecutive ones, positions 0 .. r - 1 being in the tile.
 // The tiled rule lets a pass cover U when U fits a tile whose runs are at
 // least as long as those of any union of `limit` positions, 2^(tile_bits -
 // limit) amplitudes: every union of at most `limit` positions, and larger
 // ones that hold enough of the lowest positions.  States of fewer than
-// tile_bits qubits keep to `limit` positions.
+// tile_bits qubits keep to `limit` positions here; where tile passes hold such a
+// state whole (tile_min_qubits) the rule takes any union.
 // FP64 passes (13 tile bits of 16-byte amplitudes) have the runs, in bytes, of
 // 14 tile bits of complex64, so the same limit serves both.
 bool tile_union_fits(uint64_t U, int n, int tile_bits, int limit);

@@ -60,15 +60,6 @@ static int g_tile_union = [] {
 int tile_union_limit() { return g_tile_union; }
 void set_tile_union_limit(int u) { g_tile_union = std::min(std::max(u, 8), kTilePassMaxUnion); }
 
-int tile_run_bits(uint64_t U, int tile_bits)
-{
-    uint64_t t = U;
-    for (int p = 0; p < 64 && __builtin_popcountll(t) < tile_bits; ++p) t |= uint64_t(1) << p;
-    int r = 0;
-    while (r < 64 && ((t >> r) & 1)) ++r;
-    return r;
-}
-
 bool tile_union_fits(uint64_t U, int n, int tile_bits, int limit)
 {
     // a union of u <= limit positions leaves tile_bits - u fillers, and the
@@ -77,7 +68,7 @@ bool tile_union_fits(uint64_t U, int n, int tile_bits, int limit)
     if (u <= limit) return true;
     if (n < tile_bits || u > tile_bits) return false;
     // the tile_bits - u fillers must close every gap of U among the lowest
-    // tile_bits - limit positions (tile_run_bits(U, tile_bits) >= tile_bits - limit)
+    // tile_bits - limit positions
     const int run = tile_bits - limit;
     return run <= 0 || __builtin_popcountll(~U & ((uint64_t(1) << run) - 1)) <= tile_bits - u;
 }

@@ -17,6 +17,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "device.h"
 #include "kernels.h"
 
 namespace sv {
@@ -380,29 +381,9 @@ struct PauliTables {
     const double *tc;
 };
 
-// A read-only table entry through the scalar cache (uniform index).
-template <typename V>
-__device__ __forceinline__ V table(const V *p, int i)
-{
-    typedef const __attribute__((address_space(4))) V *cptr;
-    return reinterpret_cast<cptr>(reinterpret_cast<uintptr_t>(p))[i];
-}
-
 __device__ __forceinline__ double flip_sign(double v, uint32_t parity)
 {
     return __longlong_as_double(__double_as_longlong(v) ^ (uint64_t(parity) << 63));
-}
-
-// the amplitudes of a 16-byte slot, widened
-typedef float vfloat4 __attribute__((ext_vector_type(4)));
-typedef double vdouble2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void slot_amps(vfloat4 v, double (&re)[2], double (&im)[2])
-{
-    re[0] = v.x; im[0] = v.y; re[1] = v.z; im[1] = v.w;
-}
-__device__ __forceinline__ void slot_amps(vdouble2 v, double (&re)[1], double (&im)[1])
-{
-    re[0] = v.x; im[0] = v.y;
 }
 
 template <typename T, bool APPLY>
@@ -410,7 +391,7 @@ __global__ void __launch_bounds__(kPauliTileThreads, 4)
     k_pauli_tile(const T *__restrict__ psi_, T *__restrict__ out_, int slot_bits, int w, int g0, int g1, const PauliTables H,
                  double *__restrict__ partials, int add)
 {
-    using Slot = typename std::conditional<sizeof(T) == 4, vfloat4, vdouble2>::type;
+    using Slot = typename std::conditional<sizeof(T) == 4, vf4, vd2>::type;
     constexpr int PB = PauliTile<T>::PB, R = PauliTile<T>::R, NA = 1 << PB;
     __shared__ Slot X[1 << kPauliTileSlotBits];
     const Slot *__restrict__ psi = reinterpret_cast<const Slot *>(psi_);
@@ -446,10 +427,10 @@ __global__ void __launch_bounds__(kPauliTileThreads, 4)
 #pragma unroll
         for (int r = 0; r < R; ++r) sr[r] = si[r] = 0.0;
         for (int g = g0; g < g1; ++g) {
-            const uint64_t gx = table(H.gx, g);
+            const uint64_t gx = scalar_load(H.gx, g);
             const uint64_t x = gx & ~kPauliImag, xs = x >> PB;
             const bool imag = (gx & kPauliImag) != 0, swap = PB && (x & 1u);
-            const int t0 = table(H.goff, g), t1 = table(H.goff, g + 1);
+            const int t0 = scalar_load(H.goff, g), t1 = scalar_load(H.goff, g + 1);
             // a term's coefficient with its sign on this thread's amplitude r = 0
             // and the r bits (rr, position 0) that its z masks
             auto term = [&](uint64_t z, double c, uint32_t &zr) __attribute__((always_inline)) {
@@ -493,7 +474,7 @@ __global__ void __launch_bounds__(kPauliTileThreads, 4)
             auto group = [&](auto partner) __attribute__((always_inline)) {
                 if (t1 - t0 == 1) {
                     uint32_t zr;
-                    const double c = term(table(H.tz, t0), table(H.tc, t0), zr);
+                    const double c = term(scalar_load(H.tz, t0), scalar_load(H.tc, t0), zr);
                     if (zr == 0)
                         accumulate(partner, [&](int) { return c; });
                     else
@@ -510,8 +491,8 @@ __global__ void __launch_bounds__(kPauliTileThreads, 4)
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         const int tu = t + u < t1 ? t + u : t1 - 1;
-                        z[u] = table(H.tz, tu);
-                        c[u] = table(H.tc, tu);
+                        z[u] = scalar_load(H.tz, tu);
+                        c[u] = scalar_load(H.tc, tu);
                     }
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
@@ -612,7 +593,7 @@ __global__ void __launch_bounds__(256) k_weighted_bins(const T *__restrict__ psi
 {
     constexpr int NA = sizeof(T) == 4 ? 2 : 1;  // amplitudes of a 16-byte load
     constexpr int L = 8 / NA;
-    using Slot = typename std::conditional<sizeof(T) == 4, vfloat4, vdouble2>::type;
+    using Slot = typename std::conditional<sizeof(T) == 4, vf4, vd2>::type;
     __shared__ double tab[3][256];
     __shared__ double sums[1 << kBinTileBits];
     const int tid = threadIdx.x;

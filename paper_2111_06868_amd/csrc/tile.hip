@@ -25,6 +25,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "device.h"
 #include "kernels.h"
 
 namespace sv {
@@ -35,8 +36,6 @@ namespace {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef double vd2 __attribute__((ext_vector_type(2)));
-typedef float vf4 __attribute__((ext_vector_type(4)));
 typedef float vf2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -127,14 +126,6 @@ struct TileCfg {
     static_assert(THREADS <= 1024 && NB_PER_WAVE >= 1 && OP_AREA >= MAX_SUB * OPERAND_WORDS,
                   "tile shape");
 };
-
-// A read-only value through the scalar cache (uniform index).
-template <typename V>
-__device__ __forceinline__ V scalar_load(const V *p, uint32_t i)
-{
-    typedef const __attribute__((address_space(4))) V *cptr;
-    return reinterpret_cast<cptr>(reinterpret_cast<uintptr_t>(p))[i];
-}
 
 __device__ __forceinline__ uint32_t deposit(uint32_t v, uint32_t mask)
 {
@@ -343,9 +334,9 @@ __device__ __forceinline__ void norm_scale(double r, float &scale, float &unscal
 // Per-block data staged in LDS: the A operand and the swizzled column terms
 // of lane l32 and column block cb = w NBW + q of wave w: cq[cb] ^ cl[l32].
 // Column index c (deposited into the block's column bits, ascending):
-// FP32 c = 32 cb + l32; split c = (32 w + l32) NBW + q, which puts q on the
-// lowest column bits, so that when tile bit 0 is a column bit the column
-// blocks q and q + 1 of a lane share one 16-byte slot.
+// c = (32 w + l32) NBW + q, which puts q on the lowest column bits, so that
+// when tile bit 0 is a column bit the column blocks q and q + 1 of a lane share
+// one 16-byte slot.
 template <int TB, int WAVES, int LW>
 struct TileShared {
     using C = TileCfg<TB, WAVES, LW>;
@@ -500,10 +491,6 @@ __device__ __forceinline__ f32x16 mfma16(f16x8 a, f16x8 b, f32x16 c)
 __device__ __forceinline__ f32x4 mfma16x16(bf16x8 a, bf16x8 b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x4 mfma16x16(f16x8 a, f16x8 b, f32x4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
 __device__ __forceinline__ void lds_st4(char *Xb, uint32_t byte_off, float a, float b, float c, float d)
@@ -1457,8 +1444,8 @@ hipError_t make_tile_args(int n_sub, const int (*sub_pos)[4], int n, int tile_bi
             a.tbit[s][i] = t;
         }
     a.n_tiles = uint64_t(1) << (n - kTileBits);
-    // lanes of a wave take columns l32 NBW + q (split) or l32 (FP32), so a
-    // lane group's columns differ from column bit log2(NBW) (split) or 0 up
+    // lanes of a wave take columns l32 NBW + q, so a lane group's columns differ
+    // from column bit log2(NBW) up
     if (waves <= 0 || (1 << (tile_bits - 9)) % waves) return hipErrorInvalidValue;
     choose_tile_placement(a, tile_bits, waves, prec);
     return hipSuccess;
@@ -1478,7 +1465,9 @@ hipError_t launch_tile_pass(int n_sub, const int (*sub_pos)[4], const void *d_a,
     if (prec == kTileOperandF64) {
         // virtual position 0 is re / im: every position moves up by one
         if (n_sub < 1 || n_sub > tile_max_blocks(kF64TileBits, kF64TileWaves, prec)) return hipErrorInvalidValue;
-        if (tile_bits != kF64TileBits && tile_bits != 13 && !small_shape(tile_bits, waves)) return hipErrorInvalidValue;
+        // n >= 10 and the virtual position: 11 tile bits at least
+        if (tile_bits != kF64TileBits && tile_bits != 13 && !(tile_bits > 10 && small_shape(tile_bits, waves)))
+            return hipErrorInvalidValue;
         int pos[kMaxTileSubBlocks][4];
         for (int s = 0; s < n_sub; ++s)
             for (int i = 0; i < 4; ++i) pos[s][i] = sub_pos[s][i] + 1;
@@ -1489,7 +1478,6 @@ hipError_t launch_tile_pass(int n_sub, const int (*sub_pos)[4], const void *d_a,
         TileNorm nv = norm;
         if (nv.basis >= 0) nv.basis <<= 1;
         float *p = static_cast<float *>(psi), *p2 = static_cast<float *>(psi2);
-        if (tile_bits == 10) return tile_launch<10, 1>(a, d_a, prec, p, p2, st, grid_cap, nv, grid_out);
         if (tile_bits == 11) return tile_launch<11, 2>(a, d_a, prec, p, p2, st, grid_cap, nv, grid_out);
         if (tile_bits == 12) return tile_launch<12, 4>(a, d_a, prec, p, p2, st, grid_cap, nv, grid_out);
         if (tile_bits == 13) return tile_launch<13, 8>(a, d_a, prec, p, p2, st, grid_cap, nv, grid_out);
