@@ -521,12 +521,29 @@ int group_gate_passes(std::vector<Launch> &launches, int n, int dtype)
     if (n < dev::kMinTileQubits) return SV_OK;
     const int precision = dtype == SV_C64 ? SV_PREC_FP32 : SV_PREC_FP64;
     auto small = [](const Launch &L) { return L.path == PATH_REG && L.k <= 3; };
+    // Below 20 qubits a launch is host time, and a pass takes more of it than a
+    // gate does: 11 us more than the first launch, against what a further gate in
+    // the pass saves, about 3, 2 and 4 us for one, two and three qubits
+    // (complex128, whose register kernel is slower: 4, 4 and 11).  16 qubits,
+    // launches against passes: two H 17 and 23 us, four 25 and 25, eight 38 and
+    // 31; three FSIM 24 and 28, six 37 and 36, ten 54 and 48.
+    const int gain[4] = {0, dtype == SV_C64 ? 3 : 4, dtype == SV_C64 ? 2 : 4, dtype == SV_C64 ? 4 : 11};
+    auto worth = [&](int sum) { return n >= 20 || sum >= 11; };
+    int longest = 0, run = 0, count = 0;
+    for (const Launch &L : launches) {
+        run = small(L) ? run + gain[L.k] : 0;
+        count = small(L) ? count + 1 : 0;
+        if (count >= 2) longest = std::max(longest, run);
+    }
+    if (longest == 0 || !worth(longest)) return SV_OK;
     std::vector<Launch> out;
     for (size_t at = 0; at < launches.size();) {
         size_t end = at;
-        while (end < launches.size() && small(launches[end])) ++end;
-        if (end - at < 2) {
-            out.push_back(std::move(launches[at++]));
+        int saved = 0;
+        for (; end < launches.size() && small(launches[end]); ++end) saved += gain[launches[end].k];
+        if (end - at < 2 || !worth(saved)) {
+            do out.push_back(std::move(launches[at++]));
+            while (at < end);
             continue;
         }
         // stages and passes of the run: blocks of <= 4 positions in tile passes
@@ -541,8 +558,13 @@ int group_gate_passes(std::vector<Launch> &launches, int n, int dtype)
         for (const auto &grp : tile_groups(blocks, n, precision))
             for (size_t c = 0; c < grp.size(); c += cap) {
                 const size_t stop = std::min(grp.size(), c + cap);
-                if (stop - c == 1 && blocks[grp[c]].members.size() == 1) {  // a gate alone
-                    out.push_back(std::move(launches[at + size_t(blocks[grp[c]].members[0])]));
+                size_t count = 0;
+                int pass_saved = 0;
+                for (size_t i = c; i < stop; ++i)
+                    for (int mem : blocks[grp[i]].members) ++count, pass_saved += gain[launches[at + size_t(mem)].k];
+                if (count == 1 || !worth(pass_saved)) {  // the gates alone
+                    for (size_t i = c; i < stop; ++i)
+                        for (int mem : blocks[grp[i]].members) out.push_back(std::move(launches[at + size_t(mem)]));
                     continue;
                 }
                 Launch P;
