@@ -1546,6 +1546,19 @@ int plan_daggers(const sv_state *s, int prec, DaggerPlan &p)
     const std::vector<sv_gate> &dg = p.dg;
     const int cnt = int(dg.size()), kmax = p.kmax;
     std::vector<Block> &blocks = p.blocks;
+    // gates on at most three qubits: one block, which the register kernel applies
+    // to both states at the rate of a copy, and with which a single qubit's sums
+    // share a launch (launch_transition_step)
+    uint64_t on = 0;
+    for (const sv_gate &x : dg)
+        for (int j = 0; j < x.k; ++j) on |= uint64_t(1) << x.q[j];
+    if (__builtin_popcountll(on) <= 3) {
+        blocks.resize(1);
+        for (uint64_t m = on; m; m &= m - 1) blocks[0].q[blocks[0].k++] = __builtin_ctzll(m);
+        blocks[0].members.resize(size_t(cnt));
+        std::iota(blocks[0].members.begin(), blocks[0].members.end(), 0);
+        return SV_OK;
+    }
     const CostTable cost = lookup_costs(s->n, prec, nullptr);
     // The plan of a run (dense blocks of the cheapest k, or tile passes)
     // depends on its gates' positions and the cost table only; it is
@@ -1619,6 +1632,14 @@ size_t operand_bound(const DaggerPlan &p, int prec)
         total += 256 + std::max({tile, split ? 6 * form + 512 : 4 * form, 16 * D2});
     }
     return total;
+}
+
+// Whether the sums of a step and its launches are one pass: one qubit with
+// parameters, one dense block of at most three qubits that holds it.
+bool one_pass(const BwdStep &st, const std::vector<Launch> &out)
+{
+    return st.qubits.size() == 1 && out.size() == 1 && !is_tile_path(out[0].path) && out[0].k <= 3 &&
+           std::count(out[0].q, out[0].q + out[0].k, st.qubits[0]);
 }
 
 // The launches of a plan, whose blocks' matrices are formed here.
@@ -1771,16 +1792,29 @@ int backward_impl(sv_state *psi, sv_state *scratch, const sv_gate *g, int G, con
         });
         std::vector<Launch> launches;
         std::vector<size_t> end;  // of each step's launches
-        for (auto &out : outs) {
+        std::vector<char> together;
+        for (size_t t = from; t < to; ++t) {
+            auto &out = outs[t - from];
+            together.push_back(one_pass(steps[t], out));
+            if (together.back()) out[0].path = PATH_REG;  // the matrix is an argument
             for (auto &L : out) launches.push_back(std::move(L));
             end.push_back(launches.size());
         }
-        SV_HIP(hipEventSynchronize(at->arena_free));
-        const size_t bytes = pack_operands(launches, psi->dtype, at->stage);
+        // only blocks of other kernels than the register kernel have operands
+        const bool operands = std::any_of(launches.begin(), launches.end(), [](const Launch &L) { return L.path != PATH_REG; });
+        if (operands) SV_HIP(hipEventSynchronize(at->arena_free));
+        const size_t bytes = operands ? pack_operands(launches, psi->dtype, at->stage) : 0;
         if (bytes > at->arena.cap) return fail(SV_ERR_HIP, "operands of %zu bytes in an arena of %zu", bytes, at->arena.cap);
         if (bytes) SV_HIP(hipMemcpyAsync(at->arena.p, at->stage.p, bytes, hipMemcpyHostToDevice, psi->stream));
         for (size_t t = from, l = 0; t < to; l = end[t++ - from]) {
             const BwdStep &st = steps[t];
+            const Launch *L = launches.data() + l;
+            if (together[t - from]) {
+                LaunchTimer timer(stat_class(FAM_ADJOINT, L->k), psi->stream);
+                SV_HIP(dev::launch_transition_step(psi->dtype, L->k, L->q, L->m.data(), st.qubits[0], psi->buf,
+                                                   scratch->buf, psi->n, part, st.slot, psi->stream));
+                continue;
+            }
             if (!st.qubits.empty()) {
                 LaunchTimer timer(stat_class(FAM_ADJOINT, 3), psi->stream);
                 SV_HIP(dev::launch_transitions(psi->dtype, int(st.qubits.size()), st.qubits.data(), psi->buf,
@@ -1796,7 +1830,7 @@ int backward_impl(sv_state *psi, sv_state *scratch, const sv_gate *g, int G, con
     // after a failed launch too, nothing may touch the arenas or the scratch
     // state before what is in flight
     SV_HIP(hipEventRecord(scratch->arena_free, psi->stream));
-    if (!swept) swept = sweep(ahead, steps.size(), psi);
+    if (!swept && ahead < steps.size()) swept = sweep(ahead, steps.size(), psi);
     SV_HIP(hipEventRecord(psi->arena_free, psi->stream));
     if (swept) {
         const std::string msg = last_error_cstr();

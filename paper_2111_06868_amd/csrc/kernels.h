@@ -268,6 +268,10 @@ constexpr int kTransQubits = 4;  // qubits per workgroup
 int transition_blocks(int n);
 hipError_t launch_transitions(int dtype, int nq, const int *q, const void *phi, const void *lam, int n,
                               double *d_partials, int slot0, hipStream_t st);
+// The same of one qubit (slot `slot`), then U on phi and on lam, U canonical on
+// the k <= 3 ascending positions sorted_q, the qubit among them: one pass.
+hipError_t launch_transition_step(int dtype, int k, const int *sorted_q, const cd *m, int qubit, void *phi, void *lam,
+                                  int n, double *d_partials, int slot, hipStream_t st);
 hipError_t launch_transitions_final(const double *d_partials, int n_slots, int n, double *out, hipStream_t st);
 
 // ------------------------------------------------------------------ batches
