@@ -279,7 +279,7 @@ int choose_plan_uncached(const sv_gate *g, int G, int n, int dtype, int precisio
     return SV_OK;
 }
 
-int pauli_tables(sv_state *s, const sv_pauli_sum *H, int n, dev::PauliDev &P);
+int pauli_tables(sv_state *s, const sv_pauli_sum *H, int n, PauliUse use, dev::PauliDev &P);
 
 }  // namespace
 
@@ -752,12 +752,12 @@ size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Group the terms, stage the tables and upload them into the arena.
 // The caller synchronised arena_free and records it after its launches.
-int pauli_tables(sv_state *s, const sv_pauli_sum *H, int n, dev::PauliDev &P)
+int pauli_tables(sv_state *s, const sv_pauli_sum *H, int n, PauliUse use, dev::PauliDev &P)
 {
     const size_t total = pauli_table_bytes(H);
     SV_HIP(s->stage.ensure(total));
     SV_HIP(s->arena.ensure(total));
-    pauli_table_fill(H, n, s->dtype, static_cast<char *>(s->stage.p), static_cast<const char *>(s->arena.p), P);
+    pauli_table_fill(H, n, s->dtype, use, static_cast<char *>(s->stage.p), static_cast<const char *>(s->arena.p), P);
     SV_HIP(hipMemcpyAsync(s->arena.p, s->stage.p, total, hipMemcpyHostToDevice, s->stream));
     return SV_OK;
 }
@@ -815,19 +815,31 @@ int count_groups(const sv_pauli_sum *H)
 
 size_t pauli_table_bytes(const sv_pauli_sum *H) { return PauliLayout(count_groups(H), H->n_terms).total; }
 
-void pauli_table_fill(const sv_pauli_sum *H, int n, int dtype, char *h, const char *d, dev::PauliDev &P)
+void pauli_table_fill(const sv_pauli_sum *H, int n, int dtype, PauliUse use, char *h, const char *d, dev::PauliDev &P)
 {
     const int nt = H->n_terms;
     P.n_pass = dev::pauli_passes(n, dtype, P.pass_w);
-    std::vector<int> order(nt), pass(nt);
+    std::vector<int> order(nt), pass(nt, 0);
     std::vector<uint64_t> group(nt);
     for (int t = 0; t < nt; ++t) {
         order[t] = t;
         group[t] = pauli_group(H, t);
-        pass[t] = dev::pauli_pass_of(H->xmask[t], dtype, P.n_pass, P.pass_w);
     }
+    {
+        std::vector<uint64_t> distinct(group);
+        std::sort(distinct.begin(), distinct.end());
+        distinct.erase(std::unique(distinct.begin(), distinct.end()), distinct.end());
+        dev::pauli_choose(n, dtype, nt, distinct.data(), int(distinct.size()), P);
+    }
+    // the tiled kernels take the groups by pass; a thread of the others gathers
+    // them in the order of their masks
+    const bool tiled = use == PAULI_EXPECT ? P.tile_expect : use == PAULI_APPLY && P.tile_apply;
+    if (tiled)
+        for (int t = 0; t < nt; ++t) pass[t] = dev::pauli_pass_of(H->xmask[t], dtype, P.n_pass, P.pass_w);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-        return pass[a] != pass[b] ? pass[a] < pass[b] : group[a] < group[b];
+        if (pass[a] != pass[b]) return pass[a] < pass[b];
+        if (!tiled && H->xmask[a] != H->xmask[b]) return H->xmask[a] < H->xmask[b];
+        return group[a] < group[b];
     });
     std::vector<uint64_t> gx;
     std::vector<int32_t> goff;
@@ -907,7 +919,7 @@ extern "C" int sv_expectation(sv_state *s, const sv_pauli_sum *H, double *out)
     if (int rc = select_device(s)) return rc;
     SV_HIP(hipEventSynchronize(s->arena_free));
     dev::PauliDev P;
-    if (int rc = pauli_tables(s, H, s->n, P)) return rc;
+    if (int rc = pauli_tables(s, H, s->n, PAULI_EXPECT, P)) return rc;
     double *part = static_cast<double *>(s->red.p), *res = nullptr;
     if (int rc = result_slots(s, 1, &res)) return rc;
     {
@@ -933,7 +945,7 @@ extern "C" int sv_dm_expectation(sv_state *rho, const sv_pauli_sum *H, double *o
     if (int rc = select_device(rho)) return rc;
     SV_HIP(hipEventSynchronize(rho->arena_free));
     dev::PauliDev P;
-    if (int rc = pauli_tables(rho, H, n, P)) return rc;
+    if (int rc = pauli_tables(rho, H, n, PAULI_TRACE, P)) return rc;
     double *part = static_cast<double *>(rho->red.p), *res = nullptr;
     if (int rc = result_slots(rho, 1, &res)) return rc;
     {
@@ -1435,7 +1447,7 @@ extern "C" int sv_apply_pauli_sum(sv_state *psi, const sv_pauli_sum *H, sv_state
     if (H->n_terms == 0) {
         SV_HIP(dev::launch_fill_basis(out->dtype, out->buf, out->n, ~uint64_t(0), psi->stream));
     } else {
-        if (int rc = pauli_tables(psi, H, psi->n, P)) return rc;
+        if (int rc = pauli_tables(psi, H, psi->n, PAULI_APPLY, P)) return rc;
         LaunchTimer t(stat_class(FAM_REDUCE, 4), psi->stream);
         SV_HIP(dev::launch_pauli_apply(psi->dtype, psi->buf, out->buf, psi->n, P, psi->stream));
     }

@@ -223,11 +223,15 @@ struct PauliDev {
     int n_pass;
     int pass_w[kPauliMaxPasses];
     int pass_end[kPauliMaxPasses];
+    bool tile_expect, tile_apply;  // whether the tiled kernels run (pauli_choose)
 };
 // The windows (first slot bit) of the tiled kernels' passes over an n-qubit
 // state, and the first of them whose tile holds x (0 when none does).
 int pauli_passes(int n, int dtype, int *w);
 int pauli_pass_of(uint64_t x, int dtype, int n_pass, const int *w);
+// Choose the kernels for n_terms terms in groups gx[0..n_groups) (H.n_pass and
+// H.pass_w are set).
+void pauli_choose(int n, int dtype, int n_terms, const uint64_t *gx, int n_groups, PauliDev &H);
 hipError_t launch_pauli_expect(int dtype, const void *psi, int n, const PauliDev &H, double *d_partials,
                                double *d_out, hipStream_t st);
 hipError_t launch_pauli_apply(int dtype, const void *psi, void *out, int n, const PauliDev &H,

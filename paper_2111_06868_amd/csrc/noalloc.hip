@@ -64,7 +64,7 @@ extern "C" int sv_expectation_noalloc(const void *dev_psi, int n, int dtype, voi
     if (int rc = scratch_on(dev, &base)) return rc;
     const hipStream_t st = static_cast<hipStream_t>(hip_stream);
     sv::dev::PauliDev P;
-    sv::pauli_table_fill(H, n, dtype, g_host, base, P);
+    sv::pauli_table_fill(H, n, dtype, sv::PAULI_EXPECT, g_host, base, P);
     double *part = reinterpret_cast<double *>(base + kTableBytes);
     double *res = part + sv::dev::kRedBlocks;
     double host_res = 0.0;

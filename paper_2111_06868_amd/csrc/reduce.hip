@@ -749,7 +749,7 @@ template <typename T>
 hipError_t pauli_expect_t(const T *psi, int n, const PauliDev &H, double *d_partials, double *d_out, hipStream_t st)
 {
     unsigned blocks;
-    if (n >= kPauliTileMin) {
+    if (H.tile_expect) {
         const int slot_bits = n - PauliTile<T>::PB;
         blocks = pauli_tile_grid(slot_bits, kRedBlocks);
         int add = 0;
@@ -772,14 +772,14 @@ hipError_t pauli_expect_t(const T *psi, int n, const PauliDev &H, double *d_part
 template <typename T>
 hipError_t pauli_apply_t(const T *psi, T *out, int n, const PauliDev &H, hipStream_t st)
 {
-    if (n >= kPauliTileMin) {
+    if (H.tile_apply) {
         const int slot_bits = n - PauliTile<T>::PB;
         hipLaunchKernelGGL((k_pauli_tile<T, true>), dim3(pauli_tile_grid(slot_bits, 512)), dim3(kPauliTileThreads), 0, st,
                            psi, out, slot_bits, 3, 0, H.n_groups, PauliTables{H.gx, H.goff, H.tz, H.tc},
                            static_cast<double *>(nullptr), 0);
     } else {
-        const uint64_t N = uint64_t(1) << n;
-        hipLaunchKernelGGL(k_pauli_apply<T>, dim3(unsigned((N + 255) / 256)), dim3(256), 0, st, psi, out, N, H);
+        const uint64_t N = uint64_t(1) << n, b = (N + 255) / 256;
+        hipLaunchKernelGGL(k_pauli_apply<T>, dim3(unsigned(b < 16384 ? b : 16384)), dim3(256), 0, st, psi, out, N, H);
     }
     return hipGetLastError();
 }
@@ -804,6 +804,45 @@ int pauli_pass_of(uint64_t x, int dtype, int n_pass, const int *w)
     for (int p = 0; p < n_pass; ++p)
         if (!(xs & ~(uint64_t(7) | uint64_t(kPauliWinMask) << w[p]))) return p;
     return 0;
+}
+
+// Where the tiled kernels win.  An amplitude's thread costs 9 us a term and 9 us
+// a group at 24 qubits of complex64 (the gather), hidden behind the reading of
+// the state up to some 3 terms; a tile 20 us more than reading the state, 1.5 us a
+// term and, for a group that no window holds, the same gather.  So what counts
+// is terms and, twice, groups that the window holds; measured for one to 40
+// terms on one X mask, on a position each, and random (us, amplitudes and tiles):
+//   complex64, H psi: 24 qubits, Z terms, four 67 and 76, eight 103 and 78; X
+//     terms, two 60 and 74, four 95 and 87; random, four 98 and 127, eight 174
+//     and 166; 19 qubits, 16 X terms 27 and 27.
+//   complex128: gathers of 16 bytes a lane gain nothing (24 qubits, 24 random
+//     terms 668 and 734; eight Z 108 and 119, sixteen 176 and 122), until the
+//     state outgrows the memory-side cache (26 qubits, two random 705 and 583).
+//   <H>: a pass per window and one for the groups of none; two or three terms of
+//     which half are in none read the state too often (24 qubits, two random
+//     terms, complex64 84 and 95, complex128 84 and 133).
+void pauli_choose(int n, int dtype, int n_terms, const uint64_t *gx, int n_groups, PauliDev &H)
+{
+    const bool c64 = dtype == SV_C64;
+    int near = 0, none = 0;  // groups in H psi's window, groups in no window of <H>
+    for (int g = 0; g < n_groups; ++g) {
+        const uint64_t xs = (gx[g] & ~kPauliImag) >> (c64 ? 1 : 0);
+        bool any = false;
+        for (int p = 0; p < H.n_pass; ++p) {
+            const bool in = !(xs & ~(uint64_t(7) | uint64_t(kPauliWinMask) << H.pass_w[p]));
+            any = any || in;
+            if (p == 0) near += in;
+        }
+        none += !any;
+    }
+    const int far = n_groups - near;
+    bool apply;
+    if (c64) apply = n_terms + 2 * near >= (n == 19 ? 40 : n >= 23 && n <= 25 ? 7 : 6);
+    else if (n <= 21) apply = true;
+    else if (n <= 25) apply = n_terms + 4 * near - 4 * far >= 12;
+    else apply = n_terms > 1 || near > 0;
+    H.tile_apply = n >= kPauliTileMin && apply;
+    H.tile_expect = n >= kPauliTileMin && !(2 * none >= n_groups && n_terms <= (c64 ? 2 : 3) && n >= (c64 ? 24 : 22));
 }
 
 hipError_t launch_pauli_expect(int dtype, const void *psi, int n, const PauliDev &H, double *d_partials,

@@ -173,7 +173,8 @@ int load_tuning(const char *path, int device, int *loaded);
 // d: their byte size, and the fill, which also points P at d.
 int check_pauli(const sv_pauli_sum *H, int n);
 size_t pauli_table_bytes(const sv_pauli_sum *H);
-void pauli_table_fill(const sv_pauli_sum *H, int n, int dtype, char *h, const char *d, dev::PauliDev &P);
+enum PauliUse { PAULI_EXPECT, PAULI_APPLY, PAULI_TRACE };  // the kernel that reads the tables
+void pauli_table_fill(const sv_pauli_sum *H, int n, int dtype, PauliUse use, char *h, const char *d, dev::PauliDev &P);
 
 }  // namespace sv
 
