@@ -177,16 +177,33 @@ bool tiles_are_cheaper(const std::vector<Block> &blocks, const std::vector<Block
     const CostTable cost = lookup_costs(n, precision, nullptr);
     return tiled_plan_cost(tiled, n, precision, cost) < plan_cost(blocks, cost) - 1e-12;
 }
+// Whether a plan has blocks that tile passes would replace, and no gate that
+// is wider than theirs.
+bool may_be_tiles(const sv_gate *g, int G, const std::vector<Block> &blocks)
+{
+    bool wide = false;
+    for (const auto &b : blocks) wide = wide || b.k >= 4;
+    for (int i = 0; i < G; ++i) wide = wide && g[i].k <= 4;
+    return wide;
+}
 // The tile passes of the gates of a plan (positions and members, no matrices),
-// or none where one of its gates or all of its blocks rule them out.
+// or none where they are ruled out.
 int gates_as_tiles(const sv_gate *g, int G, int n, int precision, const std::vector<Block> &blocks,
                    std::vector<Block> &tiled)
 {
     tiled.clear();
-    bool wide = false;
-    for (const auto &b : blocks) wide = wide || b.k >= 4;
-    for (int i = 0; i < G; ++i) wide = wide && g[i].k <= 4;
-    return wide ? fuse_gates(g, G, n, 4, SV_RULE_TILED, default_costs(), tiled, false, precision) : SV_OK;
+    if (!may_be_tiles(g, G, blocks)) return SV_OK;
+    return fuse_gates(g, G, n, 4, SV_RULE_TILED, default_costs(), tiled, false, precision);
+}
+// The tile passes of a kept plan's gates, once for all threads that apply it:
+// a program that only reads a plan does not pay for them.
+int plan_tiles(const sv_plan *p)
+{
+    std::call_once(p->tiles_formed, [p] {
+        p->tiles_rc = fuse_gates(p->gates.data(), int(p->gates.size()), p->n, 4, SV_RULE_TILED, default_costs(), p->tiled,
+                                 true, p->precision);
+    });
+    return p->tiles_rc;
 }
 
 int choose_plan_uncached(const sv_gate *g, int G, int n, int dtype, int precision, int rule, int max_k, bool found,
@@ -508,11 +525,24 @@ int fuse_plan(const sv_gate *g, int G, int n, int max_k, int rule, int precision
     p->max_k = max_k;
     p->rule = rule;
     int rc = fuse_gates(g, G, n, max_k, rule, lookup_costs(n, cost_prec, nullptr), p->blocks, true, precision);
-    if (!rc && takes_tiles(rule, cost_prec, n)) rc = gates_as_tiles(g, G, n, precision, p->blocks, p->tiled);
-    if (!rc) block_matrices(g, p->tiled);
     if (rc) {
         delete p;
         return rc;
+    }
+    p->precision = precision;
+    if (takes_tiles(rule, cost_prec, n) && may_be_tiles(g, G, p->blocks)) {
+        p->gates.assign(g, g + G);
+        size_t at = 0;
+        for (int i = 0; i < G; ++i)
+            if (g[i].kind == SV_G_MATRIX) at += size_t(2) << (2 * g[i].k);
+        p->matrices.resize(at);
+        at = 0;
+        for (sv_gate &x : p->gates)
+            if (x.kind == SV_G_MATRIX) {
+                const size_t count = size_t(2) << (2 * x.k);
+                x.m = static_cast<const double *>(std::memcpy(p->matrices.data() + at, x.m, count * sizeof(double)));
+                at += count;
+            }
     }
     *out = p;
     return SV_OK;
@@ -633,8 +663,11 @@ extern "C" int sv_apply_plan(sv_state *s, const sv_plan *p, int precision, int u
             if (int rc = check_unitary(p->blocks[i].m, p->blocks[i].k, what.c_str())) return rc;
         }
     std::vector<Launch> L;
-    const bool tiles = !p->own_blocks && !p->tiled.empty() && takes_tiles(p->rule, precision, s->n) &&
-                       tiles_are_cheaper(p->blocks, p->tiled, s->n, precision);
+    bool tiles = !p->own_blocks && !p->gates.empty() && takes_tiles(p->rule, precision, s->n);
+    if (tiles) {
+        if (int rc = plan_tiles(p)) return rc;
+        tiles = tiles_are_cheaper(p->blocks, p->tiled, s->n, precision);
+    }
     if (int rc = blocks_to_launches(tiles ? p->tiled : p->blocks, s, precision, tiles ? SV_RULE_TILED : p->rule, L,
                                     p->own_blocks))
         return rc;

@@ -3,6 +3,7 @@
 
 #include <complex>
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -162,8 +163,15 @@ struct sv_plan {
     int max_k = 0;
     int rule = 0;
     std::vector<sv::Block> blocks;
-    std::vector<sv::Block> tiled;  // the same gates as tile passes, or empty (gates_as_tiles)
-    bool own_blocks = false;       // apply `blocks` as they are, one launch each (sv_plan_own_blocks)
+    // The same gates as tile passes, formed when the plan is first applied where
+    // they may run (plan_tiles); empty where they may not.
+    std::vector<sv_gate> gates;       // copied, with their matrices, where they may
+    std::vector<double> matrices;
+    int precision = -1;               // as sv_fuse_prec was told
+    mutable std::once_flag tiles_formed;
+    mutable int tiles_rc = SV_OK;
+    mutable std::vector<sv::Block> tiled;
+    bool own_blocks = false;          // apply `blocks` as they are, one launch each (sv_plan_own_blocks)
     // device-side cache (filled by the runtime when the plan is applied)
     void *cache = nullptr;
 };
