@@ -488,8 +488,8 @@ def _super_op_array(ops) -> ctypes.Array:
     entries point into the SuperOps' arrays, which the array keeps alive."""
     arr = (N.sv_super_op * max(len(ops), 1))()
     plain = lambda a: a is None or (a.dtype.char == "D" and a.flags.c_contiguous)
-    if not all(type(op) is SuperOp and plain(op.left) and (op.right is op.left or plain(op.right)) and plain(op.s)
-               and plain(op.superop) for op in ops):
+    if not all(type(op) is SuperOp and type(op.qubits) is tuple and plain(op.left) and plain(op.s) and
+               (op.right is op.left or plain(op.right)) and plain(op.superop) for op in ops):
         arr.keep = []
         for j, op in enumerate(ops):
             op.fill(arr[j], arr.keep)
