@@ -540,8 +540,13 @@ int group_gate_passes(std::vector<Launch> &launches, int n, int dtype)
     for (size_t at = 0; at < launches.size();) {
         size_t end = at;
         int saved = 0;
-        for (; end < launches.size() && small(launches[end]); ++end) saved += gain[launches[end].k];
-        if (end - at < 2 || !worth(saved)) {
+        uint64_t on = 0;
+        for (; end < launches.size() && small(launches[end]); ++end) {
+            saved += gain[launches[end].k];
+            for (int j = 0; j < launches[end].k; ++j) on |= uint64_t(1) << launches[end].q[j];
+        }
+        // planning costs as well: more positions than a pass takes are two passes
+        if (end - at < 2 || !worth(__builtin_popcountll(on) > tile_union_limit() ? saved / 2 : saved)) {
             do out.push_back(std::move(launches[at++]));
             while (at < end);
             continue;
