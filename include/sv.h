@@ -59,7 +59,8 @@ extern "C" {
 /* arithmetic used to apply fused blocks (sv_run_opts.precision) */
 #define SV_PREC_FP32 0       /* complex64 state; FP32 matvec / FP32 MFMA; tile     */
                              /* passes as SV_PREC_SPLIT_BF16X3 (closer to 64-bit   */
-                             /* values than FP32 MFMA)                             */
+                             /* values than FP32 MFMA down to amplitudes of 1e-33, */
+                             /* whose third BF16 part leaves FP32's normal range)  */
 #define SV_PREC_SPLIT_BF16 1 /* complex64 state; k>=4 blocks as hi+lo BF16 MFMA    */
 #define SV_PREC_SPLIT_FP16 2 /* complex64 state; k>=4 blocks as hi+lo FP16 MFMA;   */
                              /* MATRIX gates must be unitary (to 1e-6), else       */
@@ -253,7 +254,8 @@ int sv_plan_own_blocks(sv_plan *p, int on);
  * (SV_PREC_SPLIT_BF16X3 likewise) and FP64, a plan of the paper or enhanced rule
  * with blocks of four and more qubits runs as tile passes of the same gates
  * (every qubit keeps its gate order) where the cost table prices those lower,
- * on states of >= 14 qubits and with no gate of more than four.  With
+ * on states of >= 10 qubits and with no gate of more than four (formed when the
+ * plan is first applied so; sv_plan_own_blocks asks for the plan's own).  With
  * use_graph = 1 the launches are captured into a hipGraph and launched as one;
  * the state keeps the instantiated graph, and a later call whose launches have
  * the same structure (block positions, kernels, launch shapes; the matrices
@@ -268,18 +270,22 @@ int sv_apply_plan(sv_state *s, const sv_plan *p, int precision, int use_graph);
  * 'evolution')).  Nothing is applied if any gate is invalid.  Asynchronous
  * (use_graph as for sv_apply_plan).  o == NULL means plain per-gate
  * application: {SV_MAX_K, FP32 or FP64 by amplitude type, SV_RULE_NONE, 0}.
- * With SV_RULE_TILED on a state of >= 14 qubits, in FP32 (SV_PREC_SPLIT_BF16X3
- * likewise) and FP64 of >= 10 (complex64 below; complex128 likewise, with FP64
- * MFMA and tiles of 2^13 amplitudes; small states take smaller tiles), the gates are
- * grouped into passes whose positions U leave contiguous HBM runs no shorter
+ * SV_RULE_TILED groups the gates into tile passes on states of at least
+ *   10 qubits in SV_PREC_FP32, SV_PREC_SPLIT_BF16X3 and SV_PREC_FP64,
+ *   14 qubits in SV_PREC_SPLIT_BF16 and SV_PREC_SPLIT_FP16;
+ * smaller states take a launch for each block.  A tile has 2^14 amplitudes of
+ * complex64 (2^13 with a set shape of 13 bits) or 2^13 of complex128, or, with
+ * the default shape, on states of at most 21 qubits 2^10 to 2^13 of either where
+ * the pass's positions U fit.  U leaves contiguous HBM runs no shorter
  * than those of a union of sv_set_tile_union() positions (default 10): the
  * tile of a pass is U plus the lowest positions outside it, 14 (or 13) in
  * all, and its runs, 2^r amplitudes with r its lowest positions 0, 1, .. in
  * a row, must hold at least 2^(tile bits - limit); so every union of <= 10
- * positions qualifies, and up to 14 when U holds the lowest positions.  Each
+ * positions qualifies, and up to a whole tile when U holds the lowest positions;
+ * in a state that one tile holds, every U.  Each
  * pass is fused into blocks of <= 4 qubits
  * (gates move only where every qubit keeps its own gate order).  Each tile
- * of 2^14 (or 2^13) amplitudes is staged in LDS once, every block of the
+ * is staged in LDS once, every block of the
  * pass is applied to it (SV_PREC_FP32: as SV_PREC_SPLIT_BF16X3; SV_PREC_SPLIT_BF16 /
  * SV_PREC_SPLIT_FP16: hi+lo 16-bit MFMA, the FP16 values scaled by a power of
  * two, chosen per tile from its largest magnitude in the call's first FP16
@@ -593,8 +599,9 @@ int sv_get_tile_shape(int *tile_bits, int *waves, int *max_blocks);
  * over the set bits b of i, a permutation of 0 .. 2^tile_bits - 1 that keeps
  * bit 0; it is chosen per pass so that the 16-byte LDS accesses of the
  * blocks hit distinct banks.  *conflicts (may be NULL) receives the extra
- * LDS cycles left by that choice (0 when it is free of bank conflicts; 0
- * for FP32).  Errors: SV_ERR_ARG. */
+ * LDS cycles left by that choice (0 when it is free of bank conflicts).
+ * Errors: SV_ERR_ARG (also for SV_PREC_FP64, whose passes are laid out as those
+ * of a complex64 state of one position more). */
 int sv_tile_placement(int n_sub, const int32_t *sub_pos, int n, int tile_bits, int waves, int precision,
                       int32_t *tile_pos, uint32_t *lds_image, int32_t *conflicts);
 /* Union limit of the passes that SV_RULE_TILED plans (8..10; default 10,

@@ -112,8 +112,7 @@ hipError_t make_tile_args(int n_sub, const int (*sub_pos)[4], int n, int tile_bi
 // shape and arithmetic (placement.cpp; make_tile_args calls it).
 void choose_tile_placement(TileArgs &a, int tile_bits, int waves, int prec);
 // Extra LDS cycles (bank conflicts) that the placement of `a` leaves in the
-// block loop of a split pass, by the bank model of choose_tile_placement; 0
-// for FP32.
+// block loop, by the bank model of choose_tile_placement.
 int tile_placement_conflicts(const TileArgs &a, int tile_bits, int waves, int prec);
 // Batched passes (shape (kBatchTileBits, kBatchTileWaves), at most
 // tile_max_blocks() blocks per pass, operands of precision `prec` as
@@ -157,7 +156,7 @@ struct TileNorm {
     int n_in = 0;
     double *out = nullptr;
     int in_scaled = 0, out_scaled = 0;
-    // >= 0 (FP32 and split FP16, one state): the pass reads nothing from
+    // >= 0 (FP32, FP64 and split FP16, one state): the pass reads nothing from
     // HBM; its input is the computational basis state |basis> (amplitude 1
     // there, 0 elsewhere), and it writes the whole state as any pass does.
     int64_t basis = -1;

@@ -144,8 +144,9 @@ void group_tile_passes(const std::vector<Block> &blocks, int n, int precision, s
 // same blocks, in an order that keeps every qubit's own, where those are priced
 // lower: eight cycles on a two-row ladder took 268 us at 14 qubits, 438 at 20
 // and 1486 at 24 as launches, 136, 264 and 743 as passes, with the same error
-// (3.6e-7 at 20 qubits).  Split BF16 stays as it is: its error, 1.4e-5, is of
-// the size of what a caller may look at, and another order gives another one.
+// (3.6e-7 at 20 qubits).  Split BF16 keeps its blocks' order by choice: its
+// error, 1.4e-5 there, is one that a caller sees, and another order of the same
+// roundings gives another.
 int group_dense_passes(std::vector<Launch> &launches, int n, int precision);
 // Replace runs of launches of single gates (PATH_REG, at most 3 qubits) by gate
 // passes (see tile.hip), for states of at least dev::kMinTileQubits qubits.

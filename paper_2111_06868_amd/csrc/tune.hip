@@ -454,7 +454,7 @@ extern "C" int sv_tile_placement(int n_sub, const int32_t *sub_pos, int n, int t
     if (!dev::tile_shape_supported(tile_bits, waves))
         return fail(SV_ERR_ARG, "tile shape (%d bits, %d waves) is not supported", tile_bits, waves);
     if (precision < SV_PREC_FP32 || precision > SV_PREC_SPLIT_BF16X3 || precision == SV_PREC_FP64)
-        return fail(SV_ERR_ARG, "precision %d has no tile passes", precision);
+        return fail(SV_ERR_ARG, "precision %d: the layout reported is that of complex64 passes", precision);
     if (n_sub < 1 || n_sub > dev::kMaxTileSubBlocks) return fail(SV_ERR_ARG, "n_sub = %d", n_sub);
     if (n < tile_bits || n > SV_MAX_QUBITS_C64) return fail(SV_ERR_ARG, "n = %d", n);
     int pos[dev::kMaxTileSubBlocks][4];
