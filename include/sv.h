@@ -706,7 +706,9 @@ int sv_stream_probe(sv_state *s, uint64_t tile_positions, int reps, double *ms_p
  * apply, 2 = generic apply, 3 = MFMA FP32, 4 = MFMA split BF16, 5 = MFMA split
  * FP16, 6 = reductions, 7 = adjoint, 8 = batch, 9 = FP32 tile passes, 10 =
  * split-BF16 tile passes, 11 = split-FP16 tile passes; k is the block size,
- * for tile passes the number of blocks in the launch, and for reductions 1 =
+ * for tile passes the number of blocks in the launch, for the adjoint sweep 3 (a
+ * pass of transition sums) or the block size of a step whose sums and block are
+ * one launch, and for reductions 1 =
  * norm, 2 = inner product, 3 = expectation, 4 = Pauli-sum matvec, 5 =
  * density-matrix trace Tr(rho H), 6 = Kraus outcome weights.  Family 13 = FP64
  * tile passes (complex128), 12 = BF16X3.  A pass that applies several gates of

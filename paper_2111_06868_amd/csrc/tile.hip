@@ -1028,9 +1028,10 @@ __device__ __forceinline__ void apply_stage(TileShared<TB, WAVES, lane_words(kPr
 // 2^-17 (BF16: the state's third part, A_1 X_1), 2^-22 (FP16) and 2^-25
 // (X3) relative to the result.  FP16 passes scale the values per tile
 // (tile_scale; SCALE 0, SCALE 5, which holds the tile scaled in LDS, and SCALE 2,
-// which is SCALE 0 and also reports the workgroup's sum of squares to norm.out) or per pass from the state's norm (norm_scale;
-// SCALE 1, from the sums an earlier pass of the run reported; SCALE 3, the
-// same scale with the state already held scaled in HBM, copied as it is).
+// which is SCALE 0 and also reports the workgroup's sum of squares to norm.out)
+// or per pass from the state's norm (norm_scale; SCALE 1, from the sums an
+// earlier pass of the run reported; SCALE 3, the same scale with the state
+// already held scaled in HBM, copied as it is).
 template <int TB, int WAVES, int PREC, int SCALE, int WHOLE, bool SPREAD>
 __device__ __forceinline__ void tile_loop(TileShared<TB, WAVES, lane_words(PREC)> &sh, float *__restrict__ psi,
                                           const uint32_t *__restrict__ A, const TileArgs &args, uint64_t T,
